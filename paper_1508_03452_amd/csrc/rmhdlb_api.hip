@@ -34,8 +34,7 @@ struct rmhdlb_ctx {
     void* mem;         // the block every buffer below (to result) is carved from
     bool own_mem;      // mem was allocated by rmhdlb_create (else the caller's workspace)
     bool has_state;    // rmhdlb_init_fields or rmhdlb_set_state has run
-    void* buf[2];      // state buffers (distributions, then E_prev and, with the previous-B reading, B_prev)
-    rmhd::StateBuf sb[2];
+    char* buf[2];      // state buffers (layout in rmhdlb_device.h)
     int cur;
     double* scratch;   // 6 N doubles: initial J0 and E'0, then B and E^z of the moments pass
     double* part;      // per-tile partial diagnostics
@@ -95,6 +94,16 @@ int validate(const rmhdlb_params* P) {
 // a driven low-z face, rounded up so that cell 0 stays 64-element aligned.
 int64_t ghost_cells(const Consts& K) { return K.drv ? ((int64_t)2 * K.nx * K.ny + 63) / 64 * 64 : 0; }
 
+// Bytes of one 64-cell chunk of a state buffer: the distributions and E_prev, and with the
+// previous-B reading B_prev.
+int chunk_bytes(int storage, int bprev) {
+    switch (storage) {
+        case RMHDLB_STORE_F64: return bprev ? rmhd::Lay<double>::BYTES_BPREV : rmhd::Lay<double>::BYTES;
+        case RMHDLB_STORE_F32: return bprev ? rmhd::Lay<float>::BYTES_BPREV : rmhd::Lay<float>::BYTES;
+        default: return bprev ? rmhd::Lay<_Float16>::BYTES_BPREV : rmhd::Lay<_Float16>::BYTES;
+    }
+}
+
 Consts make_consts(const rmhdlb_params* P) {
     Consts K;
     memset(&K, 0, sizeof(K));
@@ -120,7 +129,8 @@ Consts make_consts(const rmhdlb_params* P) {
     for (int f = 0; f < 6; ++f) K.fo[f + 1] = K.fo[f] + fsz[f >> 1];
     K.N = (int64_t)P->nx * P->ny * P->nz;
     K.g0 = ghost_cells(K);
-    K.stride = (K.g0 + K.N + 63) / 64 * 64;
+    K.chunks = (K.g0 + K.N + rmhd::CHUNK - 1) / rmhd::CHUNK;
+    K.cb = chunk_bytes(P->storage, P->b_prev);
     const double dt = P->dx / (sqrt(2.0) * P->c);  // dx / dt = sqrt(2) c
     K.c = P->c;
     K.dx = P->dx;
@@ -144,31 +154,17 @@ Consts make_consts(const rmhdlb_params* P) {
     return K;
 }
 
-size_t dist_elem(int storage) {
-    return storage == RMHDLB_STORE_F64 ? 8 : (storage == RMHDLB_STORE_F32 ? 4 : 2);
-}
-size_t efield_elem(int storage) { return storage == RMHDLB_STORE_F64 ? 8 : 4; }
-// The distribution block: 63 arrays of `stride` values in the pair layout (FP64), 65 in the quad and
-// double-quad layouts (FP32, FP16: the rest pair takes a quad with two unused values).
-size_t efield_offset(int storage, int64_t stride) {
-    const int arrays = rmhd::quad_storage(storage) ? rmhd::QUAD_DIST_ARRAYS : rmhd::PAIR_DIST_ARRAYS;
-    const size_t b = (size_t)arrays * (size_t)stride * dist_elem(storage);
-    return (b + 255) / 256 * 256;
-}
-// The field block holds E_prev (3 arrays) and, with the previous-B reading, B_prev (3 more).
-size_t buffer_bytes(const Consts& K, int storage) {
-    return efield_offset(storage, K.stride) + (size_t)(K.bprev ? 6 : 3) * (size_t)K.stride * efield_elem(storage);
-}
+size_t buffer_bytes(const Consts& K) { return (size_t)K.chunks * (size_t)K.cb; }
 
 // The device memory of a context: the buffers below, each at a 256-byte
 // aligned offset of one block.
 enum { M_BUF0, M_BUF1, M_SCRATCH, M_PART, M_PART2, M_NULLP, M_FACEB, M_EZ0, M_AUX, M_RESULT, M_GATE, M_COUNT };
 
-size_t mem_layout(const Consts& K, int storage, size_t off[M_COUNT]) {
+size_t mem_layout(const Consts& K, size_t off[M_COUNT]) {
     const size_t nt = (size_t)rmhd::num_tiles(K);
     const size_t nred = (size_t)((K.N + 255) / 256);  // blocks of the init-reference reduction
     size_t sz[M_COUNT];
-    sz[M_BUF0] = sz[M_BUF1] = buffer_bytes(K, storage);
+    sz[M_BUF0] = sz[M_BUF1] = buffer_bytes(K);
     sz[M_SCRATCH] = sizeof(double) * 6 * (size_t)K.N;  // initial J0 and E'0, then B and E^z of the moments pass
     sz[M_PART] = sizeof(double) * std::max(std::max((size_t)rmhd::NPART * nt, 2 * nred), (size_t)K.nx * K.ny);
     sz[M_PART2] = sizeof(double) * std::max(nt, nred);
@@ -327,7 +323,7 @@ const char* rmhdlb_strerror(int code) {
 size_t rmhdlb_workspace_bytes(const rmhdlb_params* params) {
     if (validate(params) != RMHDLB_OK) return 0;
     size_t off[M_COUNT];
-    return mem_layout(make_consts(params), params->storage, off);
+    return mem_layout(make_consts(params), off);
 }
 
 int rmhdlb_create(const rmhdlb_params* params, void* hip_stream, rmhdlb_ctx** out) {
@@ -337,7 +333,7 @@ int rmhdlb_create(const rmhdlb_params* params, void* hip_stream, rmhdlb_ctx** ou
     if (v != RMHDLB_OK) return v;
     const Consts K = make_consts(params);
     size_t off[M_COUNT];
-    const size_t total = mem_layout(K, params->storage, off);
+    const size_t total = mem_layout(K, off);
     if (params->workspace && (params->workspace_bytes < total || ((uintptr_t)params->workspace & 255) != 0))
         return RMHDLB_EINVAL;
     rmhdlb_ctx* C = new (std::nothrow) rmhdlb_ctx();
@@ -367,12 +363,7 @@ int rmhdlb_create(const rmhdlb_params* params, void* hip_stream, rmhdlb_ctx** ou
         return RMHDLB_EDEVICE;
     }
     char* base = (char*)C->mem;
-    const int64_t g0 = ghost_cells(C->K);
-    for (int b = 0; b < 2; ++b) {
-        C->buf[b] = base + off[M_BUF0 + b];
-        C->sb[b].dist = (char*)C->buf[b] + g0 * dist_elem(C->storage);
-        C->sb[b].efield = (char*)C->buf[b] + efield_offset(C->storage, C->K.stride) + g0 * efield_elem(C->storage);
-    }
+    for (int b = 0; b < 2; ++b) C->buf[b] = base + off[M_BUF0 + b];
     C->scratch = (double*)(base + off[M_SCRATCH]);
     C->part = (double*)(base + off[M_PART]);
     C->part2 = (double*)(base + off[M_PART2]);
@@ -437,7 +428,7 @@ int rmhdlb_init_fields(rmhdlb_ctx* C, const rmhdlb_fields_in* in) {
     } else {
         set_shifts(C->K, C->storage, 0.0, 0.0);
     }
-    hipError_t e = RMHD_DISPATCH(C, launch_init)(ip, C->K, C->scratch, C->sb[0], C->stream);
+    hipError_t e = RMHD_DISPATCH(C, launch_init)(ip, C->K, C->scratch, C->buf[0], C->stream);
     if (e != hipSuccess) return RMHDLB_EDEVICE;
     // references of the reconnection rate: E^z_0 and B0 = max |B|
     if (hipMemcpyAsync(C->ez0, in->E[2], sizeof(double) * (size_t)C->K.N, hipMemcpyDeviceToDevice, C->stream) !=
@@ -454,7 +445,7 @@ int rmhdlb_init_fields(rmhdlb_ctx* C, const rmhdlb_fields_in* in) {
             fp.B[a] = in->B[a];
         }
         for (int b = 0; b < 2; ++b)
-            if (RMHD_DISPATCH(C, launch_ghost)(fp, C->K, C->sb[b], C->stream) != hipSuccess) return RMHDLB_EDEVICE;
+            if (RMHD_DISPATCH(C, launch_ghost)(fp, C->K, C->buf[b], C->stream) != hipSuccess) return RMHDLB_EDEVICE;
     }
     if (C->K.forced && hipMemsetAsync(C->vmax, 0, sizeof(double), C->stream) != hipSuccess)
         return RMHDLB_EDEVICE;  // the force gate starts open
@@ -514,7 +505,7 @@ int rmhdlb_set_driven_face(rmhdlb_ctx* C, const rmhdlb_face_in* face) {
         return RMHDLB_EDEVICE;
     if (bad != 0.0) return RMHDLB_EINVAL;
     for (int b = 0; b < 2; ++b)
-        if (RMHD_DISPATCH(C, launch_ghost)(fp, C->K, C->sb[b], C->stream) != hipSuccess) return RMHDLB_EDEVICE;
+        if (RMHD_DISPATCH(C, launch_ghost)(fp, C->K, C->buf[b], C->stream) != hipSuccess) return RMHDLB_EDEVICE;
     return RMHDLB_OK;
 }
 
@@ -522,7 +513,7 @@ int rmhdlb_step(rmhdlb_ctx* C, int64_t nsteps) {
     if (!C || nsteps < 0) return RMHDLB_EINVAL;
     if (!C->has_state) return RMHDLB_ESTATE;
     for (int64_t s = 0; s < nsteps; ++s) {
-        hipError_t e = RMHD_DISPATCH(C, launch_step)(C->sb[C->cur], C->sb[1 - C->cur], step_consts(C, true), C->tune,
+        hipError_t e = RMHD_DISPATCH(C, launch_step)(C->buf[C->cur], C->buf[1 - C->cur], step_consts(C, true), C->tune,
                                                      C->faceB, C->guess_mode ? C->gt : nullptr, C->stream);
         if (e != hipSuccess) return RMHDLB_EDEVICE;
         C->cur = 1 - C->cur;
@@ -557,7 +548,7 @@ int rmhdlb_moments(rmhdlb_ctx* C, rmhdlb_fields_out* out, rmhdlb_diag* diag) {
     D.ez0 = C->ez0;
     D.b0 = C->aux;
     D.result = C->result;
-    hipError_t e = RMHD_DISPATCH(C, launch_moments)(C->sb[C->cur], step_consts(C, false), op, D,
+    hipError_t e = RMHD_DISPATCH(C, launch_moments)(C->buf[C->cur], step_consts(C, false), op, D,
                                                     C->guess_mode ? C->gt : nullptr, C->stream);
     if (e != hipSuccess) return RMHDLB_EDEVICE;
     double r[RESULT_LEN];
@@ -606,7 +597,7 @@ int rmhdlb_set_guess(rmhdlb_ctx* C, int32_t mode) {
 }
 
 static int sample_cells(rmhdlb_ctx* C, int ns, double* F, double* T, double* part, double sums[rmhd::SAMPLE_SUMS]) {
-    hipError_t e = RMHD_DISPATCH(C, launch_guess_samples)(C->sb[C->cur], C->K, C->faceB, ns, F, T, part, C->result,
+    hipError_t e = RMHD_DISPATCH(C, launch_guess_samples)(C->buf[C->cur], C->K, C->faceB, ns, F, T, part, C->result,
                                                           C->stream);
     if (e != hipSuccess ||
         hipMemcpyAsync(sums, C->result, sizeof(double) * rmhd::SAMPLE_SUMS, hipMemcpyDeviceToHost, C->stream) !=
@@ -880,7 +871,7 @@ int rmhdlb_autotune(rmhdlb_ctx* C, int32_t* px_out, int32_t* zb_out, int32_t* zg
                 // into, with this step's number and from this step's state: what the real step records
                 rmhd::Consts Kt = step_consts(C, true);
                 Kt.gcount = nullptr;  // trials are not steps
-                return RMHD_DISPATCH(C, launch_step)(C->sb[C->cur], C->sb[1 - C->cur], Kt, t, C->faceB,
+                return RMHD_DISPATCH(C, launch_step)(C->buf[C->cur], C->buf[1 - C->cur], Kt, t, C->faceB,
                                                      C->guess_mode ? C->gt : nullptr, C->stream);
             }, &ms);
             if (rc != RMHDLB_OK) return rc;
@@ -979,10 +970,7 @@ int batch_table(rmhdlb_batch* B) {
         rmhdlb_ctx* C = B->ctx[i];
         rmhd::BatchInst& I = B->host[i];
         I.K = C->K;
-        for (int b = 0; b < 2; ++b) {
-            I.dist[b] = C->sb[b].dist;
-            I.efield[b] = C->sb[b].efield;
-        }
+        for (int b = 0; b < 2; ++b) I.buf[b] = C->buf[b];
         I.faceB = C->faceB;
         I.zb = std::max(1, std::min(C->tune.zb, C->K.nz));
         I.yw = B->yw;
@@ -1281,14 +1269,14 @@ int64_t rmhdlb_state_len(const rmhdlb_ctx* C) { return C ? (int64_t)rmhd::state_
 int rmhdlb_get_state(rmhdlb_ctx* C, double* dst) {
     if (!C || !dst) return RMHDLB_EINVAL;
     if (!C->has_state) return RMHDLB_ESTATE;
-    hipError_t e = RMHD_DISPATCH(C, launch_export)(C->sb[C->cur], dst, C->K, C->stream);
+    hipError_t e = RMHD_DISPATCH(C, launch_export)(C->buf[C->cur], dst, C->K, C->stream);
     if (e != hipSuccess || hipStreamSynchronize(C->stream) != hipSuccess) return RMHDLB_EDEVICE;
     return RMHDLB_OK;
 }
 
 int rmhdlb_set_state(rmhdlb_ctx* C, const double* src) {
     if (!C || !src) return RMHDLB_EINVAL;
-    hipError_t e = RMHD_DISPATCH(C, launch_import)(src, C->sb[C->cur], C->K, C->stream);
+    hipError_t e = RMHD_DISPATCH(C, launch_import)(src, C->buf[C->cur], C->K, C->stream);
     if (e != hipSuccess || hipStreamSynchronize(C->stream) != hipSuccess) return RMHDLB_EDEVICE;
     C->has_state = true;
     return C->guess_mode == RMHDLB_GUESS_MLP ? arm_gate(C, false) : RMHDLB_OK;

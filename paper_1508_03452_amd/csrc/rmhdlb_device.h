@@ -44,8 +44,7 @@ constexpr int BHX[QH] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, -1, 1, 
 constexpr int BHY[QH] = {0, 0, 0, 0, 0, 0, 0, 0, 1, -1, 1, -1, 1, -1, 1, -1, 0, 0, 0, 0, 0, 0, 0, 0};
 constexpr int BHZ[QH] = {-1, 1, -1, 1, -1, 1, -1, 1, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
 
-// Offsets of the state arrays (each `stride` values long); E_prev (OFF_E..)
-// lives in its own block of the buffer.
+// First array of each group in the raw (interface) state.
 constexpr int OFF_F = 0, OFF_G = Q, OFF_H = 2 * Q, OFF_E = 2 * Q + QH + 1;
 
 // --------------------------------------------------------------- constants
@@ -59,8 +58,9 @@ struct Consts {
     int band;            // half-width in rows of the reconnection null search band
     int64_t fo[7];       // offsets of the six face arrays of adjusted normal B (x lo, x hi, y lo, ...), fo[6] = total
     int64_t N;           // cells
-    int64_t stride;      // values per state array (ghost planes + N, rounded up)
-    int64_t g0;          // ghost cells in front of cell 0 of every array
+    int64_t chunks;      // 64-position chunks of a state buffer (ghost planes + N, rounded up)
+    int cb;              // bytes of a chunk
+    int64_t g0;          // position of cell 0: the ghost cells of a driven face in front of it, rounded up to 64
     double c, dx, eps0;
     double cour;         // Courant number along a link: kappa c dt / dx
     double kv;           // bulk-viscosity coefficient alpha c dt / dx
@@ -81,7 +81,7 @@ struct Consts {
     double slope;        // weight of the limited slope in a face value: 1/2 (MUSCL) or (1 - cour)/2 (Lax-Wendroff)
     int coll;            // f collision: 0 explicit, 1 the printed semi-implicit form
     int flux;            // face values: 0 MUSCL, 1 limited Lax-Wendroff
-    int bprev;           // 1: the previous step's B in the recovery and f_eq; the field block then holds
+    int bprev;           // 1: the previous step's B in the recovery and f_eq; a chunk then holds
                          // E_prev[3] and B_prev[3] (else E_prev[3] only)
     // external force density (3 arrays of N, cell order) and its gate: on while
     // the previous step's largest |beta| (*vmax_prev) is below fgate (<= 0: always)
@@ -101,47 +101,56 @@ struct Consts {
     int64_t* gcount;     // steps that ran the network (null: not counted)
 };
 
-// Layout of the distributions in a state buffer.  Element indices are
-// relative to the buffer's distribution pointer, which sits g0 elements into
-// the buffer (the ghost planes of a driven face take the g0 positions in
-// front of cell 0 of every array; position p = g0 + c of cell c).
-//  - FP64 (pair layout): direction i as pairs (f_i, g_i), pair of cell c at
-//    2 (i S + p); Maxwell population k as its own array at (38 + k) S + p.
+// Layout of a state buffer: chunks of 64 consecutive positions (position
+// p = g0 + c of cell c; the ghost planes of a driven face take the g0
+// positions in front of cell 0).  A chunk holds every array of its 64 cells,
+// one after the other, so that all a wavefront reads of one row of cells is
+// one contiguous block of 9-34 KB.  With one array per population across the
+// whole grid instead, a wavefront touched more than 150 pages per plane: in the
+// FP64 step 3.6 % of the L1 translations missed and another 30 % waited on
+// such a miss, and even a plain pass over the 66 arrays (no stencil) took
+// 7.38 ms where this order takes 6.40 (256x256x512).
+// Byte offsets in a chunk (value of lane l = p % 64):
+//  - FP64 (pair layout): direction i as pairs (f_i, g_i) at 1024 i + 16 l, then
+//    the 25 Maxwell populations at 512 k + 8 l, then E_prev.
 //  - FP32 (quad layout): direction slot s = 1..9 holds the opposite
 //    directions 2s - 1 (e) and 2s (-e) as quads (f_{2s-1}, g_{2s-1}, f_{2s},
-//    g_{2s}) at 4 (s S + p), slot 0 the rest pair (f_0, g_0, 0, 0); the moving
-//    Maxwell populations 2m and 2m + 1, which stream from the same cell, as
-//    pairs at 40 S + 2 (m S + p), the rest one at 64 S + p.  One lane then
-//    reads both directions of a slot, and both populations of a pair, with one
-//    load per stencil point.
+//    g_{2s}) at 1024 s + 16 l, slot 0 the rest quad (f_0, g_0, h_rest, 0);
+//    the moving Maxwell populations 2m and 2m + 1, which stream from the same
+//    cell, as pairs; then E_prev.  One lane then reads both directions of a
+//    slot, and both populations of a pair, with one load per stencil point.
 //  - FP16 (double-quad layout): the quads of two slots side by side in one
 //    16-byte record, record r = 0..3 holding slots 2r + 1 and 2r + 2, record
-//    4 slot 9 and the rest pair (f_0, g_0, 0, 0), at 8 (r S + p); the Maxwell
-//    populations as in the quad layout.  The centre point and the six
-//    Laplacian points of two slots then take one load.
-constexpr int QUAD_SLOTS = 10;           // quad layout: 40 S elements of f and g
-constexpr int QUAD_DIST_ARRAYS = 65;     // quad layout: distribution block of 65 S elements
-constexpr int PAIR_DIST_ARRAYS = 63;     // pair layout: 38 S of f, g and 25 S of h
-__host__ __device__ inline int64_t quad_index(const Consts& K, int slot, int64_t c) {
-    return 4 * ((int64_t)slot * K.stride + c) + 3 * K.g0;
-}
-__host__ __device__ inline int64_t hpair_index(const Consts& K, int m, int64_t c) {
-    return 4 * (int64_t)QUAD_SLOTS * K.stride + 2 * ((int64_t)m * K.stride + c) + K.g0;
-}
-__host__ __device__ inline int64_t hrest_quad_index(const Consts& K, int64_t c) {
-    return (4 * (int64_t)QUAD_SLOTS + QH) * K.stride + c;
+//    4 slot 9 and the rest quad, at 1024 r + 16 l; the Maxwell pairs as in the
+//    quad layout.  The centre point and the six Laplacian points of two slots
+//    then take one load.
+// E_prev takes three arrays (FP64, or FP32 in the FP32 and FP16 forms) and
+// the previous-B reading three more for B_prev; K.cb is the chunk's size.
+constexpr int CHUNK = 64;
+template <typename TS>
+struct Lay {
+    static constexpr int REC = 16;                                       // bytes of a cell's f-g record
+    static constexpr int RECORDS = sizeof(TS) == 8 ? Q : (sizeof(TS) == 4 ? 10 : 5);
+    static constexpr int HREC = sizeof(TS) == 8 ? 8 : 2 * (int)sizeof(TS);  // bytes of a Maxwell record
+    static constexpr int HRECORDS = sizeof(TS) == 8 ? QH + 1 : QH / 2;
+    static constexpr int EREC = sizeof(TS) == 8 ? 8 : 4;
+    static constexpr int H = CHUNK * REC * RECORDS;
+    static constexpr int E = H + CHUNK * HREC * HRECORDS;
+    static constexpr int BYTES = E + 3 * CHUNK * EREC;
+    static constexpr int BYTES_BPREV = BYTES + 3 * CHUNK * EREC;
+};
+// Byte offset of the lane of position p in an array of W-byte records at the start of its chunk.
+template <int W>
+__host__ __device__ __forceinline__ int64_t lane_off(const Consts& K, int p) {
+    return (int64_t)((uint64_t)((uint32_t)p >> 6) * (uint32_t)K.cb) + (p & (CHUNK - 1)) * W;
 }
 // Direction i of the quad layout: its slot and its position (0 or 2) in the quad.
 __host__ __device__ constexpr int quad_slot(int i) { return (i + 1) / 2; }
 __host__ __device__ constexpr int quad_pos(int i) { return (i == 0 || (i & 1)) ? 0 : 2; }
-// Double-quad layout: record r of cell c, and slot s's record and offset (0 or 4) in it.
+// Double-quad layout: slot s's record and offset (0 or 4 elements) in it.
 constexpr int DQUAD_RECORDS = 5;
-__host__ __device__ inline int64_t dquad_index(const Consts& K, int r, int64_t c) {
-    return 8 * ((int64_t)r * K.stride + c) + 7 * K.g0;
-}
 __host__ __device__ constexpr int dquad_rec(int s) { return s == 0 ? 4 : (s - 1) / 2; }
 __host__ __device__ constexpr int dquad_off(int s) { return s == 0 ? 4 : (s == 9 ? 0 : ((s - 1) & 1) * 4); }
-static_assert(8 * DQUAD_RECORDS == 4 * QUAD_SLOTS, "the Maxwell block follows the same 40 S elements");
 
 // The pairings the quad layout relies on: slot s holds e_{2s-1} and its opposite; the Maxwell
 // populations 2m and 2m + 1 share the streaming offset and have opposite e and b.
@@ -170,6 +179,10 @@ __device__ __forceinline__ V minmod(V a, V b) {
     if (a * b <= V(0)) return V(0);
     return fabs(a) < fabs(b) ? a : b;
 }
+
+// |b|^2 with its rounding fixed: left to the compiler, which of the products
+// is fused depends on what else uses them, and with it the last bit of gamma.
+__device__ __forceinline__ double norm2(const double b[3]) { return fma(b[2], b[2], fma(b[0], b[0], b[1] * b[1])); }
 
 // Solve (Pi + lam I) y = S for the symmetric 3x3 Pi (xx, yy, zz, xy, xz, yz)
 // by cofactors.

@@ -110,13 +110,11 @@ struct StepTuning {
     int yw = 1;
 };
 
-// One instance of a batched step: its constants, both state buffers (cell
-// 0 of the distributions and of E_prev), its face-pass output, its launch
-// geometry and its first block and face-pass thread in the batched launches.
+// One instance of a batched step: its constants, both state buffers, its
+// face-pass output, its launch geometry and its first block and face-pass thread in the batched launches.
 struct BatchInst {
     Consts K;
-    void* dist[2];
-    void* efield[2];
+    char* buf[2];
     double* faceB;
     int tiles_x, ncol, zb, yw, nblk;
     int64_t blk0;
@@ -148,13 +146,6 @@ struct TrainArgs {
 };
 
 
-
-// Device pointers of one state buffer: the 63 distribution arrays and the 3
-// E_prev arrays (each `stride` values long).
-struct StateBuf {
-    void* dist;
-    void* efield;
-};
 
 // Storage type -> (E_prev storage type, arithmetic type of the step).
 template <typename TS>
@@ -190,18 +181,18 @@ struct DiagBufs {
 // gt: inference tables of the learned recovery guess, or nullptr for the
 // plain recovery (Newton from E_f).
 template <typename TS>
-hipError_t launch_step(const StateBuf& src, const StateBuf& dst, const Consts& K, const StepTuning& tune,
+hipError_t launch_step(const char* src, char* dst, const Consts& K, const StepTuning& tune,
                        double* faceB, const GuessTables* gt, hipStream_t s);
 template <typename TS>
-hipError_t launch_moments(const StateBuf& src, const Consts& K, const OutPtrs& out, const DiagBufs& D,
+hipError_t launch_moments(const char* src, const Consts& K, const OutPtrs& out, const DiagBufs& D,
                           const GuessTables* gt, hipStream_t s);
 hipError_t launch_init_bmax(const InPtrs& in, const Consts& K, double* part, double* b0, hipStream_t s);
 hipError_t launch_face_check(const FacePtrs& in, const Consts& K, double* part, double* result, hipStream_t s);
 template <typename TS>
-hipError_t launch_ghost(const FacePtrs& in, const Consts& K, const StateBuf& dst, hipStream_t s);
+hipError_t launch_ghost(const FacePtrs& in, const Consts& K, char* dst, hipStream_t s);
 hipError_t launch_init_ref(const InPtrs& in, const Consts& K, double* part, double* result, hipStream_t s);
 template <typename TS>
-hipError_t launch_face_b(const StateBuf& src, const Consts& K, double* faceB, hipStream_t s);
+hipError_t launch_face_b(const char* src, const Consts& K, double* faceB, hipStream_t s);
 // Launch geometry of the fused step for a tile width px, zb planes per block
 // and zg blocks per column and chunk of zg * zb planes: tiles along x,
 // columns, blocks.
@@ -224,18 +215,18 @@ template <typename TS>
 hipError_t launch_batch_persistent(const BatchInst* dev, int ninst, int total_blocks, int px, int waves, int parity,
                                    int nsteps, int* next, hipStream_t s);
 template <typename TS>
-hipError_t launch_guess_samples(const StateBuf& src, const Consts& K, double* faceB, int ns, double* F, double* T,
+hipError_t launch_guess_samples(const char* src, const Consts& K, double* faceB, int ns, double* F, double* T,
                                 double* part, double* result, hipStream_t s);
 hipError_t launch_guess_normalise(const double* F, const double* T, int ns, const Norm4& nm, float* X, float* Y,
                                   hipStream_t s);
 hipError_t launch_train(const TrainArgs& A, hipStream_t s);
 template <typename TS>
-hipError_t launch_init(const InPtrs& in, const Consts& K, double* scr, const StateBuf& dst, hipStream_t s);
+hipError_t launch_init(const InPtrs& in, const Consts& K, double* scr, char* dst, hipStream_t s);
 // Plain copy of n16 16-byte words (the HBM reference rate).
 hipError_t launch_copy16(const void* src, void* dst, int64_t n16, hipStream_t s);
 template <typename TS>
-hipError_t launch_export(const StateBuf& src, double* dst, const Consts& K, hipStream_t s);
+hipError_t launch_export(const char* src, double* dst, const Consts& K, hipStream_t s);
 template <typename TS>
-hipError_t launch_import(const double* src, const StateBuf& dst, const Consts& K, hipStream_t s);
+hipError_t launch_import(const double* src, char* dst, const Consts& K, hipStream_t s);
 
 }  // namespace rmhd

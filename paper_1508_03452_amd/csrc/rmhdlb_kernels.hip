@@ -1,14 +1,13 @@
 // rmhdlb_kernels.hip -- gfx950 kernels of the resistive relativistic MHD
 // lattice Boltzmann step (arXiv:1508.03452, Sec. III).
 //
-// Layout in HBM: structure of arrays, x fastest.  A state buffer holds the
-// distributions F[0..18], G[0..18], h*[0..24] of storage type TS, interleaved
-// as (f_i, g_i) pairs (FP64, 63 arrays), as quads of opposite directions
-// (FP32, 65 arrays) or as records of two such quads (FP16, 65 arrays; the
-// layouts are described in rmhdlb_device.h),
-// then (256-byte aligned) the 3 E_prev arrays of type TE (TS, or FP32 when TS
-// is FP16); two buffers, read one and write the other.  The stored state is post-collision.  On the FP32 and FP16
-// storage paths F and G are stored as deviations from w_i E_ref and
+// Layout in HBM: chunks of 64 cells (x fastest), each holding every array of
+// its cells: the distributions F[0..18], G[0..18], h*[0..24] of storage type
+// TS as (f_i, g_i) pairs (FP64), as quads of opposite directions (FP32) or as
+// records of two such quads (FP16), then E_prev of type TE (TS, or FP32 when
+// TS is FP16); the layouts are described in rmhdlb_device.h.  Two buffers, read
+// one and write the other.  The stored state is post-collision.  On the FP32
+// and FP16 storage paths F and G are stored as deviations from w_i E_ref and
 // w'_i N_ref (references from the initial fields) and the step runs in FP32
 // arithmetic, with the recovery and the Ohm solve in FP64.
 #include <hip/hip_cooperative_groups.h>
@@ -22,73 +21,80 @@ namespace rmhd {
 constexpr int TX = 64, TY = 4, TPB = TX * TY;
 
 template <typename T>
-__device__ __forceinline__ double ld(const T* __restrict__ p, int64_t i) {
-    return static_cast<double>(p[i]);
-}
+using vec2 = T __attribute__((ext_vector_type(2)));
+template <typename T>
+using vec4 = T __attribute__((ext_vector_type(4)));
 
+// The value of type T at byte offset o of a state buffer, as V.
 template <typename V, typename T>
-__device__ __forceinline__ V ldv(const T* __restrict__ p, int64_t i) {
-    return static_cast<V>(p[i]);
+__device__ __forceinline__ V ldv(const char* __restrict__ s, int64_t o) {
+    return static_cast<V>(*reinterpret_cast<const T*>(s + o));
+}
+template <typename T>
+__device__ __forceinline__ double ld(const char* __restrict__ s, int64_t o) {
+    return ldv<double, T>(s, o);
 }
 
 // Loads of values that no other cell of the step reads (each streamed h* is
 // pulled by exactly one cell): the non-temporal hint keeps them from
-// evicting the stencil lines that the neighbours' loads will hit.  Used for
-// 4- and 8-byte values only: a 2-byte array shares each cache line between
-// two wavefronts, and the hint then costs the second one a refetch.
+// evicting the stencil lines that the neighbours' loads will hit.
 template <typename V, typename T>
-__device__ __forceinline__ V ldv_once(const T* __restrict__ p, int64_t i) {
-    if constexpr (sizeof(T) >= 4)
-        return static_cast<V>(__builtin_nontemporal_load(p + i));
-    else
-        return static_cast<V>(p[i]);
-}
-
-// Stores of the next state are never read again in this step: the
-// non-temporal hint keeps them from evicting the stencil lines from L2.
-template <bool NT, typename T, typename V>
-__device__ __forceinline__ void st(T* __restrict__ p, V v) {
-    if constexpr (NT)
-        __builtin_nontemporal_store(static_cast<T>(v), p);
-    else
-        *p = static_cast<T>(v);
-}
-
-// f and g of one direction are stored interleaved: the pair (f_i, g_i) of
-// cell c sits at fg[2 (i S + c)], fg = dist + g0 (the f-g block spans the
-// first 38 S values; ghost cells in front of cell 0 take 2 g0 of them).
-// Both use the same transport stencil, so one vector load serves both.
-template <typename T>
-using vec2 = T __attribute__((ext_vector_type(2)));
-
-__device__ __forceinline__ int64_t fg_index(const Consts& K, int i, int64_t c) {
-    return 2 * ((int64_t)i * K.stride + c) + K.g0;
+__device__ __forceinline__ V ldv_once(const char* __restrict__ s, int64_t o) {
+    return static_cast<V>(__builtin_nontemporal_load(reinterpret_cast<const T*>(s + o)));
 }
 
 template <typename V, typename T>
-__device__ __forceinline__ vec2<V> ldv2(const T* __restrict__ p, int64_t i) {
-    const vec2<T> v = *reinterpret_cast<const vec2<T>*>(p + i);
+__device__ __forceinline__ vec2<V> ldv2(const char* __restrict__ s, int64_t o) {
+    const vec2<T> v = *reinterpret_cast<const vec2<T>*>(s + o);
     vec2<V> r;
     r.x = static_cast<V>(v.x);
     r.y = static_cast<V>(v.y);
     return r;
 }
 
+template <typename V, typename T>
+__device__ __forceinline__ vec4<V> ldv4(const char* __restrict__ s, int64_t o) {
+    const vec4<T> v = *reinterpret_cast<const vec4<T>*>(s + o);
+    vec4<V> r;
+    r.x = static_cast<V>(v.x);
+    r.y = static_cast<V>(v.y);
+    r.z = static_cast<V>(v.z);
+    r.w = static_cast<V>(v.w);
+    return r;
+}
+
+// Stores of the next state are never read again in this step: the
+// non-temporal hint keeps them from evicting the stencil lines from L2.
+template <bool NT, typename T>
+__device__ __forceinline__ void put_raw(char* __restrict__ d, int64_t o, T v) {
+    if constexpr (NT)
+        __builtin_nontemporal_store(v, reinterpret_cast<T*>(d + o));
+    else
+        *reinterpret_cast<T*>(d + o) = v;
+}
 template <bool NT, typename T, typename V>
-__device__ __forceinline__ void st2(T* __restrict__ p, V f, V g) {
+__device__ __forceinline__ void st(char* __restrict__ d, int64_t o, V v) {
+    put_raw<NT, T>(d, o, static_cast<T>(v));
+}
+template <bool NT, typename T, typename V>
+__device__ __forceinline__ void st2(char* __restrict__ d, int64_t o, V f, V g) {
     vec2<T> v;
     v.x = static_cast<T>(f);
     v.y = static_cast<T>(g);
-    if constexpr (NT)
-        __builtin_nontemporal_store(v, reinterpret_cast<vec2<T>*>(p));
-    else
-        *reinterpret_cast<vec2<T>*>(p) = v;
+    put_raw<NT>(d, o, v);
+}
+template <bool NT, typename T, typename V>
+__device__ __forceinline__ void st4(char* __restrict__ d, int64_t o, const vec4<V>& q) {
+    vec4<T> v;
+    v.x = static_cast<T>(q.x);
+    v.y = static_cast<T>(q.y);
+    v.z = static_cast<T>(q.z);
+    v.w = static_cast<T>(q.w);
+    put_raw<NT>(d, o, v);
 }
 
 // FP64 storage uses the pair layout (two lanes per cell), FP32 the quad and
 // FP16 the double-quad layout (one lane per cell; see rmhdlb_device.h).
-// Element indices of f_i, g_i and h_k of cell c (c may be a ghost cell of a
-// driven face, down to -g0), for the kernels that read or write single values.
 template <typename TS>
 constexpr bool quad_layout() {  // one lane per cell
     return sizeof(TS) != 8;
@@ -97,31 +103,37 @@ template <typename TS>
 constexpr bool dquad_layout() {
     return sizeof(TS) == 2;
 }
-// Element index of the quad of slot s of cell c in the quad and double-quad layouts.
+// Byte offsets of single values at position p, for the kernels that read or
+// write them one by one: the f-g record of direction i (quad: of its slot's half of the record), ...
 template <typename TS>
-__host__ __device__ __forceinline__ int64_t slot_index(const Consts& K, int s, int64_t c) {
-    if constexpr (dquad_layout<TS>())
-        return dquad_index(K, dquad_rec(s), c) + dquad_off(s);
-    else
-        return quad_index(K, s, c);
+__host__ __device__ constexpr int rec_off(int i) {  // ... within the chunk, without the lane
+    if (dquad_layout<TS>())
+        return CHUNK * 16 * dquad_rec(quad_slot(i)) + 2 * (dquad_off(quad_slot(i)) + quad_pos(i));
+    if (quad_layout<TS>()) return CHUNK * 16 * quad_slot(i) + 4 * quad_pos(i);
+    return CHUNK * 16 * i;
 }
 template <typename TS>
-__device__ __forceinline__ int64_t f_at(const Consts& K, int i, int64_t c) {
-    if constexpr (quad_layout<TS>())
-        return slot_index<TS>(K, quad_slot(i), c) + quad_pos(i);
-    else
-        return fg_index(K, i, c);
+__device__ __forceinline__ int64_t f_at(const Consts& K, int i, int p) {
+    return lane_off<16>(K, p) + rec_off<TS>(i);
 }
 template <typename TS>
-__device__ __forceinline__ int64_t g_at(const Consts& K, int i, int64_t c) {
-    return f_at<TS>(K, i, c) + 1;
+__device__ __forceinline__ int64_t g_at(const Consts& K, int i, int p) {
+    return f_at<TS>(K, i, p) + (int)sizeof(TS);
 }
 template <typename TS>
-__device__ __forceinline__ int64_t h_at(const Consts& K, int k, int64_t c) {
-    if constexpr (quad_layout<TS>())
-        return k < QH ? hpair_index(K, k / 2, c) + (k & 1) : hrest_quad_index(K, c);
-    else
-        return (int64_t)(OFF_H + k) * K.stride + c;
+__device__ __forceinline__ int64_t h_at(const Consts& K, int k, int p) {
+    if constexpr (quad_layout<TS>()) {
+        if (k == QH) return f_at<TS>(K, 0, p) + 2 * (int)sizeof(TS);  // third value of the rest quad
+        return lane_off<Lay<TS>::HREC>(K, p) + Lay<TS>::H + CHUNK * Lay<TS>::HREC * (k / 2) +
+               (k & 1) * (int)sizeof(TS);
+    } else {
+        return lane_off<8>(K, p) + Lay<TS>::H + CHUNK * 8 * k;
+    }
+}
+// E_prev (a = 0..2) and, with the previous-B reading, B_prev (a = 3..5)
+template <typename TS>
+__device__ __forceinline__ int64_t e_at(const Consts& K, int a, int p) {
+    return lane_off<Lay<TS>::EREC>(K, p) + Lay<TS>::E + CHUNK * Lay<TS>::EREC * a;
 }
 
 // Shift of the stored f, g of direction i (0 on the plain FP64 path).
@@ -332,7 +344,7 @@ __device__ __forceinline__ void solve_cell(const Consts& K, CellSol& M, const do
         const double lam0 = guess_lambda<GM>(gt, Ef, S, Pi, M.N0, gate);
         M.iters = recover_from_guess(Ef, S, Pi, lam0, lam, M.beta, M.fallback);
     }
-    const double b2 = M.beta[0] * M.beta[0] + M.beta[1] * M.beta[1] + M.beta[2] * M.beta[2];
+    const double b2 = norm2(M.beta);
     M.gam = 1.0 / sqrt(1.0 - b2);
     M.n = M.N0 / M.gam;
     M.p = K.gm1 * (lam - M.n * c2);
@@ -376,21 +388,19 @@ __device__ __forceinline__ void solve_cell(const Consts& K, CellSol& M, const do
 // shift of a stored array is constant in space, so it transports to itself
 // and is added back after the transport.
 template <int GM, typename TS, typename TE>
-__device__ __forceinline__ void macroscopic(const TS* __restrict__ src, const TE* __restrict__ esrc,
-                                            const double* __restrict__ faceB, const GuessTables* __restrict__ gt,
-                                            const Consts& K, int cell, const Nbr& nb, int x, int y, int z, Macro& M) {
+__device__ __forceinline__ void macroscopic(const char* __restrict__ src, const double* __restrict__ faceB,
+                                            const GuessTables* __restrict__ gt, const Consts& K, int cell,
+                                            const Nbr& nb, int x, int y, int z, Macro& M) {
+    const int pos = (int)K.g0 + cell;
     M.T00 = 0.0;
     M.N0 = 0.0;
     double t0x = 0, t0y = 0, t0z = 0, txx = 0, tyy = 0, tzz = 0, txy = 0, txz = 0, tyz = 0;
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
         auto fg = [&](int o) {
-            vec2<double> r;
-            r.x = ld(src, f_at<TS>(K, i, (int64_t)cell + o));
-            r.y = ld(src, g_at<TS>(K, i, (int64_t)cell + o));
-            return r;
+            return ldv2<double, TS>(src, f_at<TS>(K, i, pos + o));
         };
-        auto fo = [&](int o) { return ld(src, f_at<TS>(K, i, (int64_t)cell + o)); };
+        auto fo = [&](int o) { return ld<TS>(src, f_at<TS>(K, i, pos + o)); };
         const vec2<double> c0 = fg(0);
         const double f0 = c0.x, g0 = c0.y;
         double fv = f0, gv = g0;
@@ -444,7 +454,7 @@ __device__ __forceinline__ void macroscopic(const TS* __restrict__ src, const TE
     double ehx = 0, ehy = 0, ehz = 0, bx = 0, by = 0, bz = 0, hs = 0;
 #pragma unroll
     for (int k = 0; k < QH; ++k) {
-        const double h = ld(src, h_at<TS>(K, k, (int64_t)cell + nb.at(-SX[k], -SY[k], -SZ[k])));
+        const double h = ld<TS>(src, h_at<TS>(K, k, pos + nb.at(-SX[k], -SY[k], -SZ[k])));
         M.H[k] = h;
         hs += h;
         if (EHX[k]) ehx += EHX[k] * h;
@@ -454,7 +464,7 @@ __device__ __forceinline__ void macroscopic(const TS* __restrict__ src, const TE
         if (BHY[k]) by += BHY[k] * h;
         if (BHZ[k]) bz += BHZ[k] * h;
     }
-    M.H[QH] = ld(src, h_at<TS>(K, QH, cell));
+    M.H[QH] = ld<TS>(src, h_at<TS>(K, QH, pos));
     const double ec = K.c * INV_SQRT2;  // |e_k| / |ehat_k|
     M.Epr[0] = ec * ehx;
     M.Epr[1] = ec * ehy;
@@ -465,21 +475,19 @@ __device__ __forceinline__ void macroscopic(const TS* __restrict__ src, const TE
     M.rho = M.H[QH] + hs;
 
     // previous E and its Gauss charge
-    const TE* __restrict__ e0 = esrc + cell;
-    const TE* __restrict__ e1 = esrc + K.stride + cell;
-    const TE* __restrict__ e2 = esrc + 2 * K.stride + cell;
-    M.Ep[0] = ld(e0, 0);
-    M.Ep[1] = ld(e1, 0);
-    M.Ep[2] = ld(e2, 0);
+    auto Ea = [&](int a, int o) { return ld<TE>(src, e_at<TS>(K, a, pos + o)); };
+    M.Ep[0] = Ea(0, 0);
+    M.Ep[1] = Ea(1, 0);
+    M.Ep[2] = Ea(2, 0);
     M.rho_g = K.eps0 * K.inv_2dx *
-              ((ld(e0, nb.at(1, 0, 0)) - ld(e0, nb.at(-1, 0, 0))) + (ld(e1, nb.at(0, 1, 0)) - ld(e1, nb.at(0, -1, 0))) +
-               (ld(e2, nb.at(0, 0, 1)) - ld(e2, nb.at(0, 0, -1))));
+              ((Ea(0, nb.at(1, 0, 0)) - Ea(0, nb.at(-1, 0, 0))) + (Ea(1, nb.at(0, 1, 0)) - Ea(1, nb.at(0, -1, 0))) +
+               (Ea(2, nb.at(0, 0, 1)) - Ea(2, nb.at(0, 0, -1))));
 
     if (K.divb) apply_face_b(K, faceB, x, y, z, M.B);
     if (K.bprev) {
         double Bp[3];
 #pragma unroll
-        for (int a = 0; a < 3; ++a) Bp[a] = ld(esrc + (int64_t)(3 + a) * K.stride + cell, 0);
+        for (int a = 0; a < 3; ++a) Bp[a] = Ea(3 + a, 0);
         solve_cell<GM>(K, M, Bp, gt);
     } else {
         solve_cell<GM>(K, M, M.B, gt);
@@ -502,7 +510,7 @@ struct FeqCellT {
         A1 = (V)(1.0 + (3.0 * p - eps) / (p + eps));
         Bc = (V)(361.0 * (3.0 * p - eps) / (33.0 * (p + eps)));
         g2 = (V)(gam * gam);
-        b2 = (V)(bta[0] * bta[0] + bta[1] * bta[1] + bta[2] * bta[2]);
+        b2 = (V)norm2(bta);
         double cb[3];
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
@@ -583,37 +591,32 @@ __device__ __forceinline__ void static_for(Fn&& fn) {
 // value is shift + transport(d); the moments add the exact sums of the shifts;
 // the collisions write the new deviations directly.
 constexpr int PTPB = 256;  // threads of a fused-step block: 128 cells, two lanes each
-// Waves per SIMD the fused kernel is compiled for: two for the FP64 and
-// FP32 forms (they lose more to spills at three than they gain: FP32 4 %
-// slower), three for FP16 storage (plain FP16 3.6 % faster on the flare box
-// than two and 31 % faster than four; with the learned guess, once the lane
-// coordinates are recomputed per plane, 2.5 % faster than two).
-#ifndef RMHDLB_WAVES
-#define RMHDLB_WAVES 2
-#endif
-#ifndef RMHDLB_WAVES_F16
-#define RMHDLB_WAVES_F16 2
-#endif
-template <typename TS, int GM>
-constexpr int fused_waves() {
-    return sizeof(TS) == 2 ? RMHDLB_WAVES_F16 : RMHDLB_WAVES;
-}
-// f/g slots whose loads may be in flight together, per storage type
-// (measured on the flare box: 2 for FP64, where 1 is 18 % and 3 is 25 %
-// slower; 3 for FP32, where 2 is 4 % and 4 is 8 % slower; 3 for FP16, 1.5 %
-// faster than 2 with and without the guess, and 1-2 % faster than 4, 5, 9)
-#ifndef RMHDLB_GROUP_F64
-#define RMHDLB_GROUP_F64 2
-#endif
-#ifndef RMHDLB_GROUP_F32
-#define RMHDLB_GROUP_F32 3
-#endif
-#ifndef RMHDLB_GROUP_F16
-#define RMHDLB_GROUP_F16 3
-#endif
-template <typename TS>
-constexpr int pin_group() {
-    return sizeof(TS) == 8 ? RMHDLB_GROUP_F64 : (sizeof(TS) == 4 ? RMHDLB_GROUP_F32 : RMHDLB_GROUP_F16);
+// Waves per SIMD the fused kernels are compiled for: two in every form, which
+// leaves a wave the 256 registers that the cell's populations and two records'
+// loads in flight take (three spilled: FP32 batch kernel 67 registers).
+constexpr int FUSED_WAVES = 2;
+// Link of a slot as the step walks it (direction 2s - 1).
+template <int S>
+struct Link {
+    static constexpr int x = EX[2 * S - 1], y = EY[2 * S - 1], z = EZ[2 * S - 1];
+    static constexpr int axes = (x != 0) + (y != 0) + (z != 0);
+    // an axis link's points x -+ e are also the Laplacian's neighbours along that axis
+    static constexpr bool lap_x = !(axes == 1 && x != 0), lap_y = !(axes == 1 && y != 0), lap_z = !(axes == 1 && z != 0);
+};
+
+// Keeps a value in a register from here on.  As the statement is volatile and
+// clobbers memory, loads written before it are issued before it and loads
+// written after it are not issued earlier: the order in which the source
+// issues a slot's loads and uses the slot before it holds in the machine code.
+// What bounds the step without it is latency: scheduled freely, the compiler
+// waited for nearly every load by itself to save registers, and a wave took
+// about 400 cycles per vector-memory instruction (FP16, two waves per SIMD).
+// With the next record's loads in flight while one is used (256x256x512, ms
+// per step, chunked layout, before -> after): FP16 8.07 -> 3.55, FP32 6.22 ->
+// 5.08, FP64 10.6 -> 10.2; before both changes 5.11, 5.53 and 11.0.
+template <typename T>
+__device__ __forceinline__ void pin(T& v) {
+    asm volatile("" : "+v"(v)::"memory");
 }
 
 // The two lanes of a cell are l and l ^ 32 of a wavefront: each half of the
@@ -630,90 +633,103 @@ __device__ __forceinline__ V pair_sum(V v) {
 // of Eq. rlb, f' = (f + omega f_eq) / (1 + omega) (else explicit, Reading
 // R4); bit 1 the limited Lax-Wendroff face values (else MUSCL, Reading R2);
 // bit 2 the external force; bit 3 the previous step's B in the recovery and
-// f_eq (else this step's, Reading R10), carried in the field block.
+// f_eq (else this step's, Reading R10), carried in the state.
 template <bool NT, typename TS, typename TE, typename V, int GM, int VR = 0>
-__device__ __forceinline__ void pair_cell(const TS* __restrict__ sd, const TE* __restrict__ se, TS* __restrict__ dd,
-                                          TE* __restrict__ de, const double* __restrict__ faceB,
-                                          const GuessTables* __restrict__ gt, const Consts& K, int cell,
-                                          const Nbr& nb, int h, int x, int y, int z, bool active, double& bmax,
-                                          bool& gate) {
-    // stores of this cell's new state (lanes that only take part in the
-    // wavefront's network evaluation store nothing)
-    auto put = [&](auto* p, auto v) {
-        if (active) st<NT>(p, v);
-    };
+__device__ __forceinline__ void pair_cell(const char* __restrict__ sd, char* __restrict__ dd,
+                                          const double* __restrict__ faceB, const GuessTables* __restrict__ gt,
+                                          const Consts& K, int cell, const Nbr& nb, int h, int x, int y, int z,
+                                          bool active, double& bmax, bool& gate) {
+    using L = Lay<TS>;
     const V sgn = h ? V(-1) : V(1);
-    const int64_t S = K.stride;
-    // Array bases stay uniform (scalar registers); the lane's choice between
-    // the two arrays of a pair is folded into its 32-bit element index.
-    const int hc = cell + (h ? (int)S : 0);
+    const int pos = (int)K.g0 + cell;
+    // Byte offset of this lane's records at a stencil point, the lane's choice
+    // between the two arrays of a pair included (the arrays of a pair are
+    // neighbours in the chunk); what is left per array is a constant.
+    const int h16 = h ? CHUNK * 16 : 0, h8 = h ? CHUNK * 8 : 0;
+    auto rec = [&](int o) { return lane_off<16>(K, pos + o) + h16; };
+    auto mrec = [&](int o) { return lane_off<8>(K, pos + o) + h8; };
+    const int64_t c16 = lane_off<16>(K, pos), c8 = lane_off<8>(K, pos);
     constexpr int CM = VR & 1;
     const V cour = (V)K.cour, kv = (V)K.kv, slope = (VR & 2) ? (V)K.slope : V(0.5);
     V Fv[10], Gv[10], Hv[13];
     V t00 = 0, t0x = 0, t0y = 0, t0z = 0, txx = 0, tyy = 0, tzz = 0, txy = 0, txz = 0, tyz = 0, n0 = 0;
     // slot 0: f_0, g_0 (lane 0) and h_rest (lane 1)
     {
-        const vec2<V> fg0 = ldv2<V>(sd, fg_index(K, 0, cell));
-        const V hr = ldv_once<V>(sd, (int64_t)(OFF_H + QH) * S + cell);
+        const vec2<V> fg0 = ldv2<V, TS>(sd, c16);
+        const V hr = ldv_once<V, TS>(sd, c8 + L::H + CHUNK * 8 * QH);
         Fv[0] = h ? V(0) : fg0.x;
         Gv[0] = h ? V(0) : fg0.y;
         Hv[12] = h ? hr : V(0);
         t00 = Fv[0];
         n0 = Gv[0];
     }
-    const int lap_xp = nb.at(1, 0, 0), lap_xm = nb.at(-1, 0, 0), lap_yp = nb.at(0, 1, 0), lap_ym = nb.at(0, -1, 0),
-              lap_zp = nb.at(0, 0, 1), lap_zm = nb.at(0, 0, -1);
+    const int64_t cc = c16 + h16;
+    const int64_t lap_xp = rec(nb.at(1, 0, 0)), lap_xm = rec(nb.at(-1, 0, 0)), lap_yp = rec(nb.at(0, 1, 0)),
+                  lap_ym = rec(nb.at(0, -1, 0)), lap_zp = rec(nb.at(0, 0, 1)), lap_zm = rec(nb.at(0, 0, -1));
+    // The loads of a slot: its pairs at the centre and the link's points, its f at the Laplacian's.
+    struct Raw {
+        vec2<TS> c0, m2, m1, p1;
+        TS xp, xm, yp, ym, zp, zm;
+    };
+    auto issue = [&](auto ic, Raw& r) {
+        using K_ = Link<decltype(ic)::value>;
+        const char* __restrict__ fga = sd + CHUNK * 16 * (2 * decltype(ic)::value - 1);  // uniform base of the pairs
+        auto pr = [&](int64_t o) { return *reinterpret_cast<const vec2<TS>*>(fga + o); };
+        auto f = [&](int64_t o) { return *reinterpret_cast<const TS*>(fga + o); };
+        r.c0 = pr(cc);
+        r.m2 = pr(rec(h ? nb.at(2 * K_::x, 2 * K_::y, 2 * K_::z) : nb.at(-2 * K_::x, -2 * K_::y, -2 * K_::z)));
+        r.m1 = pr(rec(h ? nb.at(K_::x, K_::y, K_::z) : nb.at(-K_::x, -K_::y, -K_::z)));
+        r.p1 = pr(rec(h ? nb.at(-K_::x, -K_::y, -K_::z) : nb.at(K_::x, K_::y, K_::z)));
+        if constexpr (K_::lap_x) r.xp = f(lap_xp), r.xm = f(lap_xm);
+        if constexpr (K_::lap_y) r.yp = f(lap_yp), r.ym = f(lap_ym);
+        if constexpr (K_::lap_z) r.zp = f(lap_zp), r.zm = f(lap_zm);
+    };
+    auto arrive = [&](auto ic, Raw& r) {
+        using K_ = Link<decltype(ic)::value>;
+        pin(r.c0), pin(r.m2), pin(r.m1), pin(r.p1);
+        if constexpr (K_::lap_x) pin(r.xp), pin(r.xm);
+        if constexpr (K_::lap_y) pin(r.yp), pin(r.ym);
+        if constexpr (K_::lap_z) pin(r.zp), pin(r.zm);
+    };
+    TS hraw[12];
+    auto issue_h = [&]() {
+#pragma unroll
+        for (int m = 0; m < 12; ++m) {
+            const int k0 = 2 * m;
+            hraw[m] = __builtin_nontemporal_load(reinterpret_cast<const TS*>(
+                sd + L::H + CHUNK * 8 * k0 + mrec(nb.at(-SX[k0], -SY[k0], -SZ[k0]))));
+        }
+    };
+    Raw raw[2];
+    issue(std::integral_constant<int, 1>{}, raw[1]);
     static_for<1>([&](auto ic) {
         constexpr int s = decltype(ic)::value;
         if constexpr (s <= 9) {
             constexpr int i0 = 2 * s - 1;
             constexpr int ex = EX[i0], ey = EY[i0], ez = EZ[i0];
-            const int om2 = h ? nb.at(2 * ex, 2 * ey, 2 * ez) : nb.at(-2 * ex, -2 * ey, -2 * ez);
-            const int om1 = h ? nb.at(ex, ey, ez) : nb.at(-ex, -ey, -ez);
-            const int op1 = h ? nb.at(-ex, -ey, -ez) : nb.at(ex, ey, ez);
-            const TS* __restrict__ fga = sd + fg_index(K, i0, 0);  // uniform base of direction i0's pairs
-            const vec2<V> c0 = ldv2<V>(fga, 2 * (int64_t)hc), m2 = ldv2<V>(fga, 2 * (int64_t)(hc + om2)),
-                          m1 = ldv2<V>(fga, 2 * (int64_t)(hc + om1)), p1 = ldv2<V>(fga, 2 * (int64_t)(hc + op1));
-            const V f0 = c0.x, fm2 = m2.x, fm1 = m1.x, fp1 = p1.x;
-            // On an axis slot the upwind points x -+ e are also the Laplacian's
-            // neighbours along that axis (lane 1 walks -e): reuse them.
-            constexpr bool axis_slot = (ex != 0) + (ey != 0) + (ez != 0) == 1;
-            const V up = h ? fm1 : fp1, dn = h ? fp1 : fm1;  // f at x + e_i0 and x - e_i0
-            auto lap_at = [&](int off) { return ldv<V>(fga, 2 * (int64_t)(hc + off)); };
-            V lxp, lxm, lyp, lym, lzp, lzm;
-            if constexpr (axis_slot && ex != 0) {
-                lxp = up;
-                lxm = dn;
-            } else {
-                lxp = lap_at(lap_xp);
-                lxm = lap_at(lap_xm);
-            }
-            if constexpr (axis_slot && ey != 0) {
-                lyp = up;
-                lym = dn;
-            } else {
-                lyp = lap_at(lap_yp);
-                lym = lap_at(lap_ym);
-            }
-            if constexpr (axis_slot && ez != 0) {
-                lzp = up;
-                lzm = dn;
-            } else {
-                lzp = lap_at(lap_zp);
-                lzm = lap_at(lap_zm);
-            }
+            using K_ = Link<s>;
+            // the next slot's loads (after the last slot, the Maxwell populations') are in flight while this
+            // slot's arrive and are used
+            if constexpr (s < 9)
+                issue(std::integral_constant<int, s + 1>{}, raw[(s + 1) & 1]);
+            else
+                issue_h();
+            Raw& r = raw[s & 1];
+            arrive(ic, r);
+            const V f0 = r.c0.x, fm2 = r.m2.x, fm1 = r.m1.x, fp1 = r.p1.x;
+            const V up = h ? fm1 : fp1, dn = h ? fp1 : fm1;  // f at x + e_i0 and x - e_i0 (lane 1 walks -e)
+            const V lxp = K_::lap_x ? r.xp : up, lxm = K_::lap_x ? r.xm : dn;
+            const V lyp = K_::lap_y ? r.yp : up, lym = K_::lap_y ? r.ym : dn;
+            const V lzp = K_::lap_z ? r.zp : up, lzm = K_::lap_z ? r.zm : dn;
             const V lap = (lxp + lxm) + (lyp + lym) + (lzp + lzm) - V(6) * f0;
             const V fv = f0 - cour * ((f0 + slope * minmod(f0 - fm1, fp1 - f0)) -
                                       (fm1 + slope * minmod(fm1 - fm2, f0 - fm1))) + kv * lap;
-            const V g0 = c0.y, gm2 = m2.y, gm1 = m1.y, gp1 = p1.y;
+            const V g0 = r.c0.y, gm2 = r.m2.y, gm1 = r.m1.y, gp1 = r.p1.y;
             const V gv = g0 - cour * ((g0 + slope * minmod(g0 - gm1, gp1 - g0)) -
                                       (gm1 + slope * minmod(gm1 - gm2, g0 - gm1)));
             Fv[s] = fv;
             Gv[s] = gv;
-            // Keep each slot's arithmetic next to its loads: without this the
-            // scheduler sinks all of it below every load of the cell, and the
-            // ~150 load destinations in flight cost a wave its occupancy.
-            if constexpr (s % pin_group<TS>() == 0 || s == 9) asm volatile("" : "+v"(Fv[s]), "+v"(Gv[s])::"memory");
+            pin(Fv[s]), pin(Gv[s]);  // the slot's arithmetic stays here
             t00 += fv;
             n0 += gv;
             const V sf = sgn * fv;
@@ -728,11 +744,22 @@ __device__ __forceinline__ void pair_cell(const TS* __restrict__ sd, const TE* _
             if (ey * ez) tyz += (ey * ez) * fv;
         }
     });
+    // E of the last step, and the Gauss charge: lane 0 takes E_x(x+-1), E_y(y+1); lane 1 E_y(y-1), E_z(z+-1)
+    auto Ea = [&](int a, int64_t off) { return ld<TE>(sd, off + L::E + CHUNK * 8 * a); };
+    auto at8 = [&](int dx, int dy, int dz) { return lane_off<8>(K, pos + nb.at(dx, dy, dz)); };
+    double Ep[3], ga, gb, gc;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) Ep[a] = Ea(a, c8);
+    ga = Ea(h ? 1 : 0, h ? at8(0, -1, 0) : at8(1, 0, 0));
+    gb = Ea(h ? 2 : 0, h ? at8(0, 0, 1) : at8(-1, 0, 0));
+    gc = Ea(h ? 2 : 1, h ? at8(0, 0, -1) : at8(0, 1, 0));
+#pragma unroll
+    for (int m = 0; m < 12; ++m) pin(hraw[m]);
     V ehx = 0, ehy = 0, ehz = 0, bx = 0, by = 0, bz = 0, hs = 0;
 #pragma unroll
     for (int m = 0; m < 12; ++m) {
         const int k0 = 2 * m;
-        const V v = ldv_once<V>(sd + (int64_t)(OFF_H + k0) * S, hc + nb.at(-SX[k0], -SY[k0], -SZ[k0]));
+        const V v = hraw[m];
         Hv[m] = v;
         hs += v;
         const V sv = sgn * v;
@@ -745,18 +772,8 @@ __device__ __forceinline__ void pair_cell(const TS* __restrict__ sd, const TE* _
     }
     CellSol M;
 #pragma unroll
-    for (int a = 0; a < 3; ++a) M.Ep[a] = ld(se + (int64_t)a * S + cell, 0);
-    // Gauss charge: lane 0 takes E_x(x+-1), E_y(y+1); lane 1 E_y(y-1), E_z(z+-1)
-    double gpart;
-    {
-        const TE* ex_ = se + cell;
-        const TE* ey_ = se + S + cell;
-        const TE* ez_ = se + 2 * S + cell;
-        const double a = h ? -ld(ey_, lap_ym) : ld(ex_, lap_xp);
-        const double b = h ? ld(ez_, lap_zp) : -ld(ex_, lap_xm);
-        const double c = h ? -ld(ez_, lap_zm) : ld(ey_, lap_yp);
-        gpart = (a + b) + c;
-    }
+    for (int a = 0; a < 3; ++a) M.Ep[a] = Ep[a];
+    const double gpart = ((h ? -ga : ga) + (h ? gb : -gb)) + (h ? -gc : gc);
     M.T00 = K.fs0 + (double)pair_sum(t00);
     M.N0 = K.gs0 + (double)pair_sum(n0);
     M.T0[0] = KAPPA * (double)pair_sum(t0x);
@@ -793,7 +810,7 @@ __device__ __forceinline__ void pair_cell(const TS* __restrict__ sd, const TE* _
     if constexpr ((VR & 8) != 0) {
         double Bp[3];
 #pragma unroll
-        for (int a = 0; a < 3; ++a) Bp[a] = ld(se + (int64_t)(3 + a) * S + cell, 0);
+        for (int a = 0; a < 3; ++a) Bp[a] = Ea(3 + a, c8);
         solve_cell<GM>(K, M, Bp, gt, &gate);
         fe.setup(M.eps, M.p, M.gam, M.beta, M.Ep, Bp, K.c, K.eps0);
     } else {
@@ -805,8 +822,7 @@ __device__ __forceinline__ void pair_cell(const TS* __restrict__ sd, const TE* _
     const V rate = (V)(M.gam * K.inv_tau);
     const V wg = (V)K.wg, inv1wg = (V)(1.0 / (1.0 + K.wg));
     const V ng = (V)(M.n * M.gam);
-    const V gc1 = (V)K.gc1, gc2 = (V)K.gc2, gc3b2 = (V)(K.gc3 * (M.beta[0] * M.beta[0] + M.beta[1] * M.beta[1] +
-                                                              M.beta[2] * M.beta[2]));
+    const V gc1 = (V)K.gc1, gc2 = (V)K.gc2, gc3b2 = (V)(K.gc3 * norm2(M.beta));
     const V bx_ = (V)M.beta[0], by_ = (V)M.beta[1], bz_ = (V)M.beta[2];
     // External force (Reading R26): c dt F^a into T^{0a} through the moving
     // populations, (19/9) w_i (e_i . c dt F) / kappa each, and the work
@@ -828,9 +844,9 @@ __device__ __forceinline__ void pair_cell(const TS* __restrict__ sd, const TE* _
         const V geq0 = (V)K.wp[0] * ng * (V(1) - gc3b2);
         V f0n = CM == 0 ? Fv[0] - rate * (Fv[0] + q0) : (Fv[0] - rate * q0) / (V(1) + rate);
         if constexpr ((VR & 4) != 0) f0n += (V)fw;
-        if (active) st2<NT>(dd + fg_index(K, 0, cell), f0n, (Gv[0] + wg * (geq0 - (V)K.gsh[0])) * inv1wg);
+        if (active) st2<NT, TS>(dd, c16, f0n, (Gv[0] + wg * (geq0 - (V)K.gsh[0])) * inv1wg);
     } else {
-        put(dd + (int64_t)(OFF_H + QH) * S + cell, (V)(2.0 * M.rho) - Hv[12]);
+        if (active) st<NT, TS>(dd, c8 + L::H + CHUNK * 8 * QH, (V)(2.0 * M.rho) - Hv[12]);
     }
     static_for<1>([&](auto ic) {
         constexpr int s = decltype(ic)::value;
@@ -847,48 +863,36 @@ __device__ __forceinline__ void pair_cell(const TS* __restrict__ sd, const TE* _
                 fn += (V)((19.0 / 9.0) * wcls / KAPPA * ((h ? -1.0 : 1.0) * (EX[i0] * fx + EY[i0] * fy + EZ[i0] * fz)));
             }
             if (active)
-                st2<NT>(dd + fg_index(K, i0, 0) + 2 * (int64_t)hc, fn, (Gv[s] + wg * (geq - (V)K.gsh[cls])) * inv1wg);
+                st2<NT, TS>(dd, cc + CHUNK * 16 * i0, fn, (Gv[s] + wg * (geq - (V)K.gsh[cls])) * inv1wg);
         }
     });
-    const V cj = (V)(1.0 / (16.0 * 1.4142135623730951 * K.c)), ce = (V)(1.0 / (8.0 * 1.4142135623730951 * K.c));
+    const V cj = (V)(1.0 / (16.0 * 1.4142135623730951 * K.c)), cE = (V)(1.0 / (8.0 * 1.4142135623730951 * K.c));
     const V J0 = (V)M.J[0], J1 = (V)M.J[1], J2 = (V)M.J[2];
     const V E0 = (V)M.E[0], E1 = (V)M.E[1], E2 = (V)M.E[2];
 #pragma unroll
     for (int m = 0; m < 12; ++m) {
         const int k0 = 2 * m;
-        const V heq = cj * (SX[k0] * J0 + SY[k0] * J1 + SZ[k0] * J2) + sgn * ce * (EHX[k0] * E0 + EHY[k0] * E1 + EHZ[k0] * E2);
-        put(dd + (int64_t)(OFF_H + k0) * S + hc, V(2) * heq - Hv[m]);
+        const V heq = cj * (SX[k0] * J0 + SY[k0] * J1 + SZ[k0] * J2) + sgn * cE * (EHX[k0] * E0 + EHY[k0] * E1 + EHZ[k0] * E2);
+        if (active) st<NT, TS>(dd, c8 + h8 + L::H + CHUNK * 8 * k0, V(2) * heq - Hv[m]);
     }
     if (h == 0) {
 #pragma unroll
-        for (int a = 0; a < 3; ++a) put(de + (int64_t)a * S + cell, M.E[a]);
+        for (int a = 0; a < 3; ++a)
+            if (active) st<NT, TE>(dd, c8 + L::E + CHUNK * 8 * a, M.E[a]);
     } else if constexpr ((VR & 8) != 0) {  // this step's coupling B is the next one's previous B
 #pragma unroll
-        for (int a = 0; a < 3; ++a) put(de + (int64_t)(3 + a) * S + cell, M.B[a]);
+        for (int a = 0; a < 3; ++a)
+            if (active) st<NT, TE>(dd, c8 + L::E + CHUNK * 8 * (3 + a), M.B[a]);
     }
 }
 
 // ---------------------------------------------------- one lane per cell
 
-template <typename T>
-using vec4 = T __attribute__((ext_vector_type(4)));
-
+// 16 bytes of FP16 (two quads)
 template <typename V, typename T>
-__device__ __forceinline__ vec4<V> ldv4(const T* __restrict__ p, int64_t i) {
-    const vec4<T> v = *reinterpret_cast<const vec4<T>*>(p + i);
-    vec4<V> r;
-    r.x = static_cast<V>(v.x);
-    r.y = static_cast<V>(v.y);
-    r.z = static_cast<V>(v.z);
-    r.w = static_cast<V>(v.w);
-    return r;
-}
-
-// 16 bytes of FP16 (two quads) at element i
-template <typename V, typename T>
-__device__ __forceinline__ void ldv8(const T* __restrict__ p, int64_t i, vec4<V>& lo, vec4<V>& hi) {
+__device__ __forceinline__ void ldv8(const char* __restrict__ s, int64_t o, vec4<V>& lo, vec4<V>& hi) {
     typedef T vec8 __attribute__((ext_vector_type(8)));
-    const vec8 v = *reinterpret_cast<const vec8*>(p + i);
+    const vec8 v = *reinterpret_cast<const vec8*>(s + o);
     lo.x = static_cast<V>(v[0]);
     lo.y = static_cast<V>(v[1]);
     lo.z = static_cast<V>(v[2]);
@@ -900,7 +904,7 @@ __device__ __forceinline__ void ldv8(const T* __restrict__ p, int64_t i, vec4<V>
 }
 
 template <bool NT, typename T, typename V>
-__device__ __forceinline__ void st8(T* __restrict__ p, const vec4<V>& lo, const vec4<V>& hi) {
+__device__ __forceinline__ void st8(char* __restrict__ d, int64_t o, const vec4<V>& lo, const vec4<V>& hi) {
     typedef T vec8 __attribute__((ext_vector_type(8)));
     vec8 v;
     v[0] = static_cast<T>(lo.x);
@@ -911,29 +915,8 @@ __device__ __forceinline__ void st8(T* __restrict__ p, const vec4<V>& lo, const 
     v[5] = static_cast<T>(hi.y);
     v[6] = static_cast<T>(hi.z);
     v[7] = static_cast<T>(hi.w);
-    if constexpr (NT)
-        __builtin_nontemporal_store(v, reinterpret_cast<vec8*>(p));
-    else
-        *reinterpret_cast<vec8*>(p) = v;
+    put_raw<NT>(d, o, v);
 }
-
-template <bool NT, typename T, typename V>
-__device__ __forceinline__ void st4(T* __restrict__ p, V a, V b, V c, V d) {
-    vec4<T> v;
-    v.x = static_cast<T>(a);
-    v.y = static_cast<T>(b);
-    v.z = static_cast<T>(c);
-    v.w = static_cast<T>(d);
-    if constexpr (NT)
-        __builtin_nontemporal_store(v, reinterpret_cast<vec4<T>*>(p));
-    else
-        *reinterpret_cast<vec4<T>*>(p) = v;
-}
-
-// f/g slots whose loads may be in flight together in the one-lane-per-cell step
-#ifndef RMHDLB_QGROUP
-#define RMHDLB_QGROUP 1
-#endif
 
 // The fused step of one cell in one lane (FP32 storage, quad layout; FP16,
 // double-quad layout, where one load at the centre and at each Laplacian
@@ -945,21 +928,21 @@ __device__ __forceinline__ void st4(T* __restrict__ p, V a, V b, V c, V d) {
 // pair_cell (the readings it implements are listed there); only the
 // assignment of work to lanes and the order of the moment sums differ.
 template <bool NT, typename TS, typename TE, typename V, int GM, int VR = 0>
-__device__ __forceinline__ void quad_cell(const TS* __restrict__ sd, const TE* __restrict__ se, TS* __restrict__ dd,
-                                          TE* __restrict__ de, const double* __restrict__ faceB,
-                                          const GuessTables* __restrict__ gt, const Consts& K, int cell,
-                                          const Nbr& nb, int x, int y, int z, bool active, double& bmax,
-                                          bool& gate) {
-    auto put = [&](auto* p, auto v) {
-        if (active) st<NT>(p, v);
-    };
-    const int64_t S = K.stride;
+__device__ __forceinline__ void quad_cell(const char* __restrict__ sd, char* __restrict__ dd,
+                                          const double* __restrict__ faceB, const GuessTables* __restrict__ gt,
+                                          const Consts& K, int cell, const Nbr& nb, int x, int y, int z, bool active,
+                                          double& bmax, bool& gate) {
+    using L = Lay<TS>;
+    const int pos = (int)K.g0 + cell;
+    // byte offsets of this cell's records at a stencil point; what is left per array is a constant
+    auto rec = [&](int o) { return lane_off<16>(K, pos + o); };
+    const int64_t cc = lane_off<16>(K, pos), ch = lane_off<L::HREC>(K, pos), ce = lane_off<4>(K, pos);
     constexpr int CM = VR & 1;
     const V cour = (V)K.cour, kv = (V)K.kv, slope = (VR & 2) ? (V)K.slope : V(0.5);
     V Fv[Q], Gv[Q], Hv[QH + 1];
     V t00 = 0, t0x = 0, t0y = 0, t0z = 0, txx = 0, tyy = 0, tzz = 0, txy = 0, txz = 0, tyz = 0, n0 = 0;
-    const int lap_xp = nb.at(1, 0, 0), lap_xm = nb.at(-1, 0, 0), lap_yp = nb.at(0, 1, 0), lap_ym = nb.at(0, -1, 0),
-              lap_zp = nb.at(0, 0, 1), lap_zm = nb.at(0, 0, -1);
+    const int64_t lap_xp = rec(nb.at(1, 0, 0)), lap_xm = rec(nb.at(-1, 0, 0)), lap_yp = rec(nb.at(0, 1, 0)),
+                  lap_ym = rec(nb.at(0, -1, 0)), lap_zp = rec(nb.at(0, 0, 1)), lap_zm = rec(nb.at(0, 0, -1));
     // Transport and moments of slot s from its quads at the link points x - 2e .. x + 2e and the
     // Laplacian's six neighbours.
     auto transport = [&](auto sc, const vec4<V>& q0, const vec4<V>& qm2, const vec4<V>& qm1, const vec4<V>& qp1,
@@ -996,123 +979,153 @@ __device__ __forceinline__ void quad_cell(const TS* __restrict__ sd, const TE* _
         if (ex * ez) txz += (ex * ez) * sum;
         if (ey * ez) tyz += (ey * ez) * sum;
     };
-    // a slot whose link runs along one axis finds its points x -+ e among the Laplacian's neighbours
-    if constexpr (!dquad_layout<TS>()) {
-        {
-            const vec2<V> fg0 = ldv2<V>(sd, quad_index(K, 0, cell));
-            Fv[0] = fg0.x;
-            Gv[0] = fg0.y;
-            t00 = Fv[0];
-            n0 = Gv[0];
+    // The loads of a record (FP32: one slot; FP16: two, the centre and the Laplacian's points in one load each
+    // and the link's points in one per slot); the next record's are in flight while this one's arrive and are used.
+    constexpr bool DQ = dquad_layout<TS>();
+    using Rec = unsigned __attribute__((ext_vector_type(4)));   // 16 bytes: a quad (FP32), two quads (FP16)
+    using Half = std::conditional_t<DQ, vec2<unsigned>, Rec>;   // one slot's quad
+    struct Raw {
+        Rec c, xp, xm, yp, ym, zp, zm;
+        Half a[4], b[4];  // link points x - 2e, x + 2e, x - e, x + e of the record's slots
+    };
+    constexpr int RECS = DQ ? DQUAD_RECORDS : 9;
+    auto rec16 = [&](const char* __restrict__ base, int64_t o) { return *reinterpret_cast<const Rec*>(base + o); };
+    auto half8 = [&](const char* __restrict__ base, int64_t o) { return *reinterpret_cast<const Half*>(base + o); };
+    auto issue_links = [&](auto sc, const char* __restrict__ base, Half (&q)[4]) {
+        using K_ = Link<decltype(sc)::value>;
+        q[0] = half8(base, rec(nb.at(-2 * K_::x, -2 * K_::y, -2 * K_::z)));
+        q[1] = half8(base, rec(nb.at(2 * K_::x, 2 * K_::y, 2 * K_::z)));
+        if constexpr (K_::axes > 1) {
+            q[2] = half8(base, rec(nb.at(-K_::x, -K_::y, -K_::z)));
+            q[3] = half8(base, rec(nb.at(K_::x, K_::y, K_::z)));
         }
-        static_for<1>([&](auto ic) {
-            constexpr int s = decltype(ic)::value;
-            if constexpr (s <= 9) {
-                constexpr int i0 = 2 * s - 1;
-                constexpr int ex = EX[i0], ey = EY[i0], ez = EZ[i0];
-                const TS* __restrict__ qa = sd + quad_index(K, s, 0);  // uniform base of slot s
-                auto ldq = [&](int off) { return ldv4<V>(qa, 4 * (int64_t)(cell + off)); };
-                const vec4<V> q0 = ldq(0), qm2 = ldq(nb.at(-2 * ex, -2 * ey, -2 * ez)), qm1 = ldq(nb.at(-ex, -ey, -ez)),
-                              qp1 = ldq(nb.at(ex, ey, ez)), qp2 = ldq(nb.at(2 * ex, 2 * ey, 2 * ez));
-                constexpr bool ax = (ex != 0) + (ey != 0) + (ez != 0) == 1;
-                const vec4<V> lxp = ax && ex ? qp1 : ldq(lap_xp), lxm = ax && ex ? qm1 : ldq(lap_xm);
-                const vec4<V> lyp = ax && ey ? qp1 : ldq(lap_yp), lym = ax && ey ? qm1 : ldq(lap_ym);
-                const vec4<V> lzp = ax && ez ? qp1 : ldq(lap_zp), lzm = ax && ez ? qm1 : ldq(lap_zm);
-                transport(ic, q0, qm2, qm1, qp1, qp2, lxp, lxm, lyp, lym, lzp, lzm);
-                V(&F_)[Q] = Fv;
-                V(&G_)[Q] = Gv;
-                if constexpr (s % RMHDLB_QGROUP == 0 || s == 9)
-                    asm volatile("" : "+v"(F_[i0]), "+v"(F_[i0 + 1]), "+v"(G_[i0]), "+v"(G_[i0 + 1])::"memory");
+    };
+    auto pin_links = [&](auto sc, Half (&q)[4]) {
+        pin(q[0]), pin(q[1]);
+        if constexpr (Link<decltype(sc)::value>::axes > 1) pin(q[2]), pin(q[3]);
+    };
+    // record r: slots sa and (FP16) sb, 0 when the second quad is the rest one
+    auto slot_a = [](auto rc) { return std::integral_constant<int, DQ ? 2 * decltype(rc)::value + 1 : decltype(rc)::value + 1>{}; };
+    auto slot_b = [](auto rc) { return std::integral_constant<int, DQ && decltype(rc)::value < 4 ? 2 * decltype(rc)::value + 2 : 0>{}; };
+    auto issue = [&](auto rc, Raw& q) {
+        constexpr auto sa = slot_a(rc);
+        constexpr auto sb = slot_b(rc);
+        using A = Link<sa.value>;
+        const char* __restrict__ base = sd + CHUNK * 16 * (DQ ? decltype(rc)::value : sa.value);
+        q.c = rec16(base, cc);
+        // an FP32 axis slot's points x -+ e also serve its Laplacian; an FP16 record's serve both slots
+        q.xp = rec16(base, lap_xp), q.xm = rec16(base, lap_xm);
+        q.yp = rec16(base, lap_yp), q.ym = rec16(base, lap_ym);
+        q.zp = rec16(base, lap_zp), q.zm = rec16(base, lap_zm);
+        issue_links(sa, base, q.a);
+        if constexpr (sb.value != 0) issue_links(sb, base + 8, q.b);
+        (void)sizeof(A);
+    };
+    auto arrive = [&](auto rc, Raw& q) {
+        constexpr auto sa = slot_a(rc);
+        constexpr auto sb = slot_b(rc);
+        pin(q.c), pin(q.xp), pin(q.xm), pin(q.yp), pin(q.ym), pin(q.zp), pin(q.zm);
+        pin_links(sa, q.a);
+        if constexpr (sb.value != 0) pin_links(sb, q.b);
+    };
+    auto quad_of = [](const auto& w, int half) {  // the quad in a record or half record, as V
+        vec4<V> r;
+        if constexpr (sizeof(w) == 16 && !DQ) {
+            r.x = __builtin_bit_cast(float, (unsigned)w[0]), r.y = __builtin_bit_cast(float, (unsigned)w[1]);
+            r.z = __builtin_bit_cast(float, (unsigned)w[2]), r.w = __builtin_bit_cast(float, (unsigned)w[3]);
+        } else {
+            const int o = sizeof(w) == 16 ? 2 * half : 0;
+            const vec2<_Float16> lo = __builtin_bit_cast(vec2<_Float16>, (unsigned)w[o]),
+                                 hi = __builtin_bit_cast(vec2<_Float16>, (unsigned)w[o + 1]);
+            r.x = (V)lo.x, r.y = (V)lo.y, r.z = (V)hi.x, r.w = (V)hi.y;
+        }
+        return r;
+    };
+    auto use = [&](auto sc, const Raw& q, int half, const Half (&lk)[4]) {
+        constexpr int s = decltype(sc)::value;
+        using K_ = Link<s>;
+        const vec4<V> c = quad_of(q.c, half), xp = quad_of(q.xp, half), xm = quad_of(q.xm, half),
+                      yp = quad_of(q.yp, half), ym = quad_of(q.ym, half), zp = quad_of(q.zp, half),
+                      zm = quad_of(q.zm, half), m2 = quad_of(lk[0], 0), p2 = quad_of(lk[1], 0);
+        vec4<V> m1, p1;
+        if constexpr (K_::axes > 1)
+            m1 = quad_of(lk[2], 0), p1 = quad_of(lk[3], 0);
+        else if constexpr (K_::x != 0)
+            m1 = xm, p1 = xp;
+        else if constexpr (K_::y != 0)
+            m1 = ym, p1 = yp;
+        else
+            m1 = zm, p1 = zp;
+        transport(sc, c, m2, m1, p1, p2, xp, xm, yp, ym, zp, zm);
+        pin(Fv[2 * s - 1]), pin(Fv[2 * s]), pin(Gv[2 * s - 1]), pin(Gv[2 * s]);  // the slot's arithmetic stays here
+    };
+    using HRaw = std::conditional_t<DQ, unsigned, vec2<unsigned>>;
+    HRaw hraw[12];
+    auto issue_h = [&]() {
+#pragma unroll
+        for (int m = 0; m < 12; ++m) {
+            const int k0 = 2 * m;
+            hraw[m] = *reinterpret_cast<const HRaw*>(sd + L::H + CHUNK * L::HREC * m +
+                                                     lane_off<L::HREC>(K, pos + nb.at(-SX[k0], -SY[k0], -SZ[k0])));
+        }
+    };
+    Rec rest_raw = {0, 0, 0, 0};
+    if constexpr (!DQ) rest_raw = rec16(sd, cc);
+    Raw raw[2];
+    issue(std::integral_constant<int, 0>{}, raw[0]);
+    static_for<0>([&](auto rc) {
+        constexpr int r = decltype(rc)::value;
+        if constexpr (r < RECS) {
+            if constexpr (r + 1 < RECS)
+                issue(std::integral_constant<int, r + 1>{}, raw[(r + 1) & 1]);
+            else
+                issue_h();
+            Raw& q = raw[r & 1];
+            arrive(rc, q);
+            if constexpr (r == 0 && !DQ) {
+                pin(rest_raw);
+                const vec4<V> fg0 = quad_of(rest_raw, 0);
+                Fv[0] = fg0.x;
+                Gv[0] = fg0.y;
+                Hv[QH] = fg0.z;
+                t00 = Fv[0];
+                n0 = Gv[0];
             }
-        });
-    } else {
-        // record r: slots a = 2r + 1 and b = 2r + 2 (record 4: slot 9 and the rest pair); the centre and
-        // the Laplacian's points take one 16-byte load for both slots, the link points an 8-byte one
-        static_for<0>([&](auto rc) {
-            constexpr int r = decltype(rc)::value;
-            if constexpr (r < DQUAD_RECORDS) {
-                constexpr int sa = 2 * r + 1, sb = r < 4 ? 2 * r + 2 : 0;
-                const TS* __restrict__ ra = sd + dquad_index(K, r, 0);  // uniform base of record r
-                auto ld8 = [&](int off, vec4<V>& lo, vec4<V>& hi) { ldv8<V>(ra, 8 * (int64_t)(cell + off), lo, hi); };
-                auto ld4 = [&](int off, int half) { return ldv4<V>(ra, 8 * (int64_t)(cell + off) + 4 * half); };
-                vec4<V> ca, cb;
-                ld8(0, ca, cb);
-                vec4<V> xpa, xpb, xma, xmb, ypa, ypb, yma, ymb, zpa, zpb, zma, zmb;
-                if constexpr (sb != 0) {
-                    ld8(lap_xp, xpa, xpb);
-                    ld8(lap_xm, xma, xmb);
-                    ld8(lap_yp, ypa, ypb);
-                    ld8(lap_ym, yma, ymb);
-                    ld8(lap_zp, zpa, zpb);
-                    ld8(lap_zm, zma, zmb);
-                } else {
-                    xpa = ld4(lap_xp, 0);
-                    xma = ld4(lap_xm, 0);
-                    ypa = ld4(lap_yp, 0);
-                    yma = ld4(lap_ym, 0);
-                    zpa = ld4(lap_zp, 0);
-                    zma = ld4(lap_zm, 0);
-                }
-                // the link points of slot s (half h of the record), reusing the Laplacian's on an axis slot
-                auto links = [&](auto sc, int h, const vec4<V>& xp, const vec4<V>& xm, const vec4<V>& yp,
-                                 const vec4<V>& ym, const vec4<V>& zp, const vec4<V>& zm, vec4<V>& qm2, vec4<V>& qm1,
-                                 vec4<V>& qp1, vec4<V>& qp2) {
-                    constexpr int s = decltype(sc)::value;
-                    constexpr int ex = EX[2 * s - 1], ey = EY[2 * s - 1], ez = EZ[2 * s - 1];
-                    constexpr bool ax = (ex != 0) + (ey != 0) + (ez != 0) == 1;
-                    qm2 = ld4(nb.at(-2 * ex, -2 * ey, -2 * ez), h);
-                    qp2 = ld4(nb.at(2 * ex, 2 * ey, 2 * ez), h);
-                    if constexpr (ax && ex == 1) {
-                        qp1 = xp;
-                        qm1 = xm;
-                    } else if constexpr (ax && ex == -1) {
-                        qp1 = xm;
-                        qm1 = xp;
-                    } else if constexpr (ax && ey == 1) {
-                        qp1 = yp;
-                        qm1 = ym;
-                    } else if constexpr (ax && ey == -1) {
-                        qp1 = ym;
-                        qm1 = yp;
-                    } else if constexpr (ax && ez == 1) {
-                        qp1 = zp;
-                        qm1 = zm;
-                    } else if constexpr (ax && ez == -1) {
-                        qp1 = zm;
-                        qm1 = zp;
-                    } else {
-                        qp1 = ld4(nb.at(ex, ey, ez), h);
-                        qm1 = ld4(nb.at(-ex, -ey, -ez), h);
-                    }
-                };
-                vec4<V> am2, am1, ap1, ap2;
-                links(std::integral_constant<int, sa>{}, 0, xpa, xma, ypa, yma, zpa, zma, am2, am1, ap1, ap2);
-                transport(std::integral_constant<int, sa>{}, ca, am2, am1, ap1, ap2, xpa, xma, ypa, yma, zpa, zma);
-                V(&F_)[Q] = Fv;
-                V(&G_)[Q] = Gv;
-                asm volatile("" : "+v"(F_[2 * sa - 1]), "+v"(F_[2 * sa]), "+v"(G_[2 * sa - 1]), "+v"(G_[2 * sa])::"memory");
-                if constexpr (sb != 0) {
-                    vec4<V> bm2, bm1, bp1, bp2;
-                    links(std::integral_constant<int, sb>{}, 1, xpb, xmb, ypb, ymb, zpb, zmb, bm2, bm1, bp1, bp2);
-                    transport(std::integral_constant<int, sb>{}, cb, bm2, bm1, bp1, bp2, xpb, xmb, ypb, ymb, zpb,
-                              zmb);
-                    asm volatile("" : "+v"(F_[2 * sb - 1]), "+v"(F_[2 * sb]), "+v"(G_[2 * sb - 1]),
-                                 "+v"(G_[2 * sb])::"memory");
-                } else {  // the rest pair
-                    Fv[0] = cb.x;
-                    Gv[0] = cb.y;
-                    t00 += Fv[0];
-                    n0 += Gv[0];
-                }
+            use(slot_a(rc), q, 0, q.a);
+            if constexpr (slot_b(rc).value != 0) {
+                use(slot_b(rc), q, 1, q.b);
+            } else if constexpr (DQ) {  // the rest quad
+                const vec4<V> fg0 = quad_of(q.c, 1);
+                Fv[0] = fg0.x;
+                Gv[0] = fg0.y;
+                Hv[QH] = fg0.z;
+                t00 += Fv[0];
+                n0 += Gv[0];
             }
-        });
-    }
+        }
+    });
+    // E of the last step and its neighbours for the Gauss charge
+    auto Ea = [&](int a, int64_t off) { return ldv<V, TE>(sd, off + L::E + CHUNK * 4 * a); };
+    auto at4 = [&](int dx, int dy, int dz) { return lane_off<4>(K, pos + nb.at(dx, dy, dz)); };
+    V Ep[3], gE[6];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) Ep[a] = Ea(a, ce);
+    gE[0] = Ea(0, at4(1, 0, 0)), gE[1] = Ea(0, at4(-1, 0, 0)), gE[2] = Ea(1, at4(0, 1, 0));
+    gE[3] = Ea(1, at4(0, -1, 0)), gE[4] = Ea(2, at4(0, 0, 1)), gE[5] = Ea(2, at4(0, 0, -1));
+#pragma unroll
+    for (int m = 0; m < 12; ++m) pin(hraw[m]);
     // stream h (Eq. LB_Maxwell): the pair 2m, 2m + 1 from its common source cell
     V ehx = 0, ehy = 0, ehz = 0, bx = 0, by = 0, bz = 0, hs = 0;
 #pragma unroll
     for (int m = 0; m < 12; ++m) {
         const int k0 = 2 * m;
-        const vec2<V> v = ldv2<V>(sd, hpair_index(K, m, (int64_t)cell + nb.at(-SX[k0], -SY[k0], -SZ[k0])));
+        vec2<V> v;
+        if constexpr (DQ) {
+            const vec2<_Float16> w = __builtin_bit_cast(vec2<_Float16>, hraw[m]);
+            v.x = (V)w.x, v.y = (V)w.y;
+        } else {
+            v.x = __builtin_bit_cast(float, (unsigned)hraw[m][0]), v.y = __builtin_bit_cast(float, (unsigned)hraw[m][1]);
+        }
         Hv[k0] = v.x;
         Hv[k0 + 1] = v.y;
         hs += v.x + v.y;
@@ -1124,16 +1137,12 @@ __device__ __forceinline__ void quad_cell(const TS* __restrict__ sd, const TE* _
         if (BHY[k0]) by += BHY[k0] * d;
         if (BHZ[k0]) bz += BHZ[k0] * d;
     }
-    Hv[QH] = ldv<V>(sd, hrest_quad_index(K, cell));
     CellSol M;
 #pragma unroll
-    for (int a = 0; a < 3; ++a) M.Ep[a] = ld(se + (int64_t)a * S + cell, 0);
+    for (int a = 0; a < 3; ++a) M.Ep[a] = (double)Ep[a];
     {
-        const TE* ex_ = se + cell;
-        const TE* ey_ = se + S + cell;
-        const TE* ez_ = se + 2 * S + cell;
-        const double dv = ((ld(ex_, lap_xp) - ld(ex_, lap_xm)) + (ld(ey_, lap_yp) - ld(ey_, lap_ym))) +
-                          (ld(ez_, lap_zp) - ld(ez_, lap_zm));
+        const double dv = (((double)gE[0] - (double)gE[1]) + ((double)gE[2] - (double)gE[3])) +
+                          ((double)gE[4] - (double)gE[5]);
         M.rho_g = K.eps0 * K.inv_2dx * dv;
     }
     M.T00 = K.fs0 + (double)t00;
@@ -1171,7 +1180,7 @@ __device__ __forceinline__ void quad_cell(const TS* __restrict__ sd, const TE* _
     if constexpr ((VR & 8) != 0) {
         double Bp[3];
 #pragma unroll
-        for (int a = 0; a < 3; ++a) Bp[a] = ld(se + (int64_t)(3 + a) * S + cell, 0);
+        for (int a = 0; a < 3; ++a) Bp[a] = Ea(3 + a, ce);
         solve_cell<GM>(K, M, Bp, gt, &gate);
         fe.setup(M.eps, M.p, M.gam, M.beta, M.Ep, Bp, K.c, K.eps0);
     } else {
@@ -1183,8 +1192,7 @@ __device__ __forceinline__ void quad_cell(const TS* __restrict__ sd, const TE* _
     const V rate = (V)(M.gam * K.inv_tau);
     const V wg = (V)K.wg, inv1wg = (V)(1.0 / (1.0 + K.wg));
     const V ng = (V)(M.n * M.gam);
-    const V gc1 = (V)K.gc1, gc2 = (V)K.gc2, gc3b2 = (V)(K.gc3 * (M.beta[0] * M.beta[0] + M.beta[1] * M.beta[1] +
-                                                              M.beta[2] * M.beta[2]));
+    const V gc1 = (V)K.gc1, gc2 = (V)K.gc2, gc3b2 = (V)(K.gc3 * norm2(M.beta));
     const V bx_ = (V)M.beta[0], by_ = (V)M.beta[1], bz_ = (V)M.beta[2];
     double fw = 0.0, fx = 0.0, fy = 0.0, fz = 0.0;
     if constexpr ((VR & 4) != 0) {
@@ -1197,7 +1205,7 @@ __device__ __forceinline__ void quad_cell(const TS* __restrict__ sd, const TE* _
             fw = fx * M.beta[0] + fy * M.beta[1] + fz * M.beta[2];
         }
     }
-    vec4<V> rest;  // new (f_0, g_0, 0, 0)
+    vec4<V> rest;  // new (f_0, g_0, h_rest, 0)
     {
         const V q0 = (V)K.fsh[0] - fe.template eq<0>();
         const V geq0 = (V)K.wp[0] * ng * (V(1) - gc3b2);
@@ -1205,12 +1213,11 @@ __device__ __forceinline__ void quad_cell(const TS* __restrict__ sd, const TE* _
         if constexpr ((VR & 4) != 0) f0n += (V)fw;
         rest.x = f0n;
         rest.y = (Gv[0] + wg * (geq0 - (V)K.gsh[0])) * inv1wg;
-        rest.z = V(0);
+        rest.z = (V)(2.0 * M.rho) - Hv[QH];
         rest.w = V(0);
         if constexpr (!dquad_layout<TS>())
-            if (active) st2<NT>(dd + quad_index(K, 0, cell), rest.x, rest.y);
+            if (active) st4<NT, TS>(dd, cc, rest);
     }
-    put(dd + hrest_quad_index(K, cell), (V)(2.0 * M.rho) - Hv[QH]);
     // the new quad (f, g, f-bar, g-bar) of slot s
     auto collide = [&](auto sc) {
         constexpr int s = decltype(sc)::value;
@@ -1243,7 +1250,7 @@ __device__ __forceinline__ void quad_cell(const TS* __restrict__ sd, const TE* _
             constexpr int s = decltype(ic)::value;
             if constexpr (s <= 9) {
                 const vec4<V> q = collide(ic);
-                if (active) st4<NT>(dd + quad_index(K, s, cell), q.x, q.y, q.z, q.w);
+                if (active) st4<NT, TS>(dd, cc + CHUNK * 16 * s, q);
             }
         });
     } else {
@@ -1253,29 +1260,31 @@ __device__ __forceinline__ void quad_cell(const TS* __restrict__ sd, const TE* _
                 const vec4<V> a = collide(std::integral_constant<int, 2 * r + 1>{});
                 if constexpr (r < 4) {
                     const vec4<V> b = collide(std::integral_constant<int, 2 * r + 2>{});
-                    if (active) st8<NT>(dd + dquad_index(K, r, cell), a, b);
+                    if (active) st8<NT, TS>(dd, cc + CHUNK * 16 * r, a, b);
                 } else {
-                    if (active) st8<NT>(dd + dquad_index(K, r, cell), a, rest);
+                    if (active) st8<NT, TS>(dd, cc + CHUNK * 16 * r, a, rest);
                 }
             }
         });
     }
-    const V cj = (V)(1.0 / (16.0 * 1.4142135623730951 * K.c)), ce = (V)(1.0 / (8.0 * 1.4142135623730951 * K.c));
+    const V cj = (V)(1.0 / (16.0 * 1.4142135623730951 * K.c)), cE = (V)(1.0 / (8.0 * 1.4142135623730951 * K.c));
     const V J0 = (V)M.J[0], J1 = (V)M.J[1], J2 = (V)M.J[2];
     const V E0 = (V)M.E[0], E1 = (V)M.E[1], E2 = (V)M.E[2];
 #pragma unroll
     for (int m = 0; m < 12; ++m) {
         const int k0 = 2 * m;
         const V hj = cj * (SX[k0] * J0 + SY[k0] * J1 + SZ[k0] * J2);
-        const V he = ce * (EHX[k0] * E0 + EHY[k0] * E1 + EHZ[k0] * E2);
+        const V he = cE * (EHX[k0] * E0 + EHY[k0] * E1 + EHZ[k0] * E2);
         if (active)
-            st2<NT>(dd + hpair_index(K, m, cell), V(2) * (hj + he) - Hv[k0], V(2) * (hj - he) - Hv[k0 + 1]);
+            st2<NT, TS>(dd, ch + L::H + CHUNK * L::HREC * m, V(2) * (hj + he) - Hv[k0], V(2) * (hj - he) - Hv[k0 + 1]);
     }
+    if (active) {
 #pragma unroll
-    for (int a = 0; a < 3; ++a) put(de + (int64_t)a * S + cell, M.E[a]);
-    if constexpr ((VR & 8) != 0) {
+        for (int a = 0; a < 3; ++a) st<NT, TE>(dd, ce + L::E + CHUNK * 4 * a, M.E[a]);
+        if constexpr ((VR & 8) != 0) {
 #pragma unroll
-        for (int a = 0; a < 3; ++a) put(de + (int64_t)(3 + a) * S + cell, M.B[a]);
+            for (int a = 0; a < 3; ++a) st<NT, TE>(dd, ce + L::E + CHUNK * 4 * (3 + a), M.B[a]);
+        }
     }
 }
 
@@ -1295,8 +1304,7 @@ __device__ __forceinline__ void quad_cell(const TS* __restrict__ sd, const TE* _
 // With the learned guess the network runs on whole wavefronts, so lanes past
 // a ragged edge stay and compute a copy of the edge cell without storing it.
 template <bool NT, typename TS, typename TE, typename V, int GM, int PXT, int VR = 0>
-__device__ __forceinline__ void fused_block(const TS* __restrict__ sd, const TE* __restrict__ se,
-                                            TS* __restrict__ dd, TE* __restrict__ de,
+__device__ __forceinline__ void fused_block(const char* __restrict__ sd, char* __restrict__ dd,
                                             const double* __restrict__ faceB, const GuessTables* __restrict__ gt,
                                             const Consts& K, int tiles_x, int ncol, int zb, int zg, int yw, int b) {
     // pair layout (FP64): 128 cells per row group, two lanes each; quad and double-quad layouts (FP32,
@@ -1346,10 +1354,10 @@ __device__ __forceinline__ void fused_block(const TS* __restrict__ sd, const TE*
             const int cell = xp + K.nx * (yp + K.ny * z);
             const Nbr nb = make_nbr<true>(K, xp, yp, z);
             if constexpr (ONE)
-                quad_cell<NT, TS, TE, V, GM, VR>(sd, se, dd, de, faceB, gt, K, cell, nb, xp, yp, z,
+                quad_cell<NT, TS, TE, V, GM, VR>(sd, dd, faceB, gt, K, cell, nb, xp, yp, z,
                                                  all_lanes ? active : true, bmax, gate);
             else
-                pair_cell<NT, TS, TE, V, GM, VR>(sd, se, dd, de, faceB, gt, K, cell, nb, hp, xp, yp, z,
+                pair_cell<NT, TS, TE, V, GM, VR>(sd, dd, faceB, gt, K, cell, nb, hp, xp, yp, z,
                                                  all_lanes ? active : true, bmax, gate);
         }
     }
@@ -1362,9 +1370,8 @@ __device__ __forceinline__ void fused_block(const TS* __restrict__ sd, const TE*
 }
 
 template <bool NT, typename TS, typename TE, typename V, int GM, int PXT, int VR>
-__global__ __launch_bounds__(PTPB, (fused_waves<TS, GM>())) void k_fused_step(const TS* __restrict__ sd, const TE* __restrict__ se,
-                                                        TS* __restrict__ dd, TE* __restrict__ de,
-                                                        const double* __restrict__ faceB,
+__global__ __launch_bounds__(PTPB, FUSED_WAVES) void k_fused_step(const char* __restrict__ sd,
+                                                        char* __restrict__ dd, const double* __restrict__ faceB,
                                                         const GuessTables* __restrict__ gt, Consts K,
                                                         int tiles_x, int ncol, int zb, int zg, int yw, int nblk) {
     const int b = tile_of_block(nblk);
@@ -1378,7 +1385,7 @@ __global__ __launch_bounds__(PTPB, (fused_waves<TS, GM>())) void k_fused_step(co
         if (*K.gflag_rd != K.gstep - 1) return;
         if (blockIdx.x == 0 && threadIdx.x == 0 && K.gcount) *K.gcount += 1;  // one writer per step
     }
-    fused_block<NT, TS, TE, V, GM, PXT, VR>(sd, se, dd, de, faceB, gt, K, tiles_x, ncol, zb, zg, yw, b);
+    fused_block<NT, TS, TE, V, GM, PXT, VR>(sd, dd, faceB, gt, K, tiles_x, ncol, zb, zg, yw, b);
 }
 
 // Index of the instance whose range [first[i], first[i + 1]) holds v (first
@@ -1410,21 +1417,20 @@ __global__ __launch_bounds__(PTPB, WV) void k_fused_batch(const BatchInst* __res
     const int i = find_instance(ninst, b, [&](int j) { return I[j].blk0; });
     const BatchInst& B = I[i];
     fused_block<NT, TS, TE, V, GUESS_NONE, PXT>(
-        (const TS*)B.dist[parity], (const TE*)B.efield[parity], (TS*)B.dist[1 - parity], (TE*)B.efield[1 - parity],
-        B.faceB, nullptr, B.K, B.tiles_x, B.ncol, B.zb, 1, B.yw, (int)(b - B.blk0));
+        B.buf[parity], B.buf[1 - parity], B.faceB, nullptr, B.K, B.tiles_x, B.ncol, B.zb, 1, B.yw, (int)(b - B.blk0));
 }
 
 // B of Eq. Cal_B at a cell from the streamed h (population order, FP64).
 template <typename TS>
-__device__ __forceinline__ double streamed_B(const TS* __restrict__ src, const Consts& K, int comp, int x, int y,
+__device__ __forceinline__ double streamed_B(const char* __restrict__ src, const Consts& K, int comp, int x, int y,
                                              int z) {
     const Nbr nb = make_nbr<true>(K, x, y, z);
-    const int cell = x + K.nx * (y + K.ny * z);
+    const int pos = (int)K.g0 + x + K.nx * (y + K.ny * z);
     double b = 0.0;
 #pragma unroll
     for (int k = 0; k < QH; ++k) {
         const int bk = comp == 0 ? BHX[k] : (comp == 1 ? BHY[k] : BHZ[k]);
-        if (bk) b += bk * ld(src, h_at<TS>(K, k, (int64_t)cell + nb.at(-SX[k], -SY[k], -SZ[k])));
+        if (bk) b += bk * ld<TS>(src, h_at<TS>(K, k, pos + nb.at(-SX[k], -SY[k], -SZ[k])));
     }
     return b;
 }
@@ -1437,7 +1443,7 @@ __device__ __forceinline__ double streamed_B(const TS* __restrict__ src, const C
 //                  high face B_a = B_a(x - e_a) - dx sum_{b != a} d_b B_b.
 // One thread per face cell over the six faces; inactive faces return.
 template <typename TS>
-__device__ __forceinline__ void face_b_cell(const TS* __restrict__ src, const Consts& K, double* __restrict__ faceB,
+__device__ __forceinline__ void face_b_cell(const char* __restrict__ src, const Consts& K, double* __restrict__ faceB,
                                             int64_t i) {
     if (i >= K.fo[6]) return;
     int f = 0;
@@ -1464,15 +1470,15 @@ __device__ __forceinline__ void face_b_cell(const TS* __restrict__ src, const Co
 #pragma unroll
     for (int b = 0; b < 3; ++b)
         if (b != a)
-            dsum += axis_derivative(K, b, x, y, z, [&](int xx, int yy, int zz) { return streamed_B(src, K, b, xx, yy, zz); });
+            dsum += axis_derivative(K, b, x, y, z, [&](int xx, int yy, int zz) { return streamed_B<TS>(src, K, b, xx, yy, zz); });
     const int s = high ? -1 : 1;
-    const double inner = streamed_B(src, K, a, x + s * (a == 0), y + s * (a == 1), z + s * (a == 2));
+    const double inner = streamed_B<TS>(src, K, a, x + s * (a == 0), y + s * (a == 1), z + s * (a == 2));
     faceB[i] = high ? inner - K.dx * dsum : inner + K.dx * dsum;
 }
 
 template <typename TS>
-__global__ __launch_bounds__(256) void k_face_b(const TS* __restrict__ src, Consts K, double* __restrict__ faceB) {
-    face_b_cell(src, K, faceB, (int64_t)blockIdx.x * 256 + threadIdx.x);
+__global__ __launch_bounds__(256) void k_face_b(const char* __restrict__ src, Consts K, double* __restrict__ faceB) {
+    face_b_cell<TS>(src, K, faceB, (int64_t)blockIdx.x * 256 + threadIdx.x);
 }
 
 // The face pass of every instance of a batch in one launch.
@@ -1484,7 +1490,7 @@ __global__ __launch_bounds__(256) void k_face_b_batch(const BatchInst* __restric
     const int i = find_instance(ninst, g, [&](int j) { return I[j].face0; });
     const BatchInst& B = I[i];
     if (!B.K.divb) return;
-    face_b_cell((const TS*)B.dist[parity], B.K, B.faceB, g - B.face0);
+    face_b_cell<TS>(B.buf[parity], B.K, B.faceB, g - B.face0);
 }
 
 // Persistent batched run: nsteps steps in one cooperative launch whose grid
@@ -1527,8 +1533,7 @@ __global__ __launch_bounds__(PTPB, WV) void k_fused_batch_persistent(const Batch
                 const int i = find_instance(ninst, b, [&](int jj) { return I[jj].blk0; });
                 const BatchInst& B = I[i];
                 fused_block<NT, TS, TE, V, GUESS_NONE, PXT>(
-                    (const TS*)B.dist[parity], (const TE*)B.efield[parity], (TS*)B.dist[1 - parity],
-                    (TE*)B.efield[1 - parity], B.faceB, nullptr, B.K, B.tiles_x, B.ncol, B.zb, 1, B.yw,
+                    B.buf[parity], B.buf[1 - parity], B.faceB, nullptr, B.K, B.tiles_x, B.ncol, B.zb, 1, B.yw,
                     (int)(b - B.blk0));
             }
             if (threadIdx.x == 0) tile_sh = nj;
@@ -1576,8 +1581,7 @@ constexpr double NO_INDEX = 9.0e15;  // larger than any cell index, exact in FP6
 // Every thread runs the cell pass (on the edge cell when past a ragged edge,
 // so that the network sees whole wavefronts); only real cells write.
 template <typename TS, typename TE, int GM>
-__global__ __launch_bounds__(TPB) void k_moments(const TS* __restrict__ src, const TE* __restrict__ esrc,
-                                                 const double* __restrict__ faceB,
+__global__ __launch_bounds__(TPB) void k_moments(const char* __restrict__ src, const double* __restrict__ faceB,
                                                  const GuessTables* __restrict__ gt, Consts K, int tiles_x,
                                                  int tiles_y, int ntiles, OutPtrs out, double* __restrict__ scratch,
                                                  double* __restrict__ part, double* __restrict__ nullp) {
@@ -1594,11 +1598,11 @@ __global__ __launch_bounds__(TPB) void k_moments(const TS* __restrict__ src, con
     const Nbr nb = make_nbr<true>(K, x, y, z);
     Macro M;
     if constexpr (GM == GUESS_NONE)
-        macroscopic<GM>(src, esrc, faceB, gt, K, cell, nb, x, y, z, M);
+        macroscopic<GM, TS, TE>(src, faceB, gt, K, cell, nb, x, y, z, M);
     else if (*K.gflag_rd == K.gstep - 1)  // the guess the next step would take
-        macroscopic<GM>(src, esrc, faceB, gt, K, cell, nb, x, y, z, M);
+        macroscopic<GM, TS, TE>(src, faceB, gt, K, cell, nb, x, y, z, M);
     else
-        macroscopic<GUESS_MONITOR>(src, esrc, faceB, gt, K, cell, nb, x, y, z, M);
+        macroscopic<GUESS_MONITOR, TS, TE>(src, faceB, gt, K, cell, nb, x, y, z, M);
     if (active) {
         const double c = K.c;
         if (out.n) out.n[cell] = M.n;
@@ -1759,9 +1763,9 @@ __global__ __launch_bounds__(TPB) void k_face_check(FacePtrs in, Consts K, doubl
 // E = -u x B, B) (stored minus their shifts), h* = h_eq of (J, E + q J, B)
 // with J of Eq. Ohm at zero charge (h* = h_eq is the fixed point of the
 // tau_h = 1/2 collision), rest h* = 0 and E_prev = E; both planes the same.
-// dd, de point at cell 0 of the state buffer; the planes sit just below it.
+// The planes sit just below cell 0 of the state buffer.
 template <typename TS, typename TE>
-__global__ __launch_bounds__(TPB) void k_init_ghost(FacePtrs in, Consts K, TS* __restrict__ dd, TE* __restrict__ de) {
+__global__ __launch_bounds__(TPB) void k_init_ghost(FacePtrs in, Consts K, char* __restrict__ dd) {
     const int64_t i = (int64_t)blockIdx.x * TPB + threadIdx.x;
     const int64_t plane = (int64_t)K.nx * K.ny;
     if (i >= plane) return;
@@ -1790,28 +1794,27 @@ __global__ __launch_bounds__(TPB) void k_init_ghost(FacePtrs in, Consts K, TS* _
     fe.setup(eps, p, gam, beta, E, Bv, c, K.eps0);
     const double cj = 1.0 / (16.0 * 1.4142135623730951 * c), ce = 1.0 / (8.0 * 1.4142135623730951 * c);
     for (int layer = 1; layer <= 2; ++layer) {
-        const int64_t g = i - layer * plane;  // offset of the ghost cell from cell 0
+        const int g = (int)K.g0 + (int)(i - layer * plane);  // position of the ghost cell
         static_for<0>([&](auto ic) {
             constexpr int q = decltype(ic)::value;
             const double eb = EX[q] * beta[0] + EY[q] * beta[1] + EZ[q] * beta[2];
             const double wpi = q == 0 ? K.wp[0] : (q <= 6 ? K.wp[1] : K.wp[2]);
-            dd[f_at<TS>(K, q, g)] = static_cast<TS>(fe.template eq<q>() - fshift(K, q));
-            dd[g_at<TS>(K, q, g)] =
-                static_cast<TS>(wpi * n * gam * (1.0 + K.gc1 * eb + K.gc2 * eb * eb - K.gc3 * b2) - gshift(K, q));
+            st2<false, TS>(dd, f_at<TS>(K, q, g), fe.template eq<q>() - fshift(K, q),
+                           wpi * n * gam * (1.0 + K.gc1 * eb + K.gc2 * eb * eb - K.gc3 * b2) - gshift(K, q));
         });
 #pragma unroll
         for (int k = 0; k < QH; ++k) {
             const double heq = cj * (SX[k] * J[0] + SY[k] * J[1] + SZ[k] * J[2]) +
                                ce * (EHX[k] * Epr[0] + EHY[k] * Epr[1] + EHZ[k] * Epr[2]) +
                                0.125 * (BHX[k] * Bv[0] + BHY[k] * Bv[1] + BHZ[k] * Bv[2]);
-            dd[h_at<TS>(K, k, g)] = static_cast<TS>(heq);
+            st<false, TS>(dd, h_at<TS>(K, k, g), heq);
         }
-        dd[h_at<TS>(K, QH, g)] = static_cast<TS>(0.0);
+        st<false, TS>(dd, h_at<TS>(K, QH, g), 0.0);
 #pragma unroll
-        for (int a = 0; a < 3; ++a) de[(int64_t)a * K.stride + g] = static_cast<TE>(E[a]);
+        for (int a = 0; a < 3; ++a) st<false, TE>(dd, e_at<TS>(K, a, g), E[a]);
         if (K.bprev)
 #pragma unroll
-            for (int a = 0; a < 3; ++a) de[(int64_t)(3 + a) * K.stride + g] = static_cast<TE>(Bv[a]);
+            for (int a = 0; a < 3; ++a) st<false, TE>(dd, e_at<TS>(K, 3 + a, g), Bv[a]);
     }
 }
 
@@ -1854,8 +1857,7 @@ __global__ __launch_bounds__(TPB) void k_init_current(InPtrs in, Consts K, int t
 // h*_k(x) = h_eq-form at x + s_k, h*_rest = rho_c, E_prev = E0.
 template <typename TS, typename TE>
 __global__ __launch_bounds__(TPB) void k_init_state(InPtrs in, Consts K, int tiles_x, int tiles_y, int ntiles,
-                                                    const double* __restrict__ scr, TS* __restrict__ dst,
-                                                    TE* __restrict__ edst) {
+                                                    const double* __restrict__ scr, char* __restrict__ dst) {
     const int tile = tile_of_block(ntiles);
     if (tile >= ntiles) return;
     const int tx = tile % tiles_x, rest = tile / tiles_x;
@@ -1873,6 +1875,7 @@ __global__ __launch_bounds__(TPB) void k_init_state(InPtrs in, Consts K, int til
         Bv[a] = in.B[a][cell];
         beta[a] = u[a] / c;
     }
+    const int pos = (int)K.g0 + cell;
     const double n = in.n[cell], p = in.p[cell];
     const double b2 = beta[0] * beta[0] + beta[1] * beta[1] + beta[2] * beta[2];
     const double gam = 1.0 / sqrt(1.0 - b2);
@@ -1883,9 +1886,8 @@ __global__ __launch_bounds__(TPB) void k_init_state(InPtrs in, Consts K, int til
         constexpr int i = decltype(ic)::value;
         const double eb = EX[i] * beta[0] + EY[i] * beta[1] + EZ[i] * beta[2];
         const double wpi = i == 0 ? K.wp[0] : (i <= 6 ? K.wp[1] : K.wp[2]);
-        dst[f_at<TS>(K, i, cell)] = static_cast<TS>(fe.template eq<i>() - fshift(K, i));
-        dst[g_at<TS>(K, i, cell)] =
-            static_cast<TS>(wpi * n * gam * (1.0 + K.gc1 * eb + K.gc2 * eb * eb - K.gc3 * b2) - gshift(K, i));
+        st2<false, TS>(dst, f_at<TS>(K, i, pos), fe.template eq<i>() - fshift(K, i),
+                       wpi * n * gam * (1.0 + K.gc1 * eb + K.gc2 * eb * eb - K.gc3 * b2) - gshift(K, i));
     });
     const double cj = 1.0 / (16.0 * 1.4142135623730951 * c), ce = 1.0 / (8.0 * 1.4142135623730951 * c);
 #pragma unroll
@@ -1895,7 +1897,7 @@ __global__ __launch_bounds__(TPB) void k_init_state(InPtrs in, Consts K, int til
         const double P0 = scr[3 * K.N + t], P1 = scr[4 * K.N + t], P2 = scr[5 * K.N + t];
         const double heq = cj * (SX[k] * J0 + SY[k] * J1 + SZ[k] * J2) + ce * (EHX[k] * P0 + EHY[k] * P1 + EHZ[k] * P2) +
                            0.125 * (BHX[k] * in.B[0][t] + BHY[k] * in.B[1][t] + BHZ[k] * in.B[2][t]);
-        dst[h_at<TS>(K, k, cell)] = static_cast<TS>(heq);
+        st<false, TS>(dst, h_at<TS>(K, k, pos), heq);
     }
     double rho;
     if (in.rho_c) {
@@ -1906,49 +1908,43 @@ __global__ __launch_bounds__(TPB) void k_init_state(InPtrs in, Consts K, int til
                (in.E[1][cell + nb.at(0, 1, 0)] - in.E[1][cell + nb.at(0, -1, 0)]) +
                (in.E[2][cell + nb.at(0, 0, 1)] - in.E[2][cell + nb.at(0, 0, -1)]));
     }
-    dst[h_at<TS>(K, QH, cell)] = static_cast<TS>(rho);
+    st<false, TS>(dst, h_at<TS>(K, QH, pos), rho);
 #pragma unroll
-    for (int a = 0; a < 3; ++a) edst[(int64_t)a * K.stride + cell] = static_cast<TE>(Ep[a]);
+    for (int a = 0; a < 3; ++a) st<false, TE>(dst, e_at<TS>(K, a, pos), Ep[a]);
     if (K.bprev)
 #pragma unroll
-        for (int a = 0; a < 3; ++a) edst[(int64_t)(3 + a) * K.stride + cell] = static_cast<TE>(Bv[a]);
+        for (int a = 0; a < 3; ++a) st<false, TE>(dst, e_at<TS>(K, 3 + a, pos), Bv[a]);
 }
 
 // Raw state conversion to / from the FP64 interface layout (shifts added back).
 template <typename TS, typename TE>
-__global__ void k_export(const TS* __restrict__ s, const TE* __restrict__ se, double* __restrict__ d, Consts K) {
+__global__ void k_export(const char* __restrict__ s, double* __restrict__ d, Consts K) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= K.N * state_arrays(K)) return;
-    const int64_t a = i / K.N, cell = i - a * K.N;
-    if (a < OFF_E) {
-        double v;
-        if (a < OFF_G)
-            v = static_cast<double>(s[f_at<TS>(K, (int)a, cell)]) + fshift(K, (int)a);
-        else if (a < OFF_H)
-            v = static_cast<double>(s[g_at<TS>(K, (int)(a - OFF_G), cell)]) + gshift(K, (int)(a - OFF_G));
-        else
-            v = static_cast<double>(s[h_at<TS>(K, (int)(a - OFF_H), cell)]);
-        d[i] = v;
-    } else {
-        d[i] = static_cast<double>(se[(a - OFF_E) * K.stride + cell]);
-    }
+    const int a = (int)(i / K.N), pos = (int)K.g0 + (int)(i - a * K.N);
+    if (a < OFF_G)
+        d[i] = ld<TS>(s, f_at<TS>(K, a, pos)) + fshift(K, a);
+    else if (a < OFF_H)
+        d[i] = ld<TS>(s, g_at<TS>(K, a - OFF_G, pos)) + gshift(K, a - OFF_G);
+    else if (a < OFF_E)
+        d[i] = ld<TS>(s, h_at<TS>(K, a - OFF_H, pos));
+    else
+        d[i] = ld<TE>(s, e_at<TS>(K, a - OFF_E, pos));
 }
 
 template <typename TS, typename TE>
-__global__ void k_import(const double* __restrict__ s, TS* __restrict__ d, TE* __restrict__ de, Consts K) {
+__global__ void k_import(const double* __restrict__ s, char* __restrict__ d, Consts K) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= K.N * state_arrays(K)) return;
-    const int64_t a = i / K.N, cell = i - a * K.N;
-    if (a < OFF_E) {
-        if (a < OFF_G)
-            d[f_at<TS>(K, (int)a, cell)] = static_cast<TS>(s[i] - fshift(K, (int)a));
-        else if (a < OFF_H)
-            d[g_at<TS>(K, (int)(a - OFF_G), cell)] = static_cast<TS>(s[i] - gshift(K, (int)(a - OFF_G)));
-        else
-            d[h_at<TS>(K, (int)(a - OFF_H), cell)] = static_cast<TS>(s[i]);
-    } else {
-        de[(a - OFF_E) * K.stride + cell] = static_cast<TE>(s[i]);
-    }
+    const int a = (int)(i / K.N), pos = (int)K.g0 + (int)(i - a * K.N);
+    if (a < OFF_G)
+        st<false, TS>(d, f_at<TS>(K, a, pos), s[i] - fshift(K, a));
+    else if (a < OFF_H)
+        st<false, TS>(d, g_at<TS>(K, a - OFF_G, pos), s[i] - gshift(K, a - OFF_G));
+    else if (a < OFF_E)
+        st<false, TS>(d, h_at<TS>(K, a - OFF_H, pos), s[i]);
+    else
+        st<false, TE>(d, e_at<TS>(K, a - OFF_E, pos), s[i]);
 }
 
 // (features, targets) of sampled cells of the current state with the plain
@@ -1956,7 +1952,7 @@ __global__ void k_import(const double* __restrict__ s, TS* __restrict__ d, TE* _
 // Per-block partial sums of F, F^2, T, T^2 and failed cells into part (17 per block).
 
 template <typename TS, typename TE>
-__global__ __launch_bounds__(256) void k_guess_samples(const TS* __restrict__ src, const TE* __restrict__ esrc,
+__global__ __launch_bounds__(256) void k_guess_samples(const char* __restrict__ src,
                                                        const double* __restrict__ faceB, Consts K, int ns,
                                                        double* __restrict__ F, double* __restrict__ T,
                                                        double* __restrict__ part) {
@@ -1967,7 +1963,7 @@ __global__ __launch_bounds__(256) void k_guess_samples(const TS* __restrict__ sr
         const int x = (int)(cell % K.nx), y = (int)((cell / K.nx) % K.ny), z = (int)(cell / ((int64_t)K.nx * K.ny));
         const Nbr nb = make_nbr<true>(K, x, y, z);
         Macro M;
-        macroscopic<GUESS_NONE>(src, esrc, faceB, nullptr, K, (int)cell, nb, x, y, z, M);
+        macroscopic<GUESS_NONE, TS, TE>(src, faceB, nullptr, K, (int)cell, nb, x, y, z, M);
         double Ef, S[3], Pi[6];
         fluid_tensor(K, M, M.B, Ef, S, Pi);  // the guess is not offered with the previous-B reading
         double f[6], sn;
@@ -2036,10 +2032,10 @@ int num_tiles(const Consts& K) {
 }
 
 template <typename TS>
-hipError_t launch_face_b(const StateBuf& src, const Consts& K, double* faceB, hipStream_t s) {
+hipError_t launch_face_b(const char* src, const Consts& K, double* faceB, hipStream_t s) {
     if (!K.divb) return hipSuccess;
     const int64_t blocks = (K.fo[6] + 255) / 256;
-    hipLaunchKernelGGL((k_face_b<TS>), dim3((unsigned)blocks), dim3(256), 0, s, (const TS*)src.dist, K, faceB);
+    hipLaunchKernelGGL((k_face_b<TS>), dim3((unsigned)blocks), dim3(256), 0, s, src, K, faceB);
     return hipGetLastError();
 }
 
@@ -2051,19 +2047,18 @@ void step_geometry(const Consts& K, int px, int zb, int zg, int yw, int cpb, int
 }
 
 template <typename TS, int GM, int PXT, int VR = 0>
-static void launch_fused(const TS* sd, const void* se, TS* dd, void* de, double* faceB, const GuessTables* gt,
-                         const Consts& K, int zb, int zg, int yw, hipStream_t s) {
+static void launch_fused(const char* sd, char* dd, double* faceB, const GuessTables* gt, const Consts& K, int zb, int zg, int yw, hipStream_t s) {
     using TE = typename StoreTypes<TS>::E;
     using V = typename StoreTypes<TS>::V;
     int tx, ncol, nblk;
     step_geometry(K, PXT, zb, zg, yw, cells_per_block(quad_layout<TS>()), tx, ncol, nblk);
     const int grid = ((nblk + 7) / 8) * 8;
-    hipLaunchKernelGGL((k_fused_step<true, TS, TE, V, GM, PXT, VR>), dim3(grid), dim3(PTPB), 0, s, sd, (const TE*)se, dd,
-                       (TE*)de, (const double*)faceB, gt, K, tx, ncol, zb, zg, yw, nblk);
+    hipLaunchKernelGGL((k_fused_step<true, TS, TE, V, GM, PXT, VR>), dim3(grid), dim3(PTPB), 0, s, sd, dd,
+                       (const double*)faceB, gt, K, tx, ncol, zb, zg, yw, nblk);
 }
 
 template <typename TS>
-hipError_t launch_step(const StateBuf& src, const StateBuf& dst, const Consts& K, const StepTuning& tune,
+hipError_t launch_step(const char* src, char* dst, const Consts& K, const StepTuning& tune,
                        double* faceB, const GuessTables* gt, hipStream_t s) {
     hipError_t e = launch_face_b<TS>(src, K, faceB, s);
     if (e != hipSuccess) return e;
@@ -2071,21 +2066,17 @@ hipError_t launch_step(const StateBuf& src, const StateBuf& dst, const Consts& K
     // interleaved walks: zg blocks per column and chunk (the force path keeps
     // zg = 1, the geometry its per-wavefront maxima are sized for)
     const int zg = (tune.zg > 1 && !K.forced) ? tune.zg : 1;
-    const TS* sd = (const TS*)src.dist;
-    TS* dd = (TS*)dst.dist;
     const int vr = (K.coll ? 1 : 0) | (K.flux ? 2 : 0);
     const int yw = tune.yw > 1 && !K.forced ? tune.yw : 1;  // the force's partial maxima are sized for yw = 1
-    const void* se = src.efield;
-    void* de = dst.efield;
     if (K.bprev) {  // the previous-B reading: 64-wide tiles, default collision and faces, no guess or force
         if (gt || vr || K.forced) return hipErrorNotSupported;
-        launch_fused<TS, GUESS_NONE, 64, 8>(sd, se, dd, de, faceB, gt, K, zb, zg, yw, s);
+        launch_fused<TS, GUESS_NONE, 64, 8>(src, dst, faceB, gt, K, zb, zg, yw, s);
     } else if (K.forced) {  // the external force: 64-wide tiles, MUSCL faces, no guess
         if (gt || K.flux) return hipErrorNotSupported;
         if (K.coll)
-            launch_fused<TS, GUESS_NONE, 64, 5>(sd, se, dd, de, faceB, gt, K, zb, 1, 1, s);
+            launch_fused<TS, GUESS_NONE, 64, 5>(src, dst, faceB, gt, K, zb, 1, 1, s);
         else
-            launch_fused<TS, GUESS_NONE, 64, 4>(sd, se, dd, de, faceB, gt, K, zb, 1, 1, s);
+            launch_fused<TS, GUESS_NONE, 64, 4>(src, dst, faceB, gt, K, zb, 1, 1, s);
         int tx, ncol, nblk;
         step_geometry(K, 64, zb, 1, 1, cells_per_block(quad_layout<TS>()), tx, ncol, nblk);
         hipLaunchKernelGGL(k_vmax_reduce, dim3(1), dim3(TPB), 0, s, K.vmax_part, (int64_t)nblk * (PTPB / 64),
@@ -2093,24 +2084,24 @@ hipError_t launch_step(const StateBuf& src, const StateBuf& dst, const Consts& K
     } else if (vr) {  // the alternative readings: 64-wide tiles, no guess
         if (gt) return hipErrorNotSupported;
         if (vr == 1)
-            launch_fused<TS, GUESS_NONE, 64, 1>(sd, se, dd, de, faceB, gt, K, zb, zg, yw, s);
+            launch_fused<TS, GUESS_NONE, 64, 1>(src, dst, faceB, gt, K, zb, zg, yw, s);
         else if (vr == 2)
-            launch_fused<TS, GUESS_NONE, 64, 2>(sd, se, dd, de, faceB, gt, K, zb, zg, yw, s);
+            launch_fused<TS, GUESS_NONE, 64, 2>(src, dst, faceB, gt, K, zb, zg, yw, s);
         else
-            launch_fused<TS, GUESS_NONE, 64, 3>(sd, se, dd, de, faceB, gt, K, zb, zg, yw, s);
+            launch_fused<TS, GUESS_NONE, 64, 3>(src, dst, faceB, gt, K, zb, zg, yw, s);
     } else if (gt) {  // the guess path is built for 64-wide tiles only; one cell per lane in the quad layout
         if constexpr (quad_layout<TS>())
-            launch_fused<TS, GUESS_SINGLE, 64>(sd, se, dd, de, faceB, gt, K, zb, zg, yw, s);
+            launch_fused<TS, GUESS_SINGLE, 64>(src, dst, faceB, gt, K, zb, zg, yw, s);
         else
-            launch_fused<TS, GUESS_PAIR, 64>(sd, se, dd, de, faceB, gt, K, zb, zg, yw, s);
-        launch_fused<TS, GUESS_MONITOR, 64>(sd, se, dd, de, faceB, gt, K, zb, zg, yw, s);
+            launch_fused<TS, GUESS_PAIR, 64>(src, dst, faceB, gt, K, zb, zg, yw, s);
+        launch_fused<TS, GUESS_MONITOR, 64>(src, dst, faceB, gt, K, zb, zg, yw, s);
     }
     else if (tune.px == 32)
-        launch_fused<TS, GUESS_NONE, 32>(sd, se, dd, de, faceB, gt, K, zb, zg, yw, s);
+        launch_fused<TS, GUESS_NONE, 32>(src, dst, faceB, gt, K, zb, zg, yw, s);
     else if (tune.px == 16)
-        launch_fused<TS, GUESS_NONE, 16>(sd, se, dd, de, faceB, gt, K, zb, zg, yw, s);
+        launch_fused<TS, GUESS_NONE, 16>(src, dst, faceB, gt, K, zb, zg, yw, s);
     else
-        launch_fused<TS, GUESS_NONE, 64>(sd, se, dd, de, faceB, gt, K, zb, zg, yw, s);
+        launch_fused<TS, GUESS_NONE, 64>(src, dst, faceB, gt, K, zb, zg, yw, s);
     return hipGetLastError();
 }
 
@@ -2149,7 +2140,7 @@ hipError_t launch_batch(const BatchInst* dev, int ninst, int total_blocks, int64
         else
             launch_batch_px<TS, 2>(dev, ninst, total_blocks, px, parity, s);
     } else {
-        launch_batch_px<TS, fused_waves<TS, 0>()>(dev, ninst, total_blocks, px, parity, s);
+        launch_batch_px<TS, FUSED_WAVES>(dev, ninst, total_blocks, px, parity, s);
     }
     return hipGetLastError();
 }
@@ -2205,13 +2196,13 @@ hipError_t launch_batch_persistent(const BatchInst* dev, int ninst, int total_bl
             return launch_persistent_px<TS, 3>(dev, ninst, total_blocks, px, parity, nsteps, next, s);
         return launch_persistent_px<TS, 2>(dev, ninst, total_blocks, px, parity, nsteps, next, s);
     } else {
-        return launch_persistent_px<TS, fused_waves<TS, 0>()>(dev, ninst, total_blocks, px, parity, nsteps, next,
+        return launch_persistent_px<TS, FUSED_WAVES>(dev, ninst, total_blocks, px, parity, nsteps, next,
                                                                s);
     }
 }
 
 template <typename TS>
-hipError_t launch_moments(const StateBuf& src, const Consts& K, const OutPtrs& out, const DiagBufs& D,
+hipError_t launch_moments(const char* src, const Consts& K, const OutPtrs& out, const DiagBufs& D,
                           const GuessTables* gt, hipStream_t s) {
     using TE = typename StoreTypes<TS>::E;
     int tx, ty, nt, nb;
@@ -2219,12 +2210,12 @@ hipError_t launch_moments(const StateBuf& src, const Consts& K, const OutPtrs& o
     hipError_t e = launch_face_b<TS>(src, K, D.faceB, s);
     if (e != hipSuccess) return e;
     if (gt)
-        hipLaunchKernelGGL((k_moments<TS, TE, GUESS_SINGLE>), dim3(nb), dim3(TPB), 0, s, (const TS*)src.dist,
-                           (const TE*)src.efield, (const double*)D.faceB, gt, K, tx, ty, nt, out, D.scratch, D.part,
+        hipLaunchKernelGGL((k_moments<TS, TE, GUESS_SINGLE>), dim3(nb), dim3(TPB), 0, s, src,
+                           (const double*)D.faceB, gt, K, tx, ty, nt, out, D.scratch, D.part,
                            D.nullp);
     else
-        hipLaunchKernelGGL((k_moments<TS, TE, GUESS_NONE>), dim3(nb), dim3(TPB), 0, s, (const TS*)src.dist,
-                           (const TE*)src.efield, (const double*)D.faceB, gt, K, tx, ty, nt, out, D.scratch, D.part,
+        hipLaunchKernelGGL((k_moments<TS, TE, GUESS_NONE>), dim3(nb), dim3(TPB), 0, s, src,
+                           (const double*)D.faceB, gt, K, tx, ty, nt, out, D.scratch, D.part,
                            D.nullp);
     hipLaunchKernelGGL(k_divb, dim3(nb), dim3(TPB), 0, s, (const double*)D.scratch, K, tx, ty, nt, D.part2);
     hipLaunchKernelGGL(k_reduce, dim3(1), dim3(TPB), 0, s, (const double*)D.part, nt, NPART, 0, D.result);
@@ -2251,10 +2242,10 @@ hipError_t launch_face_check(const FacePtrs& in, const Consts& K, double* part, 
 }
 
 template <typename TS>
-hipError_t launch_ghost(const FacePtrs& in, const Consts& K, const StateBuf& dst, hipStream_t s) {
+hipError_t launch_ghost(const FacePtrs& in, const Consts& K, char* dst, hipStream_t s) {
     using TE = typename StoreTypes<TS>::E;
     const int nblk = (int)(((int64_t)K.nx * K.ny + TPB - 1) / TPB);
-    hipLaunchKernelGGL((k_init_ghost<TS, TE>), dim3(nblk), dim3(TPB), 0, s, in, K, (TS*)dst.dist, (TE*)dst.efield);
+    hipLaunchKernelGGL((k_init_ghost<TS, TE>), dim3(nblk), dim3(TPB), 0, s, in, K, dst);
     return hipGetLastError();
 }
 
@@ -2266,63 +2257,59 @@ hipError_t launch_init_ref(const InPtrs& in, const Consts& K, double* part, doub
 }
 
 template <typename TS>
-hipError_t launch_init(const InPtrs& in, const Consts& K, double* scr, const StateBuf& dst, hipStream_t s) {
+hipError_t launch_init(const InPtrs& in, const Consts& K, double* scr, char* dst, hipStream_t s) {
     using TE = typename StoreTypes<TS>::E;
     int tx, ty, nt, nb;
     grid_of(K, tx, ty, nt, nb);
     hipLaunchKernelGGL(k_init_current, dim3(nb), dim3(TPB), 0, s, in, K, tx, ty, nt, scr);
-    hipLaunchKernelGGL((k_init_state<TS, TE>), dim3(nb), dim3(TPB), 0, s, in, K, tx, ty, nt, (const double*)scr,
-                       (TS*)dst.dist, (TE*)dst.efield);
+    hipLaunchKernelGGL((k_init_state<TS, TE>), dim3(nb), dim3(TPB), 0, s, in, K, tx, ty, nt, (const double*)scr, dst);
     return hipGetLastError();
 }
 
 template <typename TS>
-hipError_t launch_export(const StateBuf& src, double* dst, const Consts& K, hipStream_t s) {
+hipError_t launch_export(const char* src, double* dst, const Consts& K, hipStream_t s) {
     using TE = typename StoreTypes<TS>::E;
     const int64_t total = K.N * state_arrays(K);
     const int64_t blocks = (total + 255) / 256;
-    hipLaunchKernelGGL((k_export<TS, TE>), dim3((unsigned)blocks), dim3(256), 0, s, (const TS*)src.dist,
-                       (const TE*)src.efield, dst, K);
+    hipLaunchKernelGGL((k_export<TS, TE>), dim3((unsigned)blocks), dim3(256), 0, s, src, dst, K);
     return hipGetLastError();
 }
 
 template <typename TS>
-hipError_t launch_import(const double* src, const StateBuf& dst, const Consts& K, hipStream_t s) {
+hipError_t launch_import(const double* src, char* dst, const Consts& K, hipStream_t s) {
     using TE = typename StoreTypes<TS>::E;
     const int64_t total = K.N * state_arrays(K);
     const int64_t blocks = (total + 255) / 256;
-    hipLaunchKernelGGL((k_import<TS, TE>), dim3((unsigned)blocks), dim3(256), 0, s, src, (TS*)dst.dist,
-                       (TE*)dst.efield, K);
+    hipLaunchKernelGGL((k_import<TS, TE>), dim3((unsigned)blocks), dim3(256), 0, s, src, dst, K);
     return hipGetLastError();
 }
 
 template <typename TS>
-hipError_t launch_guess_samples(const StateBuf& src, const Consts& K, double* faceB, int ns, double* F, double* T,
+hipError_t launch_guess_samples(const char* src, const Consts& K, double* faceB, int ns, double* F, double* T,
                                 double* part, double* result, hipStream_t s) {
     using TE = typename StoreTypes<TS>::E;
     hipError_t e = launch_face_b<TS>(src, K, faceB, s);
     if (e != hipSuccess) return e;
     const int nblk = (ns + 255) / 256;
-    hipLaunchKernelGGL((k_guess_samples<TS, TE>), dim3(nblk), dim3(256), 0, s, (const TS*)src.dist,
-                       (const TE*)src.efield, (const double*)faceB, K, ns, F, T, part);
+    hipLaunchKernelGGL((k_guess_samples<TS, TE>), dim3(nblk), dim3(256), 0, s, src, (const double*)faceB, K, ns, F, T, part);
     hipLaunchKernelGGL(k_reduce, dim3(1), dim3(256), 0, s, (const double*)part, nblk, SAMPLE_SUMS, 0, result);
     return hipGetLastError();
 }
 
 #define RMHD_INSTANTIATE(TS)                                                                                          \
-    template hipError_t launch_step<TS>(const StateBuf&, const StateBuf&, const Consts&, const StepTuning&, double*,  \
+    template hipError_t launch_step<TS>(const char*, char*, const Consts&, const StepTuning&, double*,  \
                                         const GuessTables*, hipStream_t);                                             \
-    template hipError_t launch_moments<TS>(const StateBuf&, const Consts&, const OutPtrs&, const DiagBufs&,           \
+    template hipError_t launch_moments<TS>(const char*, const Consts&, const OutPtrs&, const DiagBufs&,           \
                                            const GuessTables*, hipStream_t);                                          \
-    template hipError_t launch_init<TS>(const InPtrs&, const Consts&, double*, const StateBuf&, hipStream_t);         \
-    template hipError_t launch_ghost<TS>(const FacePtrs&, const Consts&, const StateBuf&, hipStream_t);               \
+    template hipError_t launch_init<TS>(const InPtrs&, const Consts&, double*, char*, hipStream_t);         \
+    template hipError_t launch_ghost<TS>(const FacePtrs&, const Consts&, char*, hipStream_t);               \
     template hipError_t launch_batch<TS>(const BatchInst*, int, int, int64_t, int, int, int, hipStream_t);            \
     template hipError_t launch_batch_persistent<TS>(const BatchInst*, int, int, int, int, int, int, int*,            \
                                                     hipStream_t);                                                     \
-    template hipError_t launch_guess_samples<TS>(const StateBuf&, const Consts&, double*, int, double*, double*,      \
+    template hipError_t launch_guess_samples<TS>(const char*, const Consts&, double*, int, double*, double*,      \
                                                  double*, double*, hipStream_t);                                      \
-    template hipError_t launch_export<TS>(const StateBuf&, double*, const Consts&, hipStream_t);                      \
-    template hipError_t launch_import<TS>(const double*, const StateBuf&, const Consts&, hipStream_t);
+    template hipError_t launch_export<TS>(const char*, double*, const Consts&, hipStream_t);                      \
+    template hipError_t launch_import<TS>(const double*, char*, const Consts&, hipStream_t);
 
 RMHD_INSTANTIATE(double)
 RMHD_INSTANTIATE(float)
