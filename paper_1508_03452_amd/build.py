@@ -13,7 +13,9 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "librmhdlb.so")
-SOURCES = ["rmhdlb_api.hip", "rmhdlb_kernels.hip", "rmhdlb_mlp.hip"]
+# (source, object, extra flags): the kernels compile once per storage form, side by side
+UNITS = [("rmhdlb_api.hip", "rmhdlb_api.o", []), ("rmhdlb_mlp.hip", "rmhdlb_mlp.o", [])] + [
+    ("rmhdlb_kernels.hip", f"rmhdlb_kernels_f{form}.o", [f"-DRMHDLB_FORM={form}"]) for form in (64, 32, 16)]
 ARCH = os.environ.get("RMHDLB_ARCH", "gfx950")
 FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -29,9 +31,9 @@ def build(verbose=False):
     bdir = os.path.join(HERE, "_build")
     os.makedirs(bdir, exist_ok=True)
     procs = []
-    for src in SOURCES:  # translation units compile in parallel
-        obj = os.path.join(bdir, src.replace(".hip", ".o"))
-        cmd = [hipcc()] + FLAGS + ["-c", os.path.join(CSRC, src), "-o", obj]
+    for src, name, extra in UNITS:  # translation units compile in parallel
+        obj = os.path.join(bdir, name)
+        cmd = [hipcc()] + FLAGS + extra + ["-c", os.path.join(CSRC, src), "-o", obj]
         if verbose:
             print(" ".join(cmd), flush=True)
         procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.PIPE, text=True)))

@@ -943,6 +943,7 @@ struct rmhdlb_batch {
     rmhd::BatchInst* dev;
     int total_blocks;
     int64_t total_face;
+    bool flat;                 // every instance takes the kernels for a single z-plane
     int persistent;            // rmhdlb_batch_step: 1 = one cooperative launch per call
     int* next;                 // the persistent kernel's tile counters (after the instance table)
     hipGraphExec_t exec_long;  // GRAPH_LONG steps from parity 0, or null
@@ -993,13 +994,13 @@ int batch_table(rmhdlb_batch* B) {
 hipError_t batch_launch(rmhdlb_batch* B, int parity) {
     switch (B->storage) {
         case RMHDLB_STORE_F64:
-            return rmhd::launch_batch<double>(B->dev, B->n, B->total_blocks, B->total_face, B->px, B->waves, parity,
-                                              B->stream);
+            return rmhd::launch_batch<double>(B->dev, B->n, B->total_blocks, B->total_face, B->flat, B->px, B->waves,
+                                              parity, B->stream);
         case RMHDLB_STORE_F32:
-            return rmhd::launch_batch<float>(B->dev, B->n, B->total_blocks, B->total_face, B->px, B->waves, parity,
-                                             B->stream);
+            return rmhd::launch_batch<float>(B->dev, B->n, B->total_blocks, B->total_face, B->flat, B->px, B->waves,
+                                             parity, B->stream);
         default:
-            return rmhd::launch_batch<_Float16>(B->dev, B->n, B->total_blocks, B->total_face, B->px, B->waves,
+            return rmhd::launch_batch<_Float16>(B->dev, B->n, B->total_blocks, B->total_face, B->flat, B->px, B->waves,
                                                 parity, B->stream);
     }
 }
@@ -1007,13 +1008,13 @@ hipError_t batch_launch(rmhdlb_batch* B, int parity) {
 hipError_t batch_launch_persistent(rmhdlb_batch* B, int parity, int nsteps) {
     switch (B->storage) {
         case RMHDLB_STORE_F64:
-            return rmhd::launch_batch_persistent<double>(B->dev, B->n, B->total_blocks, B->px, B->waves,
+            return rmhd::launch_batch_persistent<double>(B->dev, B->n, B->total_blocks, B->flat, B->px, B->waves,
                                                          parity, nsteps, B->next, B->stream);
         case RMHDLB_STORE_F32:
-            return rmhd::launch_batch_persistent<float>(B->dev, B->n, B->total_blocks, B->px, B->waves,
+            return rmhd::launch_batch_persistent<float>(B->dev, B->n, B->total_blocks, B->flat, B->px, B->waves,
                                                         parity, nsteps, B->next, B->stream);
         default:
-            return rmhd::launch_batch_persistent<_Float16>(B->dev, B->n, B->total_blocks, B->px, B->waves,
+            return rmhd::launch_batch_persistent<_Float16>(B->dev, B->n, B->total_blocks, B->flat, B->px, B->waves,
                                                            parity, nsteps, B->next, B->stream);
     }
 }
@@ -1093,10 +1094,14 @@ int rmhdlb_batch_create(const rmhdlb_params* params, int32_t n, void* hip_stream
     B->exec_long = B->exec_pair = nullptr;
     B->total_blocks = 0;
     B->total_face = 0;
+    B->flat = true;
     B->ctx.assign(n, nullptr);
     B->host.resize(n);
     int rc = RMHDLB_OK;
-    for (int i = 0; i < n && rc == RMHDLB_OK; ++i) rc = rmhdlb_create(&params[i], hip_stream, &B->ctx[i]);
+    for (int i = 0; i < n && rc == RMHDLB_OK; ++i) {
+        rc = rmhdlb_create(&params[i], hip_stream, &B->ctx[i]);
+        if (rc == RMHDLB_OK) B->flat = B->flat && rmhd::flat_grid(B->ctx[i]->K);
+    }
     // the instance table, then the persistent kernel's 16 tile counters
     const size_t table = (sizeof(rmhd::BatchInst) * n + 255) / 256 * 256;
     if (rc == RMHDLB_OK && hipMalloc((void**)&B->dev, table + 16 * sizeof(int)) != hipSuccess) {

@@ -16,6 +16,10 @@
 #include "rmhdlb_internal.h"
 #include "rmhdlb_mlp.h"
 
+#ifndef RMHDLB_FORM
+#error "compile once per storage form with -DRMHDLB_FORM=64, 32 and 16"
+#endif
+
 namespace rmhd {
 
 constexpr int TX = 64, TY = 4, TPB = TX * TY;
@@ -157,7 +161,8 @@ struct Nbr {
 // STATE: offsets into the state arrays, which hold the ghost planes of a
 // driven face below z = 0; otherwise offsets into plain N-cell field arrays
 // (a driven face then acts as open).
-template <bool STATE>
+// FLAT: one z-plane and no driven face, where every z-displacement leads back to the cell.
+template <bool STATE, bool FLAT = false>
 __device__ __forceinline__ Nbr make_nbr(const Consts& K, int x, int y, int z) {
     Nbr n;
     const int sy = K.nx, sz = K.nx * K.ny;
@@ -165,7 +170,7 @@ __device__ __forceinline__ Nbr make_nbr(const Consts& K, int x, int y, int z) {
     for (int d = -2; d <= 2; ++d) {
         n.ox[d + 2] = map_coord(x + d, K.nx, K.per[0], 0) - x;
         n.oy[d + 2] = (map_coord(y + d, K.ny, K.per[1], 0) - y) * sy;
-        n.oz[d + 2] = (map_coord(z + d, K.nz, K.per[2], STATE ? K.drv : 0) - z) * sz;
+        n.oz[d + 2] = FLAT ? 0 : (map_coord(z + d, K.nz, K.per[2], STATE ? K.drv : 0) - z) * sz;
     }
     return n;
 }
@@ -595,13 +600,16 @@ constexpr int PTPB = 256;  // threads of a fused-step block: 128 cells, two lane
 // leaves a wave the 256 registers that the cell's populations and two records'
 // loads in flight take (three spilled: FP32 batch kernel 67 registers).
 constexpr int FUSED_WAVES = 2;
-// Link of a slot as the step walks it (direction 2s - 1).
-template <int S>
+// Link of a slot as the step walks it (direction 2s - 1).  FLAT: the grid has
+// one z-plane whose z-neighbours are the cell itself, so links and the
+// Laplacian lie in the plane.
+template <int S, bool FLAT>
 struct Link {
-    static constexpr int x = EX[2 * S - 1], y = EY[2 * S - 1], z = EZ[2 * S - 1];
+    static constexpr int x = EX[2 * S - 1], y = EY[2 * S - 1], z = FLAT ? 0 : EZ[2 * S - 1];
     static constexpr int axes = (x != 0) + (y != 0) + (z != 0);
     // an axis link's points x -+ e are also the Laplacian's neighbours along that axis
-    static constexpr bool lap_x = !(axes == 1 && x != 0), lap_y = !(axes == 1 && y != 0), lap_z = !(axes == 1 && z != 0);
+    static constexpr bool lap_x = !(axes == 1 && x != 0), lap_y = !(axes == 1 && y != 0),
+                          lap_z = !FLAT && !(axes == 1 && z != 0);
 };
 
 // Keeps a value in a register from here on.  As the statement is volatile and
@@ -634,7 +642,7 @@ __device__ __forceinline__ V pair_sum(V v) {
 // R4); bit 1 the limited Lax-Wendroff face values (else MUSCL, Reading R2);
 // bit 2 the external force; bit 3 the previous step's B in the recovery and
 // f_eq (else this step's, Reading R10), carried in the state.
-template <bool NT, typename TS, typename TE, typename V, int GM, int VR = 0>
+template <bool NT, typename TS, typename TE, typename V, int GM, int VR, bool FLAT>
 __device__ __forceinline__ void pair_cell(const char* __restrict__ sd, char* __restrict__ dd,
                                           const double* __restrict__ faceB, const GuessTables* __restrict__ gt,
                                           const Consts& K, int cell, const Nbr& nb, int h, int x, int y, int z,
@@ -672,24 +680,31 @@ __device__ __forceinline__ void pair_cell(const char* __restrict__ sd, char* __r
         TS xp, xm, yp, ym, zp, zm;
     };
     auto issue = [&](auto ic, Raw& r) {
-        using K_ = Link<decltype(ic)::value>;
+        using K_ = Link<decltype(ic)::value, FLAT>;
         const char* __restrict__ fga = sd + CHUNK * 16 * (2 * decltype(ic)::value - 1);  // uniform base of the pairs
         auto pr = [&](int64_t o) { return *reinterpret_cast<const vec2<TS>*>(fga + o); };
         auto f = [&](int64_t o) { return *reinterpret_cast<const TS*>(fga + o); };
         r.c0 = pr(cc);
-        r.m2 = pr(rec(h ? nb.at(2 * K_::x, 2 * K_::y, 2 * K_::z) : nb.at(-2 * K_::x, -2 * K_::y, -2 * K_::z)));
-        r.m1 = pr(rec(h ? nb.at(K_::x, K_::y, K_::z) : nb.at(-K_::x, -K_::y, -K_::z)));
-        r.p1 = pr(rec(h ? nb.at(-K_::x, -K_::y, -K_::z) : nb.at(K_::x, K_::y, K_::z)));
+        if constexpr (K_::axes > 0) {
+            r.m2 = pr(rec(h ? nb.at(2 * K_::x, 2 * K_::y, 2 * K_::z) : nb.at(-2 * K_::x, -2 * K_::y, -2 * K_::z)));
+            r.m1 = pr(rec(h ? nb.at(K_::x, K_::y, K_::z) : nb.at(-K_::x, -K_::y, -K_::z)));
+            r.p1 = pr(rec(h ? nb.at(-K_::x, -K_::y, -K_::z) : nb.at(K_::x, K_::y, K_::z)));
+        }
         if constexpr (K_::lap_x) r.xp = f(lap_xp), r.xm = f(lap_xm);
         if constexpr (K_::lap_y) r.yp = f(lap_yp), r.ym = f(lap_ym);
         if constexpr (K_::lap_z) r.zp = f(lap_zp), r.zm = f(lap_zm);
     };
     auto arrive = [&](auto ic, Raw& r) {
-        using K_ = Link<decltype(ic)::value>;
-        pin(r.c0), pin(r.m2), pin(r.m1), pin(r.p1);
+        using K_ = Link<decltype(ic)::value, FLAT>;
+        pin(r.c0);
+        if constexpr (K_::axes > 0)
+            pin(r.m2), pin(r.m1), pin(r.p1);
+        else
+            r.m2 = r.m1 = r.p1 = r.c0;
         if constexpr (K_::lap_x) pin(r.xp), pin(r.xm);
         if constexpr (K_::lap_y) pin(r.yp), pin(r.ym);
         if constexpr (K_::lap_z) pin(r.zp), pin(r.zm);
+        if constexpr (FLAT) r.zp = r.zm = r.c0.x;
     };
     TS hraw[12];
     auto issue_h = [&]() {
@@ -707,7 +722,7 @@ __device__ __forceinline__ void pair_cell(const char* __restrict__ sd, char* __r
         if constexpr (s <= 9) {
             constexpr int i0 = 2 * s - 1;
             constexpr int ex = EX[i0], ey = EY[i0], ez = EZ[i0];
-            using K_ = Link<s>;
+            using K_ = Link<s, FLAT>;
             // the next slot's loads (after the last slot, the Maxwell populations') are in flight while this
             // slot's arrive and are used
             if constexpr (s < 9)
@@ -720,7 +735,7 @@ __device__ __forceinline__ void pair_cell(const char* __restrict__ sd, char* __r
             const V up = h ? fm1 : fp1, dn = h ? fp1 : fm1;  // f at x + e_i0 and x - e_i0 (lane 1 walks -e)
             const V lxp = K_::lap_x ? r.xp : up, lxm = K_::lap_x ? r.xm : dn;
             const V lyp = K_::lap_y ? r.yp : up, lym = K_::lap_y ? r.ym : dn;
-            const V lzp = K_::lap_z ? r.zp : up, lzm = K_::lap_z ? r.zm : dn;
+            const V lzp = K_::lap_z || FLAT ? r.zp : up, lzm = K_::lap_z || FLAT ? r.zm : dn;
             const V lap = (lxp + lxm) + (lyp + lym) + (lzp + lzm) - V(6) * f0;
             const V fv = f0 - cour * ((f0 + slope * minmod(f0 - fm1, fp1 - f0)) -
                                       (fm1 + slope * minmod(fm1 - fm2, f0 - fm1))) + kv * lap;
@@ -927,7 +942,7 @@ __device__ __forceinline__ void st8(char* __restrict__ d, int64_t o, const vec4<
 // of the cell they stream from.  The arithmetic per direction is that of
 // pair_cell (the readings it implements are listed there); only the
 // assignment of work to lanes and the order of the moment sums differ.
-template <bool NT, typename TS, typename TE, typename V, int GM, int VR = 0>
+template <bool NT, typename TS, typename TE, typename V, int GM, int VR, bool FLAT>
 __device__ __forceinline__ void quad_cell(const char* __restrict__ sd, char* __restrict__ dd,
                                           const double* __restrict__ faceB, const GuessTables* __restrict__ gt,
                                           const Consts& K, int cell, const Nbr& nb, int x, int y, int z, bool active,
@@ -992,17 +1007,20 @@ __device__ __forceinline__ void quad_cell(const char* __restrict__ sd, char* __r
     auto rec16 = [&](const char* __restrict__ base, int64_t o) { return *reinterpret_cast<const Rec*>(base + o); };
     auto half8 = [&](const char* __restrict__ base, int64_t o) { return *reinterpret_cast<const Half*>(base + o); };
     auto issue_links = [&](auto sc, const char* __restrict__ base, Half (&q)[4]) {
-        using K_ = Link<decltype(sc)::value>;
-        q[0] = half8(base, rec(nb.at(-2 * K_::x, -2 * K_::y, -2 * K_::z)));
-        q[1] = half8(base, rec(nb.at(2 * K_::x, 2 * K_::y, 2 * K_::z)));
+        using K_ = Link<decltype(sc)::value, FLAT>;
+        if constexpr (K_::axes > 0) {
+            q[0] = half8(base, rec(nb.at(-2 * K_::x, -2 * K_::y, -2 * K_::z)));
+            q[1] = half8(base, rec(nb.at(2 * K_::x, 2 * K_::y, 2 * K_::z)));
+        }
         if constexpr (K_::axes > 1) {
             q[2] = half8(base, rec(nb.at(-K_::x, -K_::y, -K_::z)));
             q[3] = half8(base, rec(nb.at(K_::x, K_::y, K_::z)));
         }
     };
     auto pin_links = [&](auto sc, Half (&q)[4]) {
-        pin(q[0]), pin(q[1]);
-        if constexpr (Link<decltype(sc)::value>::axes > 1) pin(q[2]), pin(q[3]);
+        using K_ = Link<decltype(sc)::value, FLAT>;
+        if constexpr (K_::axes > 0) pin(q[0]), pin(q[1]);
+        if constexpr (K_::axes > 1) pin(q[2]), pin(q[3]);
     };
     // record r: slots sa and (FP16) sb, 0 when the second quad is the rest one
     auto slot_a = [](auto rc) { return std::integral_constant<int, DQ ? 2 * decltype(rc)::value + 1 : decltype(rc)::value + 1>{}; };
@@ -1010,21 +1028,20 @@ __device__ __forceinline__ void quad_cell(const char* __restrict__ sd, char* __r
     auto issue = [&](auto rc, Raw& q) {
         constexpr auto sa = slot_a(rc);
         constexpr auto sb = slot_b(rc);
-        using A = Link<sa.value>;
         const char* __restrict__ base = sd + CHUNK * 16 * (DQ ? decltype(rc)::value : sa.value);
         q.c = rec16(base, cc);
         // an FP32 axis slot's points x -+ e also serve its Laplacian; an FP16 record's serve both slots
         q.xp = rec16(base, lap_xp), q.xm = rec16(base, lap_xm);
         q.yp = rec16(base, lap_yp), q.ym = rec16(base, lap_ym);
-        q.zp = rec16(base, lap_zp), q.zm = rec16(base, lap_zm);
+        if constexpr (!FLAT) q.zp = rec16(base, lap_zp), q.zm = rec16(base, lap_zm);
         issue_links(sa, base, q.a);
         if constexpr (sb.value != 0) issue_links(sb, base + 8, q.b);
-        (void)sizeof(A);
     };
     auto arrive = [&](auto rc, Raw& q) {
         constexpr auto sa = slot_a(rc);
         constexpr auto sb = slot_b(rc);
-        pin(q.c), pin(q.xp), pin(q.xm), pin(q.yp), pin(q.ym), pin(q.zp), pin(q.zm);
+        pin(q.c), pin(q.xp), pin(q.xm), pin(q.yp), pin(q.ym);
+        if constexpr (!FLAT) pin(q.zp), pin(q.zm);
         pin_links(sa, q.a);
         if constexpr (sb.value != 0) pin_links(sb, q.b);
     };
@@ -1043,17 +1060,20 @@ __device__ __forceinline__ void quad_cell(const char* __restrict__ sd, char* __r
     };
     auto use = [&](auto sc, const Raw& q, int half, const Half (&lk)[4]) {
         constexpr int s = decltype(sc)::value;
-        using K_ = Link<s>;
+        using K_ = Link<s, FLAT>;
         const vec4<V> c = quad_of(q.c, half), xp = quad_of(q.xp, half), xm = quad_of(q.xm, half),
-                      yp = quad_of(q.yp, half), ym = quad_of(q.ym, half), zp = quad_of(q.zp, half),
-                      zm = quad_of(q.zm, half), m2 = quad_of(lk[0], 0), p2 = quad_of(lk[1], 0);
+                      yp = quad_of(q.yp, half), ym = quad_of(q.ym, half), zp = FLAT ? c : quad_of(q.zp, half),
+                      zm = FLAT ? c : quad_of(q.zm, half);
+        const vec4<V> m2 = K_::axes > 0 ? quad_of(lk[0], 0) : c, p2 = K_::axes > 0 ? quad_of(lk[1], 0) : c;
         vec4<V> m1, p1;
-        if constexpr (K_::axes > 1)
+        if constexpr (K_::axes == 0)
+            m1 = p1 = c;
+        else if constexpr (K_::axes > 1)
             m1 = quad_of(lk[2], 0), p1 = quad_of(lk[3], 0);
         else if constexpr (K_::x != 0)
-            m1 = xm, p1 = xp;
+            m1 = K_::x > 0 ? xm : xp, p1 = K_::x > 0 ? xp : xm;
         else if constexpr (K_::y != 0)
-            m1 = ym, p1 = yp;
+            m1 = K_::y > 0 ? ym : yp, p1 = K_::y > 0 ? yp : ym;
         else
             m1 = zm, p1 = zp;
         transport(sc, c, m2, m1, p1, p2, xp, xm, yp, ym, zp, zm);
@@ -1303,7 +1323,7 @@ __device__ __forceinline__ void quad_cell(const char* __restrict__ sd, char* __r
 // the same planes, so the y-halo meets in that XCD's L2 as well.
 // With the learned guess the network runs on whole wavefronts, so lanes past
 // a ragged edge stay and compute a copy of the edge cell without storing it.
-template <bool NT, typename TS, typename TE, typename V, int GM, int PXT, int VR = 0>
+template <bool NT, typename TS, typename TE, typename V, int GM, int PXT, int VR, bool FLAT>
 __device__ __forceinline__ void fused_block(const char* __restrict__ sd, char* __restrict__ dd,
                                             const double* __restrict__ faceB, const GuessTables* __restrict__ gt,
                                             const Consts& K, int tiles_x, int ncol, int zb, int zg, int yw, int b) {
@@ -1352,12 +1372,12 @@ __device__ __forceinline__ void fused_block(const char* __restrict__ sd, char* _
             int xp = x, yp = all_lanes ? min(yj, K.ny - 1) : yj, hp = h;
             if constexpr (opaque) asm volatile("" : "+v"(xp), "+v"(yp), "+v"(hp));
             const int cell = xp + K.nx * (yp + K.ny * z);
-            const Nbr nb = make_nbr<true>(K, xp, yp, z);
+            const Nbr nb = make_nbr<true, FLAT>(K, xp, yp, z);
             if constexpr (ONE)
-                quad_cell<NT, TS, TE, V, GM, VR>(sd, dd, faceB, gt, K, cell, nb, xp, yp, z,
+                quad_cell<NT, TS, TE, V, GM, VR, FLAT>(sd, dd, faceB, gt, K, cell, nb, xp, yp, z,
                                                  all_lanes ? active : true, bmax, gate);
             else
-                pair_cell<NT, TS, TE, V, GM, VR>(sd, dd, faceB, gt, K, cell, nb, hp, xp, yp, z,
+                pair_cell<NT, TS, TE, V, GM, VR, FLAT>(sd, dd, faceB, gt, K, cell, nb, hp, xp, yp, z,
                                                  all_lanes ? active : true, bmax, gate);
         }
     }
@@ -1369,7 +1389,7 @@ __device__ __forceinline__ void fused_block(const char* __restrict__ sd, char* _
     }
 }
 
-template <bool NT, typename TS, typename TE, typename V, int GM, int PXT, int VR>
+template <bool NT, typename TS, typename TE, typename V, int GM, int PXT, int VR, bool FLAT>
 __global__ __launch_bounds__(PTPB, FUSED_WAVES) void k_fused_step(const char* __restrict__ sd,
                                                         char* __restrict__ dd, const double* __restrict__ faceB,
                                                         const GuessTables* __restrict__ gt, Consts K,
@@ -1385,7 +1405,7 @@ __global__ __launch_bounds__(PTPB, FUSED_WAVES) void k_fused_step(const char* __
         if (*K.gflag_rd != K.gstep - 1) return;
         if (blockIdx.x == 0 && threadIdx.x == 0 && K.gcount) *K.gcount += 1;  // one writer per step
     }
-    fused_block<NT, TS, TE, V, GM, PXT, VR>(sd, dd, faceB, gt, K, tiles_x, ncol, zb, zg, yw, b);
+    fused_block<NT, TS, TE, V, GM, PXT, VR, FLAT>(sd, dd, faceB, gt, K, tiles_x, ncol, zb, zg, yw, b);
 }
 
 // Index of the instance whose range [first[i], first[i + 1]) holds v (first
@@ -1409,14 +1429,14 @@ __device__ __forceinline__ int find_instance(int ninst, int64_t v, Get first) {
 // an XCD.  parity selects which of each instance's buffers is read.  WV:
 // waves per SIMD the kernel is compiled for (the occupancy the batch tuner
 // sweeps).
-template <bool NT, typename TS, typename TE, typename V, int PXT, int WV>
+template <bool NT, typename TS, typename TE, typename V, int PXT, int WV, bool FLAT>
 __global__ __launch_bounds__(PTPB, WV) void k_fused_batch(const BatchInst* __restrict__ I, int ninst, int total,
                                                           int parity) {
     const int b = tile_of_block(total);
     if (b >= total) return;
     const int i = find_instance(ninst, b, [&](int j) { return I[j].blk0; });
     const BatchInst& B = I[i];
-    fused_block<NT, TS, TE, V, GUESS_NONE, PXT>(
+    fused_block<NT, TS, TE, V, GUESS_NONE, PXT, 0, FLAT>(
         B.buf[parity], B.buf[1 - parity], B.faceB, nullptr, B.K, B.tiles_x, B.ncol, B.zb, 1, B.yw, (int)(b - B.blk0));
 }
 
@@ -1508,7 +1528,7 @@ __global__ __launch_bounds__(256) void k_face_b_batch(const BatchInst* __restric
 // the open-face adjustment are stepped by graph replays.  Every block reaches
 // every barrier: no thread leaves the kernel early, and a fetch loop ends
 // once its counter passes P.
-template <bool NT, typename TS, typename TE, typename V, int PXT, int WV>
+template <bool NT, typename TS, typename TE, typename V, int PXT, int WV, bool FLAT>
 __global__ __launch_bounds__(PTPB, WV) void k_fused_batch_persistent(const BatchInst* __restrict__ I, int ninst,
                                                                      int total, int parity0, int nsteps,
                                                                      int* __restrict__ next) {
@@ -1532,7 +1552,7 @@ __global__ __launch_bounds__(PTPB, WV) void k_fused_batch_persistent(const Batch
             if (b < total) {
                 const int i = find_instance(ninst, b, [&](int jj) { return I[jj].blk0; });
                 const BatchInst& B = I[i];
-                fused_block<NT, TS, TE, V, GUESS_NONE, PXT>(
+                fused_block<NT, TS, TE, V, GUESS_NONE, PXT, 0, FLAT>(
                     B.buf[parity], B.buf[1 - parity], B.faceB, nullptr, B.K, B.tiles_x, B.ncol, B.zb, 1, B.yw,
                     (int)(b - B.blk0));
             }
@@ -1649,7 +1669,7 @@ __global__ __launch_bounds__(TPB) void k_moments(const char* __restrict__ src, c
 
 // max |div B| per block from the B written by k_moments (the derivative
 // operator of the normal-B adjustment).
-__global__ __launch_bounds__(TPB) void k_divb(const double* __restrict__ Bs, Consts K, int tiles_x, int tiles_y,
+[[maybe_unused]] static __global__ __launch_bounds__(TPB) void k_divb(const double* __restrict__ Bs, Consts K, int tiles_x, int tiles_y,
                                               int ntiles, double* __restrict__ part) {
     const int tile = tile_of_block(ntiles);
     if (tile >= ntiles) return;
@@ -1671,7 +1691,7 @@ __global__ __launch_bounds__(TPB) void k_divb(const double* __restrict__ Bs, Con
 
 // Null point over the per-block partials, then R = (E^z - E^z_0) / B0 there.
 // out[0] = R, out[1] = null cell (-1: none), out[2] = B0.
-__global__ __launch_bounds__(TPB) void k_null_reduce(const double* __restrict__ nullp, int nblk,
+[[maybe_unused]] static __global__ __launch_bounds__(TPB) void k_null_reduce(const double* __restrict__ nullp, int nblk,
                                                      const double* __restrict__ ez, const double* __restrict__ ez0,
                                                      const double* __restrict__ b0, double* __restrict__ out) {
     __shared__ double res[2];
@@ -1691,7 +1711,7 @@ __global__ __launch_bounds__(TPB) void k_null_reduce(const double* __restrict__ 
 // Fixed-order reduction of the per-block partials by one block.
 // Largest |beta| of a forced step from its per-wavefront partials (which are
 // cleared for the next step); one block.
-__global__ __launch_bounds__(TPB) void k_vmax_reduce(double* __restrict__ part, int64_t n, double* __restrict__ out) {
+[[maybe_unused]] static __global__ __launch_bounds__(TPB) void k_vmax_reduce(double* __restrict__ part, int64_t n, double* __restrict__ out) {
     double m = 0.0;
     for (int64_t i = threadIdx.x; i < n; i += TPB) {
         m = fmax(m, part[i]);
@@ -1709,7 +1729,7 @@ __global__ __launch_bounds__(TPB) void k_vmax_reduce(double* __restrict__ part, 
     }
 }
 
-__global__ __launch_bounds__(TPB) void k_reduce(const double* __restrict__ part, int nblk, int width, int is_max,
+[[maybe_unused]] static __global__ __launch_bounds__(TPB) void k_reduce(const double* __restrict__ part, int nblk, int width, int is_max,
                                                 double* __restrict__ out) {
     for (int j = 0; j < width; ++j) {
         double acc = 0.0;
@@ -1725,7 +1745,7 @@ __global__ __launch_bounds__(TPB) void k_reduce(const double* __restrict__ part,
 
 // Sums of eps = n c^2 + p / (Gamma - 1) and n over the initial fields (the
 // references of the stored deviations).
-__global__ __launch_bounds__(TPB) void k_init_ref(InPtrs in, Consts K, double* __restrict__ part) {
+[[maybe_unused]] static __global__ __launch_bounds__(TPB) void k_init_ref(InPtrs in, Consts K, double* __restrict__ part) {
     const int64_t i = (int64_t)blockIdx.x * TPB + threadIdx.x;
     double v[2] = {0.0, 0.0};
     if (i < K.N) {
@@ -1736,19 +1756,19 @@ __global__ __launch_bounds__(TPB) void k_init_ref(InPtrs in, Consts K, double* _
 }
 
 // Largest B^2 of the initial fields (as fma(B_x, B_x, fma(B_y, B_y, B_z B_z))), per block.
-__global__ __launch_bounds__(TPB) void k_init_bmax(InPtrs in, Consts K, double* __restrict__ part) {
+[[maybe_unused]] static __global__ __launch_bounds__(TPB) void k_init_bmax(InPtrs in, Consts K, double* __restrict__ part) {
     const int64_t i = (int64_t)blockIdx.x * TPB + threadIdx.x;
     double v = 0.0;
     if (i < K.N) v = fma(in.B[0][i], in.B[0][i], fma(in.B[1][i], in.B[1][i], in.B[2][i] * in.B[2][i]));
     block_max1(v, part + blockIdx.x);
 }
 
-__global__ void k_sqrt1(double* __restrict__ v) {
+[[maybe_unused]] static __global__ void k_sqrt1(double* __restrict__ v) {
     if (threadIdx.x == 0) v[0] = sqrt(v[0]);
 }
 
 // Face cells with |u| >= c, n <= 0 or p < 0, per block.
-__global__ __launch_bounds__(TPB) void k_face_check(FacePtrs in, Consts K, double* __restrict__ part) {
+[[maybe_unused]] static __global__ __launch_bounds__(TPB) void k_face_check(FacePtrs in, Consts K, double* __restrict__ part) {
     const int64_t i = (int64_t)blockIdx.x * TPB + threadIdx.x;
     double bad[1] = {0.0};
     if (i < (int64_t)K.nx * K.ny) {
@@ -1820,7 +1840,7 @@ __global__ __launch_bounds__(TPB) void k_init_ghost(FacePtrs in, Consts K, char*
 
 // Initial state, pass 1: J0 from Eq. Ohm with the Gauss charge of E0, and
 // E'0 = E0 + (dt/2) mu0 c^2 J0 (Reading of the initial h), into scratch.
-__global__ __launch_bounds__(TPB) void k_init_current(InPtrs in, Consts K, int tiles_x, int tiles_y, int ntiles,
+[[maybe_unused]] static __global__ __launch_bounds__(TPB) void k_init_current(InPtrs in, Consts K, int tiles_x, int tiles_y, int ntiles,
                                                       double* __restrict__ scr) {
     const int tile = tile_of_block(ntiles);
     if (tile >= ntiles) return;
@@ -1994,7 +2014,7 @@ __global__ __launch_bounds__(256) void k_guess_samples(const char* __restrict__ 
 // Plain copy of n 16-byte words, four per lane in flight, with the non-temporal
 // hints of the step's streamed loads and stores (the reference rate of HBM).
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-__global__ __launch_bounds__(256) void k_copy16(const u32x4* __restrict__ src, u32x4* __restrict__ dst, int64_t n) {
+[[maybe_unused]] static __global__ __launch_bounds__(256) void k_copy16(const u32x4* __restrict__ src, u32x4* __restrict__ dst, int64_t n) {
     const int64_t base = (int64_t)blockIdx.x * (256 * 4) + threadIdx.x;
     u32x4 v[4];
 #pragma unroll
@@ -2011,12 +2031,14 @@ __global__ __launch_bounds__(256) void k_copy16(const u32x4* __restrict__ src, u
 
 // ------------------------------------------------------------ host launchers
 
+#if RMHDLB_FORM == 64  // what depends on no storage form is built once
 hipError_t launch_copy16(const void* src, void* dst, int64_t n16, hipStream_t s) {
     const int64_t blocks = (n16 + 1023) / 1024;
     if (blocks > 0)
         hipLaunchKernelGGL(k_copy16, dim3((unsigned)blocks), dim3(256), 0, s, (const u32x4*)src, (u32x4*)dst, n16);
     return hipGetLastError();
 }
+#endif
 
 static inline void grid_of(const Consts& K, int& tiles_x, int& tiles_y, int& ntiles, int& nblocks) {
     tiles_x = (K.nx + TX - 1) / TX;
@@ -2025,11 +2047,13 @@ static inline void grid_of(const Consts& K, int& tiles_x, int& tiles_y, int& nti
     nblocks = ((ntiles + 7) / 8) * 8;
 }
 
+#if RMHDLB_FORM == 64  // what depends on no storage form is built once
 int num_tiles(const Consts& K) {
     int a, b, n, nb;
     grid_of(K, a, b, n, nb);
     return n;
 }
+#endif
 
 template <typename TS>
 hipError_t launch_face_b(const char* src, const Consts& K, double* faceB, hipStream_t s) {
@@ -2039,12 +2063,14 @@ hipError_t launch_face_b(const char* src, const Consts& K, double* faceB, hipStr
     return hipGetLastError();
 }
 
+#if RMHDLB_FORM == 64  // what depends on no storage form is built once
 void step_geometry(const Consts& K, int px, int zb, int zg, int yw, int cpb, int& tiles_x, int& ncol, int& nblk) {
     const int py = cpb / px * yw;
     tiles_x = (K.nx + px - 1) / px;
     ncol = tiles_x * ((K.ny + py - 1) / py);
     nblk = ncol * zg * ((K.nz + zg * zb - 1) / (zg * zb));
 }
+#endif
 
 template <typename TS, int GM, int PXT, int VR = 0>
 static void launch_fused(const char* sd, char* dd, double* faceB, const GuessTables* gt, const Consts& K, int zb, int zg, int yw, hipStream_t s) {
@@ -2053,8 +2079,12 @@ static void launch_fused(const char* sd, char* dd, double* faceB, const GuessTab
     int tx, ncol, nblk;
     step_geometry(K, PXT, zb, zg, yw, cells_per_block(quad_layout<TS>()), tx, ncol, nblk);
     const int grid = ((nblk + 7) / 8) * 8;
-    hipLaunchKernelGGL((k_fused_step<true, TS, TE, V, GM, PXT, VR>), dim3(grid), dim3(PTPB), 0, s, sd, dd,
-                       (const double*)faceB, gt, K, tx, ncol, zb, zg, yw, nblk);
+    if (flat_grid(K))
+        hipLaunchKernelGGL((k_fused_step<true, TS, TE, V, GM, PXT, VR, true>), dim3(grid), dim3(PTPB), 0, s, sd, dd,
+                           (const double*)faceB, gt, K, tx, ncol, zb, zg, yw, nblk);
+    else
+        hipLaunchKernelGGL((k_fused_step<true, TS, TE, V, GM, PXT, VR, false>), dim3(grid), dim3(PTPB), 0, s, sd, dd,
+                           (const double*)faceB, gt, K, tx, ncol, zb, zg, yw, nblk);
 }
 
 template <typename TS>
@@ -2106,29 +2136,35 @@ hipError_t launch_step(const char* src, char* dst, const Consts& K, const StepTu
 }
 
 template <typename TS, int PXT, int WV>
-static void launch_batch_fused(const BatchInst* dev, int ninst, int total_blocks, int parity, hipStream_t s) {
+static void launch_batch_fused(const BatchInst* dev, int ninst, int total_blocks, bool flat, int parity,
+                               hipStream_t s) {
     using TE = typename StoreTypes<TS>::E;
     using V = typename StoreTypes<TS>::V;
     const int grid = ((total_blocks + 7) / 8) * 8;
-    hipLaunchKernelGGL((k_fused_batch<true, TS, TE, V, PXT, WV>), dim3(grid), dim3(PTPB), 0, s, dev, ninst,
-                       total_blocks, parity);
+    if (flat)
+        hipLaunchKernelGGL((k_fused_batch<true, TS, TE, V, PXT, WV, true>), dim3(grid), dim3(PTPB), 0, s, dev, ninst,
+                           total_blocks, parity);
+    else
+        hipLaunchKernelGGL((k_fused_batch<true, TS, TE, V, PXT, WV, false>), dim3(grid), dim3(PTPB), 0, s, dev, ninst,
+                           total_blocks, parity);
 }
 
 template <typename TS, int WV>
-static void launch_batch_px(const BatchInst* dev, int ninst, int total_blocks, int px, int parity, hipStream_t s) {
+static void launch_batch_px(const BatchInst* dev, int ninst, int total_blocks, bool flat, int px, int parity,
+                            hipStream_t s) {
     if (px == 128)
-        launch_batch_fused<TS, 128, WV>(dev, ninst, total_blocks, parity, s);
+        launch_batch_fused<TS, 128, WV>(dev, ninst, total_blocks, flat, parity, s);
     else if (px == 32)
-        launch_batch_fused<TS, 32, WV>(dev, ninst, total_blocks, parity, s);
+        launch_batch_fused<TS, 32, WV>(dev, ninst, total_blocks, flat, parity, s);
     else if (px == 16)
-        launch_batch_fused<TS, 16, WV>(dev, ninst, total_blocks, parity, s);
+        launch_batch_fused<TS, 16, WV>(dev, ninst, total_blocks, flat, parity, s);
     else
-        launch_batch_fused<TS, 64, WV>(dev, ninst, total_blocks, parity, s);
+        launch_batch_fused<TS, 64, WV>(dev, ninst, total_blocks, flat, parity, s);
 }
 
 template <typename TS>
-hipError_t launch_batch(const BatchInst* dev, int ninst, int total_blocks, int64_t total_face, int px, int waves,
-                        int parity, hipStream_t s) {
+hipError_t launch_batch(const BatchInst* dev, int ninst, int total_blocks, int64_t total_face, bool flat, int px,
+                        int waves, int parity, hipStream_t s) {
     if (total_face > 0)
         hipLaunchKernelGGL((k_face_b_batch<TS>), dim3((unsigned)((total_face + 255) / 256)), dim3(256), 0, s, dev,
                            ninst, total_face, parity);
@@ -2136,18 +2172,18 @@ hipError_t launch_batch(const BatchInst* dev, int ninst, int total_blocks, int64
     // FP64 and FP16 for their single-instance counts
     if constexpr (sizeof(TS) == 4) {
         if (waves == 3)
-            launch_batch_px<TS, 3>(dev, ninst, total_blocks, px, parity, s);
+            launch_batch_px<TS, 3>(dev, ninst, total_blocks, flat, px, parity, s);
         else
-            launch_batch_px<TS, 2>(dev, ninst, total_blocks, px, parity, s);
+            launch_batch_px<TS, 2>(dev, ninst, total_blocks, flat, px, parity, s);
     } else {
-        launch_batch_px<TS, FUSED_WAVES>(dev, ninst, total_blocks, px, parity, s);
+        launch_batch_px<TS, FUSED_WAVES>(dev, ninst, total_blocks, flat, px, parity, s);
     }
     return hipGetLastError();
 }
 
 // Clears the persistent run's 16 tile counters (a kernel, not a memset node,
 // should a caller capture the step).
-__global__ void k_zero16(int* __restrict__ p) {
+[[maybe_unused]] static __global__ void k_zero16(int* __restrict__ p) {
     if (threadIdx.x < 16) p[threadIdx.x] = 0;
 }
 
@@ -2156,11 +2192,12 @@ __global__ void k_zero16(int* __restrict__ p) {
 // at most the rounded tile range.  The cooperative launch refuses a grid that
 // cannot be resident as a whole, so the grid barriers always complete.
 template <typename TS, int PXT, int WV>
-static hipError_t launch_persistent_fused(const BatchInst* dev, int ninst, int total_blocks, int parity,
+static hipError_t launch_persistent_fused(const BatchInst* dev, int ninst, int total_blocks, bool flat, int parity,
                                           int nsteps, int* next, hipStream_t s) {
     using TE = typename StoreTypes<TS>::E;
     using V = typename StoreTypes<TS>::V;
-    const void* kern = reinterpret_cast<const void*>(&k_fused_batch_persistent<true, TS, TE, V, PXT, WV>);
+    const void* kern = flat ? reinterpret_cast<const void*>(&k_fused_batch_persistent<true, TS, TE, V, PXT, WV, true>)
+                            : reinterpret_cast<const void*>(&k_fused_batch_persistent<true, TS, TE, V, PXT, WV, false>);
     int dev_id = 0, cus = 0, per_cu = 0;
     hipError_t e = hipGetDevice(&dev_id);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev_id);
@@ -2177,27 +2214,26 @@ static hipError_t launch_persistent_fused(const BatchInst* dev, int ninst, int t
 }
 
 template <typename TS, int WV>
-static hipError_t launch_persistent_px(const BatchInst* dev, int ninst, int total_blocks, int px, int parity,
-                                       int nsteps, int* next, hipStream_t s) {
+static hipError_t launch_persistent_px(const BatchInst* dev, int ninst, int total_blocks, bool flat, int px,
+                                       int parity, int nsteps, int* next, hipStream_t s) {
     if (px == 128)
-        return launch_persistent_fused<TS, 128, WV>(dev, ninst, total_blocks, parity, nsteps, next, s);
+        return launch_persistent_fused<TS, 128, WV>(dev, ninst, total_blocks, flat, parity, nsteps, next, s);
     if (px == 32)
-        return launch_persistent_fused<TS, 32, WV>(dev, ninst, total_blocks, parity, nsteps, next, s);
+        return launch_persistent_fused<TS, 32, WV>(dev, ninst, total_blocks, flat, parity, nsteps, next, s);
     if (px == 16)
-        return launch_persistent_fused<TS, 16, WV>(dev, ninst, total_blocks, parity, nsteps, next, s);
-    return launch_persistent_fused<TS, 64, WV>(dev, ninst, total_blocks, parity, nsteps, next, s);
+        return launch_persistent_fused<TS, 16, WV>(dev, ninst, total_blocks, flat, parity, nsteps, next, s);
+    return launch_persistent_fused<TS, 64, WV>(dev, ninst, total_blocks, flat, parity, nsteps, next, s);
 }
 
 template <typename TS>
-hipError_t launch_batch_persistent(const BatchInst* dev, int ninst, int total_blocks, int px, int waves, int parity,
-                                   int nsteps, int* next, hipStream_t s) {
+hipError_t launch_batch_persistent(const BatchInst* dev, int ninst, int total_blocks, bool flat, int px, int waves,
+                                   int parity, int nsteps, int* next, hipStream_t s) {
     if constexpr (sizeof(TS) == 4) {
         if (waves == 3)
-            return launch_persistent_px<TS, 3>(dev, ninst, total_blocks, px, parity, nsteps, next, s);
-        return launch_persistent_px<TS, 2>(dev, ninst, total_blocks, px, parity, nsteps, next, s);
+            return launch_persistent_px<TS, 3>(dev, ninst, total_blocks, flat, px, parity, nsteps, next, s);
+        return launch_persistent_px<TS, 2>(dev, ninst, total_blocks, flat, px, parity, nsteps, next, s);
     } else {
-        return launch_persistent_px<TS, FUSED_WAVES>(dev, ninst, total_blocks, px, parity, nsteps, next,
-                                                               s);
+        return launch_persistent_px<TS, FUSED_WAVES>(dev, ninst, total_blocks, flat, px, parity, nsteps, next, s);
     }
 }
 
@@ -2226,6 +2262,7 @@ hipError_t launch_moments(const char* src, const Consts& K, const OutPtrs& out, 
     return hipGetLastError();
 }
 
+#if RMHDLB_FORM == 64  // what depends on no storage form is built once
 hipError_t launch_init_bmax(const InPtrs& in, const Consts& K, double* part, double* b0, hipStream_t s) {
     const int nblk = (int)((K.N + TPB - 1) / TPB);
     hipLaunchKernelGGL(k_init_bmax, dim3(nblk), dim3(TPB), 0, s, in, K, part);
@@ -2240,6 +2277,7 @@ hipError_t launch_face_check(const FacePtrs& in, const Consts& K, double* part, 
     hipLaunchKernelGGL(k_reduce, dim3(1), dim3(TPB), 0, s, (const double*)part, nblk, 1, 0, result);
     return hipGetLastError();
 }
+#endif
 
 template <typename TS>
 hipError_t launch_ghost(const FacePtrs& in, const Consts& K, char* dst, hipStream_t s) {
@@ -2249,12 +2287,14 @@ hipError_t launch_ghost(const FacePtrs& in, const Consts& K, char* dst, hipStrea
     return hipGetLastError();
 }
 
+#if RMHDLB_FORM == 64  // what depends on no storage form is built once
 hipError_t launch_init_ref(const InPtrs& in, const Consts& K, double* part, double* result, hipStream_t s) {
     const int nblk = (int)((K.N + TPB - 1) / TPB);
     hipLaunchKernelGGL(k_init_ref, dim3(nblk), dim3(TPB), 0, s, in, K, part);
     hipLaunchKernelGGL(k_reduce, dim3(1), dim3(TPB), 0, s, (const double*)part, nblk, 2, 0, result);
     return hipGetLastError();
 }
+#endif
 
 template <typename TS>
 hipError_t launch_init(const InPtrs& in, const Consts& K, double* scr, char* dst, hipStream_t s) {
@@ -2297,22 +2337,27 @@ hipError_t launch_guess_samples(const char* src, const Consts& K, double* faceB,
 }
 
 #define RMHD_INSTANTIATE(TS)                                                                                          \
-    template hipError_t launch_step<TS>(const char*, char*, const Consts&, const StepTuning&, double*,  \
+    template hipError_t launch_step<TS>(const char*, char*, const Consts&, const StepTuning&, double*,                \
                                         const GuessTables*, hipStream_t);                                             \
-    template hipError_t launch_moments<TS>(const char*, const Consts&, const OutPtrs&, const DiagBufs&,           \
+    template hipError_t launch_moments<TS>(const char*, const Consts&, const OutPtrs&, const DiagBufs&,               \
                                            const GuessTables*, hipStream_t);                                          \
-    template hipError_t launch_init<TS>(const InPtrs&, const Consts&, double*, char*, hipStream_t);         \
-    template hipError_t launch_ghost<TS>(const FacePtrs&, const Consts&, char*, hipStream_t);               \
-    template hipError_t launch_batch<TS>(const BatchInst*, int, int, int64_t, int, int, int, hipStream_t);            \
-    template hipError_t launch_batch_persistent<TS>(const BatchInst*, int, int, int, int, int, int, int*,            \
+    template hipError_t launch_init<TS>(const InPtrs&, const Consts&, double*, char*, hipStream_t);                   \
+    template hipError_t launch_ghost<TS>(const FacePtrs&, const Consts&, char*, hipStream_t);                         \
+    template hipError_t launch_batch<TS>(const BatchInst*, int, int, int64_t, bool, int, int, int, hipStream_t);      \
+    template hipError_t launch_batch_persistent<TS>(const BatchInst*, int, int, bool, int, int, int, int, int*,       \
                                                     hipStream_t);                                                     \
-    template hipError_t launch_guess_samples<TS>(const char*, const Consts&, double*, int, double*, double*,      \
+    template hipError_t launch_guess_samples<TS>(const char*, const Consts&, double*, int, double*, double*,          \
                                                  double*, double*, hipStream_t);                                      \
-    template hipError_t launch_export<TS>(const char*, double*, const Consts&, hipStream_t);                      \
+    template hipError_t launch_export<TS>(const char*, double*, const Consts&, hipStream_t);                          \
     template hipError_t launch_import<TS>(const double*, char*, const Consts&, hipStream_t);
 
+// One storage form per object, so that the forms compile side by side.
+#if RMHDLB_FORM == 64
 RMHD_INSTANTIATE(double)
+#elif RMHDLB_FORM == 32
 RMHD_INSTANTIATE(float)
+#else
 RMHD_INSTANTIATE(_Float16)
+#endif
 
 }  // namespace rmhd
