@@ -532,44 +532,62 @@ struct FeqCellT {
         eps0 = (V)e0;
     }
     template <int I>
-    __device__ __forceinline__ V eq() const {
-        constexpr int ex = EX[I], ey = EY[I], ez = EZ[I];
-        const V eb = ex * beta[0] + ey * beta[1] + ez * beta[2];
-        const V cross = (ex * ey) * beta[0] * beta[1] + (ex * ez) * beta[0] * beta[2] + (ey * ez) * beta[1] * beta[2];
-        const V diag = (ex * ex) * beta[0] * beta[0] + (ey * ey) * beta[1] * beta[1] + (ez * ez) * beta[2] * beta[2];
-        V fluid = A1 + V(19) * g2 * cross + V(4 * KAPPA) * g2 * eb + V(4.0 / 15.0) * g2 * (V(19) * diag - V(4) * b2);
-        if (I == 0) fluid += Bc;
-        const V Be = ex * cB[0] + ey * cB[1] + ez * cB[2];
-        const V Ee = ex * E[0] + ey * E[1] + ez * E[2];
-        const V BxEe = ex * BxE[0] + ey * BxE[1] + ez * BxE[2];
-        const V crossEB = (ex * ey) * (E[0] * E[1] + cB[0] * cB[1]) + (ex * ez) * (E[0] * E[2] + cB[0] * cB[2]) +
-                          (ey * ez) * (E[1] * E[2] + cB[1] * cB[2]);
-        const V em = V(2.3) * X - V(SQRT19_3) * BxEe - V(3.8) * (Be * Be + Ee * Ee) - V(6.65) * crossEB;
-        return V(weight(I)) * (P34 * fluid + eps0 * em);
-    }
+    __device__ __forceinline__ V eq() const;
 };
 using FeqCell = FeqCellT<double>;
+
+// e_I . v, and the product over the axis pair that a face diagonal spans, without the terms that a zero
+// component takes away (the compiler has to keep 0 x, which is not 0 for every x).
+template <int I, typename V>
+__device__ __forceinline__ V along(const V v[3]) {
+    constexpr int ex = EX[I], ey = EY[I], ez = EZ[I];
+    V r = V(0);
+    if constexpr (ex != 0) r = ex * v[0];
+    if constexpr (ey != 0) r = ex != 0 ? r + ey * v[1] : ey * v[1];
+    if constexpr (ez != 0) r = ex != 0 || ey != 0 ? r + ez * v[2] : ez * v[2];
+    return r;
+}
+template <int I, typename V, typename Fn>
+__device__ __forceinline__ V across(Fn&& prod) {
+    constexpr int ex = EX[I], ey = EY[I], ez = EZ[I];
+    if constexpr (ex * ey != 0)
+        return (ex * ey) * prod(0, 1);
+    else if constexpr (ex * ez != 0)
+        return (ex * ez) * prod(0, 2);
+    else if constexpr (ey * ez != 0)
+        return (ey * ez) * prod(1, 2);
+    else
+        return V(0);
+}
 
 // f_eq of direction sgn * e_I (sgn = +-1): the odd terms change sign, the
 // weight is that of e_I.
 template <int I, typename V>
 __device__ __forceinline__ V feq_signed(const FeqCellT<V>& f, V sgn) {
     constexpr int ex = EX[I], ey = EY[I], ez = EZ[I];
-    const V eb = sgn * (ex * f.beta[0] + ey * f.beta[1] + ez * f.beta[2]);
-    const V cross =
-        (ex * ey) * f.beta[0] * f.beta[1] + (ex * ez) * f.beta[0] * f.beta[2] + (ey * ez) * f.beta[1] * f.beta[2];
-    const V diag = (ex * ex) * f.beta[0] * f.beta[0] + (ey * ey) * f.beta[1] * f.beta[1] +
-                   (ez * ez) * f.beta[2] * f.beta[2];
-    const V fluid =
-        f.A1 + V(19) * f.g2 * cross + V(4 * KAPPA) * f.g2 * eb + V(4.0 / 15.0) * f.g2 * (V(19) * diag - V(4) * f.b2);
-    const V Be = ex * f.cB[0] + ey * f.cB[1] + ez * f.cB[2];
-    const V Ee = ex * f.E[0] + ey * f.E[1] + ez * f.E[2];
-    const V BxEe = sgn * (ex * f.BxE[0] + ey * f.BxE[1] + ez * f.BxE[2]);
-    const V crossEB = (ex * ey) * (f.E[0] * f.E[1] + f.cB[0] * f.cB[1]) +
-                      (ex * ez) * (f.E[0] * f.E[2] + f.cB[0] * f.cB[2]) +
-                      (ey * ez) * (f.E[1] * f.E[2] + f.cB[1] * f.cB[2]);
+    const V eb = sgn * along<I>(f.beta);
+    const V cross = across<I, V>([&](int a, int b) { return f.beta[a] * f.beta[b]; });
+    constexpr int a0 = ex ? 0 : (ey ? 1 : 2), a1 = ez ? 2 : 1;  // the axes of e_I
+    // their squares; the rounding of the sum is fixed, so that a state does not depend on the compiler's choice
+    V diag = V(0);
+    if constexpr (I > 6)
+        diag = a1 == 1 && sizeof(V) == 8 ? fma(f.beta[a0], f.beta[a0], f.beta[a1] * f.beta[a1])
+                                         : fma(f.beta[a1], f.beta[a1], f.beta[a0] * f.beta[a0]);
+    else if constexpr (I > 0)
+        diag = f.beta[a0] * f.beta[a0];
+    V fluid = f.A1 + V(19) * f.g2 * cross + V(4 * KAPPA) * f.g2 * eb +
+              V(4.0 / 15.0) * f.g2 * (V(19) * diag - V(4) * f.b2);
+    if constexpr (I == 0) fluid += f.Bc;
+    const V Be = along<I>(f.cB), Ee = along<I>(f.E);
+    const V BxEe = sgn * along<I>(f.BxE);
+    const V crossEB = across<I, V>([&](int a, int b) { return f.E[a] * f.E[b] + f.cB[a] * f.cB[b]; });
     const V em = V(2.3) * f.X - V(SQRT19_3) * BxEe - V(3.8) * (Be * Be + Ee * Ee) - V(6.65) * crossEB;
     return V(weight(I)) * (f.P34 * fluid + f.eps0 * em);
+}
+template <typename V>
+template <int I>
+__device__ __forceinline__ V FeqCellT<V>::eq() const {
+    return feq_signed<I>(*this, V(1));
 }
 
 template <int I, typename Fn>
@@ -600,6 +618,34 @@ constexpr int PTPB = 256;  // threads of a fused-step block: 128 cells, two lane
 // leaves a wave the 256 registers that the cell's populations and two records'
 // loads in flight take (three spilled: FP32 batch kernel 67 registers).
 constexpr int FUSED_WAVES = 2;
+// The median of a, b and 0: minmod(a, b) in one instruction (FP64: four) instead of five (seven).
+__device__ __forceinline__ float median0(float a, float b) { return __builtin_amdgcn_fmed3f(a, b, 0.0f); }
+__device__ __forceinline__ double median0(double a, double b) { return fmax(fmin(a, b), fmin(fmax(a, b), 0.0)); }
+
+// x + y and x - y of stored values in the step's arithmetic.  FP16 values go
+// through a fused multiply-add by a 1 that the compiler does not see, which
+// the mixed-precision instruction takes with both conversions in one.
+template <typename V, typename T>
+__device__ __forceinline__ V sum_of(T x, T y, V one) {
+    return sizeof(T) == sizeof(V) ? V(x) + V(y) : fma(V(x), one, V(y));
+}
+template <typename V, typename T>
+__device__ __forceinline__ V difference(T x, T y, V one) {
+    return sizeof(T) == sizeof(V) ? V(x) - V(y) : fma(V(x), one, -V(y));
+}
+
+// A population after its transport along the link without viscosity:
+// f - C (face_p - face_m), face values f + slope minmod of the differences
+// on both sides.  (b 0 + f carries a NaN of the downwind neighbour on, as
+// comparisons would; the median of a NaN is one of the other two.)
+template <typename V, typename T>
+__device__ __forceinline__ V advect(T f, T m1, T m2, T p1, V cour, V slope, V one) {
+    const V a = difference<V>(f, m1, one), b = difference<V>(p1, f, one), c = difference<V>(m1, m2, one);
+    const V face_p = fma(slope, median0(a, b), fma(b, V(0), V(f)));
+    const V face_m = fma(slope, median0(c, a), V(m1));
+    return fma(-cour, face_p - face_m, V(f));
+}
+
 // Link of a slot as the step walks it (direction 2s - 1).  FLAT: the grid has
 // one z-plane whose z-neighbours are the cell itself, so links and the
 // Laplacian lie in the plane.
@@ -731,17 +777,14 @@ __device__ __forceinline__ void pair_cell(const char* __restrict__ sd, char* __r
                 issue_h();
             Raw& r = raw[s & 1];
             arrive(ic, r);
-            const V f0 = r.c0.x, fm2 = r.m2.x, fm1 = r.m1.x, fp1 = r.p1.x;
+            const V f0 = r.c0.x, fm1 = r.m1.x, fp1 = r.p1.x;
             const V up = h ? fm1 : fp1, dn = h ? fp1 : fm1;  // f at x + e_i0 and x - e_i0 (lane 1 walks -e)
             const V lxp = K_::lap_x ? r.xp : up, lxm = K_::lap_x ? r.xm : dn;
             const V lyp = K_::lap_y ? r.yp : up, lym = K_::lap_y ? r.ym : dn;
             const V lzp = K_::lap_z || FLAT ? r.zp : up, lzm = K_::lap_z || FLAT ? r.zm : dn;
             const V lap = (lxp + lxm) + (lyp + lym) + (lzp + lzm) - V(6) * f0;
-            const V fv = f0 - cour * ((f0 + slope * minmod(f0 - fm1, fp1 - f0)) -
-                                      (fm1 + slope * minmod(fm1 - fm2, f0 - fm1))) + kv * lap;
-            const V g0 = r.c0.y, gm2 = r.m2.y, gm1 = r.m1.y, gp1 = r.p1.y;
-            const V gv = g0 - cour * ((g0 + slope * minmod(g0 - gm1, gp1 - g0)) -
-                                      (gm1 + slope * minmod(gm1 - gm2, g0 - gm1)));
+            const V fv = fma(kv, lap, advect<V, TS>(r.c0.x, r.m1.x, r.m2.x, r.p1.x, cour, slope, V(1)));
+            const V gv = advect<V, TS>(r.c0.y, r.m1.y, r.m2.y, r.p1.y, cour, slope, V(1));
             Fv[s] = fv;
             Gv[s] = gv;
             pin(Fv[s]), pin(Gv[s]);  // the slot's arithmetic stays here
@@ -960,23 +1003,24 @@ __device__ __forceinline__ void quad_cell(const char* __restrict__ sd, char* __r
                   lap_ym = rec(nb.at(0, -1, 0)), lap_zp = rec(nb.at(0, 0, 1)), lap_zm = rec(nb.at(0, 0, -1));
     // Transport and moments of slot s from its quads at the link points x - 2e .. x + 2e and the
     // Laplacian's six neighbours.
-    auto transport = [&](auto sc, const vec4<V>& q0, const vec4<V>& qm2, const vec4<V>& qm1, const vec4<V>& qp1,
-                         const vec4<V>& qp2, const vec4<V>& lxp, const vec4<V>& lxm, const vec4<V>& lyp,
-                         const vec4<V>& lym, const vec4<V>& lzp, const vec4<V>& lzm) {
+    V one = V(1);  // not seen by the compiler: see sum_of
+    if constexpr (sizeof(TS) != sizeof(V)) asm("" : "+s"(one));
+    auto transport = [&](auto sc, const vec4<TS>& q0, const vec4<TS>& qm2, const vec4<TS>& qm1, const vec4<TS>& qp1,
+                         const vec4<TS>& qp2, const vec4<TS>& lxp, const vec4<TS>& lxm, const vec4<TS>& lyp,
+                         const vec4<TS>& lym, const vec4<TS>& lzp, const vec4<TS>& lzm) {
         constexpr int s = decltype(sc)::value;
         constexpr int i0 = 2 * s - 1, i1 = 2 * s;
         constexpr int ex = EX[i0], ey = EY[i0], ez = EZ[i0];
         // +e: upwind stencil x - 2e, x - e, x, x + e; -e: x + 2e, x + e, x, x - e
-        const V lap0 = (lxp.x + lxm.x) + (lyp.x + lym.x) + (lzp.x + lzm.x) - V(6) * q0.x;
-        const V lap1 = (lxp.z + lxm.z) + (lyp.z + lym.z) + (lzp.z + lzm.z) - V(6) * q0.z;
-        const V fv0 = q0.x - cour * ((q0.x + slope * minmod(q0.x - qm1.x, qp1.x - q0.x)) -
-                                     (qm1.x + slope * minmod(qm1.x - qm2.x, q0.x - qm1.x))) + kv * lap0;
-        const V fv1 = q0.z - cour * ((q0.z + slope * minmod(q0.z - qp1.z, qm1.z - q0.z)) -
-                                     (qp1.z + slope * minmod(qp1.z - qp2.z, q0.z - qp1.z))) + kv * lap1;
-        const V gv0 = q0.y - cour * ((q0.y + slope * minmod(q0.y - qm1.y, qp1.y - q0.y)) -
-                                     (qm1.y + slope * minmod(qm1.y - qm2.y, q0.y - qm1.y)));
-        const V gv1 = q0.w - cour * ((q0.w + slope * minmod(q0.w - qp1.w, qm1.w - q0.w)) -
-                                     (qp1.w + slope * minmod(qp1.w - qp2.w, q0.w - qp1.w)));
+        auto laplacian = [&](TS f0, TS xp, TS xm, TS yp, TS ym, TS zp, TS zm) {
+            return fma(V(-6), V(f0), sum_of<V>(xp, xm, one) + sum_of<V>(yp, ym, one) + sum_of<V>(zp, zm, one));
+        };
+        const V fv0 = fma(kv, laplacian(q0.x, lxp.x, lxm.x, lyp.x, lym.x, lzp.x, lzm.x),
+                          advect<V, TS>(q0.x, qm1.x, qm2.x, qp1.x, cour, slope, one));
+        const V fv1 = fma(kv, laplacian(q0.z, lxp.z, lxm.z, lyp.z, lym.z, lzp.z, lzm.z),
+                          advect<V, TS>(q0.z, qp1.z, qp2.z, qm1.z, cour, slope, one));
+        const V gv0 = advect<V, TS>(q0.y, qm1.y, qm2.y, qp1.y, cour, slope, one);
+        const V gv1 = advect<V, TS>(q0.w, qp1.w, qp2.w, qm1.w, cour, slope, one);
         Fv[i0] = fv0;
         Fv[i1] = fv1;
         Gv[i0] = gv0;
@@ -1045,8 +1089,8 @@ __device__ __forceinline__ void quad_cell(const char* __restrict__ sd, char* __r
         pin_links(sa, q.a);
         if constexpr (sb.value != 0) pin_links(sb, q.b);
     };
-    auto quad_of = [](const auto& w, int half) {  // the quad in a record or half record, as V
-        vec4<V> r;
+    auto quad_of = [](const auto& w, int half) {  // the quad in a record or half record
+        vec4<TS> r;
         if constexpr (sizeof(w) == 16 && !DQ) {
             r.x = __builtin_bit_cast(float, (unsigned)w[0]), r.y = __builtin_bit_cast(float, (unsigned)w[1]);
             r.z = __builtin_bit_cast(float, (unsigned)w[2]), r.w = __builtin_bit_cast(float, (unsigned)w[3]);
@@ -1054,18 +1098,18 @@ __device__ __forceinline__ void quad_cell(const char* __restrict__ sd, char* __r
             const int o = sizeof(w) == 16 ? 2 * half : 0;
             const vec2<_Float16> lo = __builtin_bit_cast(vec2<_Float16>, (unsigned)w[o]),
                                  hi = __builtin_bit_cast(vec2<_Float16>, (unsigned)w[o + 1]);
-            r.x = (V)lo.x, r.y = (V)lo.y, r.z = (V)hi.x, r.w = (V)hi.y;
+            r.x = lo.x, r.y = lo.y, r.z = hi.x, r.w = hi.y;
         }
         return r;
     };
     auto use = [&](auto sc, const Raw& q, int half, const Half (&lk)[4]) {
         constexpr int s = decltype(sc)::value;
         using K_ = Link<s, FLAT>;
-        const vec4<V> c = quad_of(q.c, half), xp = quad_of(q.xp, half), xm = quad_of(q.xm, half),
+        const vec4<TS> c = quad_of(q.c, half), xp = quad_of(q.xp, half), xm = quad_of(q.xm, half),
                       yp = quad_of(q.yp, half), ym = quad_of(q.ym, half), zp = FLAT ? c : quad_of(q.zp, half),
                       zm = FLAT ? c : quad_of(q.zm, half);
-        const vec4<V> m2 = K_::axes > 0 ? quad_of(lk[0], 0) : c, p2 = K_::axes > 0 ? quad_of(lk[1], 0) : c;
-        vec4<V> m1, p1;
+        const vec4<TS> m2 = K_::axes > 0 ? quad_of(lk[0], 0) : c, p2 = K_::axes > 0 ? quad_of(lk[1], 0) : c;
+        vec4<TS> m1, p1;
         if constexpr (K_::axes == 0)
             m1 = p1 = c;
         else if constexpr (K_::axes > 1)
@@ -1104,7 +1148,7 @@ __device__ __forceinline__ void quad_cell(const char* __restrict__ sd, char* __r
             arrive(rc, q);
             if constexpr (r == 0 && !DQ) {
                 pin(rest_raw);
-                const vec4<V> fg0 = quad_of(rest_raw, 0);
+                const vec4<TS> fg0 = quad_of(rest_raw, 0);
                 Fv[0] = fg0.x;
                 Gv[0] = fg0.y;
                 Hv[QH] = fg0.z;
@@ -1115,7 +1159,7 @@ __device__ __forceinline__ void quad_cell(const char* __restrict__ sd, char* __r
             if constexpr (slot_b(rc).value != 0) {
                 use(slot_b(rc), q, 1, q.b);
             } else if constexpr (DQ) {  // the rest quad
-                const vec4<V> fg0 = quad_of(q.c, 1);
+                const vec4<TS> fg0 = quad_of(q.c, 1);
                 Fv[0] = fg0.x;
                 Gv[0] = fg0.y;
                 Hv[QH] = fg0.z;
