@@ -174,12 +174,6 @@ constexpr double INV_SQRT2 = 0.70710678118654752;
 
 // ------------------------------------------------------------- primitives
 
-template <typename V>
-__device__ __forceinline__ V minmod(V a, V b) {
-    if (a * b <= V(0)) return V(0);
-    return fabs(a) < fabs(b) ? a : b;
-}
-
 // |b|^2 with its rounding fixed: left to the compiler, which of the products
 // is fused depends on what else uses them, and with it the last bit of gamma.
 __device__ __forceinline__ double norm2(const double b[3]) { return fma(b[2], b[2], fma(b[0], b[0], b[1] * b[1])); }

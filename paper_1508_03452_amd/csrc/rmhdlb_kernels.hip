@@ -240,11 +240,6 @@ struct CellSol {
     bool ok;
 };
 
-// ... plus the transported f, g and streamed h (one thread per cell).
-struct Macro : CellSol {
-    double F[Q], G[Q], H[QH + 1];
-};
-
 // Fluid tensor T_fl = T - T_EM of the recovery: E_f = T_fl^00, S = T_fl^0a,
 // Pi = T_fl^ab (xx, yy, zz, xy, xz, yz), with E_prev and the recovery's B
 // (this step's, or with the previous-B reading the previous step's).
@@ -383,120 +378,6 @@ __device__ __forceinline__ void solve_cell(const Consts& K, CellSol& M, const do
     M.J[0] = sg * (M.E[0] + uxB0 - Eu * u0) + M.rho_g * u0;
     M.J[1] = sg * (M.E[1] + uxB1 - Eu * u1) + M.rho_g * u1;
     M.J[2] = sg * (M.E[2] + uxB2 - Eu * u2) + M.rho_g * u2;
-}
-
-// Transport (collide-then-transport reading of Eq. rlb): link-wise
-// minmod-MUSCL flux difference, plus the 7-point bulk-viscosity Laplacian
-// for i != 0; g without viscosity.  Then the streaming of h, the moments,
-// the recovery and E, J.
-// One thread per cell, FP64 arithmetic (moments and diagnostics pass).  The
-// shift of a stored array is constant in space, so it transports to itself
-// and is added back after the transport.
-template <int GM, typename TS, typename TE>
-__device__ __forceinline__ void macroscopic(const char* __restrict__ src, const double* __restrict__ faceB,
-                                            const GuessTables* __restrict__ gt, const Consts& K, int cell,
-                                            const Nbr& nb, int x, int y, int z, Macro& M) {
-    const int pos = (int)K.g0 + cell;
-    M.T00 = 0.0;
-    M.N0 = 0.0;
-    double t0x = 0, t0y = 0, t0z = 0, txx = 0, tyy = 0, tzz = 0, txy = 0, txz = 0, tyz = 0;
-#pragma unroll
-    for (int i = 0; i < Q; ++i) {
-        auto fg = [&](int o) {
-            return ldv2<double, TS>(src, f_at<TS>(K, i, pos + o));
-        };
-        auto fo = [&](int o) { return ld<TS>(src, f_at<TS>(K, i, pos + o)); };
-        const vec2<double> c0 = fg(0);
-        const double f0 = c0.x, g0 = c0.y;
-        double fv = f0, gv = g0;
-        if (i != 0) {
-            const int ex = EX[i], ey = EY[i], ez = EZ[i];
-            const int om2 = nb.at(-2 * ex, -2 * ey, -2 * ez), om1 = nb.at(-ex, -ey, -ez), op1 = nb.at(ex, ey, ez);
-            const vec2<double> m2 = fg(om2), m1 = fg(om1), p1 = fg(op1);
-            {
-                const double fm2 = m2.x, fm1 = m1.x, fp1 = p1.x;
-                const double face_p = f0 + K.slope * minmod(f0 - fm1, fp1 - f0);
-                const double face_m = fm1 + K.slope * minmod(fm1 - fm2, f0 - fm1);
-                const double lap = (fo(nb.at(1, 0, 0)) + fo(nb.at(-1, 0, 0))) +
-                                   (fo(nb.at(0, 1, 0)) + fo(nb.at(0, -1, 0))) +
-                                   (fo(nb.at(0, 0, 1)) + fo(nb.at(0, 0, -1))) - 6.0 * f0;
-                fv = f0 - K.cour * (face_p - face_m) + K.kv * lap;
-            }
-            {
-                const double gm2 = m2.y, gm1 = m1.y, gp1 = p1.y;
-                const double face_p = g0 + K.slope * minmod(g0 - gm1, gp1 - g0);
-                const double face_m = gm1 + K.slope * minmod(gm1 - gm2, g0 - gm1);
-                gv = g0 - K.cour * (face_p - face_m);
-            }
-        }
-        fv += fshift(K, i);
-        gv += gshift(K, i);
-        M.F[i] = fv;
-        M.G[i] = gv;
-        M.T00 += fv;
-        M.N0 += gv;
-        if (EX[i]) t0x += EX[i] * fv;
-        if (EY[i]) t0y += EY[i] * fv;
-        if (EZ[i]) t0z += EZ[i] * fv;
-        if (EX[i]) txx += fv;
-        if (EY[i]) tyy += fv;
-        if (EZ[i]) tzz += fv;
-        if (EX[i] * EY[i]) txy += (EX[i] * EY[i]) * fv;
-        if (EX[i] * EZ[i]) txz += (EX[i] * EZ[i]) * fv;
-        if (EY[i] * EZ[i]) tyz += (EY[i] * EZ[i]) * fv;
-    }
-    M.T0[0] = KAPPA * t0x;
-    M.T0[1] = KAPPA * t0y;
-    M.T0[2] = KAPPA * t0z;
-    M.Tab[0] = KAPPA2 * txx;
-    M.Tab[1] = KAPPA2 * tyy;
-    M.Tab[2] = KAPPA2 * tzz;
-    M.Tab[3] = KAPPA2 * txy;
-    M.Tab[4] = KAPPA2 * txz;
-    M.Tab[5] = KAPPA2 * tyz;
-
-    // stream h (Eq. LB_Maxwell): h_k(x) = h*_k(x - v_k dt)
-    double ehx = 0, ehy = 0, ehz = 0, bx = 0, by = 0, bz = 0, hs = 0;
-#pragma unroll
-    for (int k = 0; k < QH; ++k) {
-        const double h = ld<TS>(src, h_at<TS>(K, k, pos + nb.at(-SX[k], -SY[k], -SZ[k])));
-        M.H[k] = h;
-        hs += h;
-        if (EHX[k]) ehx += EHX[k] * h;
-        if (EHY[k]) ehy += EHY[k] * h;
-        if (EHZ[k]) ehz += EHZ[k] * h;
-        if (BHX[k]) bx += BHX[k] * h;
-        if (BHY[k]) by += BHY[k] * h;
-        if (BHZ[k]) bz += BHZ[k] * h;
-    }
-    M.H[QH] = ld<TS>(src, h_at<TS>(K, QH, pos));
-    const double ec = K.c * INV_SQRT2;  // |e_k| / |ehat_k|
-    M.Epr[0] = ec * ehx;
-    M.Epr[1] = ec * ehy;
-    M.Epr[2] = ec * ehz;
-    M.B[0] = bx;
-    M.B[1] = by;
-    M.B[2] = bz;
-    M.rho = M.H[QH] + hs;
-
-    // previous E and its Gauss charge
-    auto Ea = [&](int a, int o) { return ld<TE>(src, e_at<TS>(K, a, pos + o)); };
-    M.Ep[0] = Ea(0, 0);
-    M.Ep[1] = Ea(1, 0);
-    M.Ep[2] = Ea(2, 0);
-    M.rho_g = K.eps0 * K.inv_2dx *
-              ((Ea(0, nb.at(1, 0, 0)) - Ea(0, nb.at(-1, 0, 0))) + (Ea(1, nb.at(0, 1, 0)) - Ea(1, nb.at(0, -1, 0))) +
-               (Ea(2, nb.at(0, 0, 1)) - Ea(2, nb.at(0, 0, -1))));
-
-    if (K.divb) apply_face_b(K, faceB, x, y, z, M.B);
-    if (K.bprev) {
-        double Bp[3];
-#pragma unroll
-        for (int a = 0; a < 3; ++a) Bp[a] = Ea(3 + a, 0);
-        solve_cell<GM>(K, M, Bp, gt);
-    } else {
-        solve_cell<GM>(K, M, M.B, gt);
-    }
 }
 
 // f_eq of Eq. Dis_fun_EM in normalised variables (F = (c_t/c_0)^2 f), with
@@ -671,6 +552,207 @@ struct Link {
 template <typename T>
 __device__ __forceinline__ void pin(T& v) {
     asm volatile("" : "+v"(v)::"memory");
+}
+
+// Transport (collide-then-transport reading of Eq. rlb): link-wise
+// minmod-MUSCL flux difference, plus the 7-point bulk-viscosity Laplacian
+// for i != 0; g without viscosity.  Then the streaming of h, the moments,
+// the recovery and E, J.
+// One thread per cell, FP64 arithmetic (moments and diagnostics pass).  The
+// shift of a stored array is constant in space, so it transports to itself
+// and is added back after the transport.  What bounds it is what bounds the
+// step, so a slot's loads (its two opposite directions) are likewise in
+// flight while the slot before it is used; 256x256x512, the whole pass in
+// FP64: 20.4 ms with loads where the compiler put them (100 registers
+// spilled), 10.2 so; FP16 10.8 and 3.8.
+template <int GM, typename TS, typename TE>
+__device__ __forceinline__ void macroscopic(const char* __restrict__ src, const double* __restrict__ faceB,
+                                            const GuessTables* __restrict__ gt, const Consts& K, int cell,
+                                            const Nbr& nb, int x, int y, int z, CellSol& M) {
+    using L = Lay<TS>;
+    constexpr bool PAIR = !quad_layout<TS>();
+    const int pos = (int)K.g0 + cell;
+    double t0x = 0, t0y = 0, t0z = 0, txx = 0, tyy = 0, tzz = 0, txy = 0, txz = 0, tyz = 0;
+    // (f, g) of the slot's direction 2s - 1 and of 2s
+    using Both = vec4<TS>;
+    // f of both directions (quads come whole)
+    using Fs = std::conditional_t<PAIR, vec2<TS>, vec4<TS>>;
+    struct Raw {
+        Both c, m1, p1;
+        std::conditional_t<PAIR, vec2<TS>, vec4<TS>> m2, p2;  // FP64: of the direction that needs them
+        Fs xp, xm, yp, ym, zp, zm;
+    };
+    auto issue = [&](auto ic, Raw& r) {
+        constexpr int s = decltype(ic)::value;
+        using K_ = Link<s, false>;
+        constexpr int i0 = 2 * s - 1, i1 = 2 * s;
+        auto both = [&](int o) {
+            const int64_t q = lane_off<16>(K, pos + o);
+            Both v;
+            if constexpr (PAIR) {
+                const vec2<TS> a = *reinterpret_cast<const vec2<TS>*>(src + q + rec_off<TS>(i0));
+                const vec2<TS> b = *reinterpret_cast<const vec2<TS>*>(src + q + rec_off<TS>(i1));
+                v.x = a.x, v.y = a.y, v.z = b.x, v.w = b.y;
+            } else {
+                v = *reinterpret_cast<const Both*>(src + q + rec_off<TS>(i0));
+            }
+            return v;
+        };
+        auto one_of = [&](int i, int o) {
+            return *reinterpret_cast<const std::conditional_t<PAIR, vec2<TS>, vec4<TS>>*>(
+                src + lane_off<16>(K, pos + o) + rec_off<TS>(PAIR ? i : i0));
+        };
+        auto fs = [&](int o) {
+            if constexpr (PAIR) {
+                const int64_t q = lane_off<16>(K, pos + o);
+                Fs v;
+                v.x = *reinterpret_cast<const TS*>(src + q + rec_off<TS>(i0));
+                v.y = *reinterpret_cast<const TS*>(src + q + rec_off<TS>(i1));
+                return v;
+            } else {
+                return both(o);
+            }
+        };
+        r.c = both(0);
+        r.m1 = both(nb.at(-K_::x, -K_::y, -K_::z));
+        r.p1 = both(nb.at(K_::x, K_::y, K_::z));
+        r.m2 = one_of(i0, nb.at(-2 * K_::x, -2 * K_::y, -2 * K_::z));
+        r.p2 = one_of(i1, nb.at(2 * K_::x, 2 * K_::y, 2 * K_::z));
+        if constexpr (K_::lap_x) r.xp = fs(nb.at(1, 0, 0)), r.xm = fs(nb.at(-1, 0, 0));
+        if constexpr (K_::lap_y) r.yp = fs(nb.at(0, 1, 0)), r.ym = fs(nb.at(0, -1, 0));
+        if constexpr (K_::lap_z) r.zp = fs(nb.at(0, 0, 1)), r.zm = fs(nb.at(0, 0, -1));
+    };
+    auto arrive = [&](auto ic, Raw& r) {
+        using K_ = Link<decltype(ic)::value, false>;
+        pin(r.c), pin(r.m1), pin(r.p1), pin(r.m2), pin(r.p2);
+        auto from_link = [](const Both& v) {
+            Fs f;
+            if constexpr (PAIR)
+                f.x = v.x, f.y = v.z;
+            else
+                f = v;
+            return f;
+        };
+        if constexpr (K_::lap_x)
+            pin(r.xp), pin(r.xm);
+        else
+            r.xp = from_link(r.p1), r.xm = from_link(r.m1);
+        if constexpr (K_::lap_y)
+            pin(r.yp), pin(r.ym);
+        else
+            r.yp = from_link(r.p1), r.ym = from_link(r.m1);
+        if constexpr (K_::lap_z)
+            pin(r.zp), pin(r.zm);
+        else
+            r.zp = from_link(r.p1), r.zm = from_link(r.m1);
+    };
+    TS hraw[QH];
+    auto issue_h = [&]() {
+#pragma unroll
+        for (int m = 0; m < QH / 2; ++m) {
+            const int k0 = 2 * m, o = nb.at(-SX[k0], -SY[k0], -SZ[k0]);
+            if constexpr (PAIR) {
+                hraw[k0] = *reinterpret_cast<const TS*>(src + h_at<TS>(K, k0, pos + o));
+                hraw[k0 + 1] = *reinterpret_cast<const TS*>(src + h_at<TS>(K, k0 + 1, pos + o));
+            } else {
+                const vec2<TS> v = *reinterpret_cast<const vec2<TS>*>(src + h_at<TS>(K, k0, pos + o));
+                hraw[k0] = v.x, hraw[k0 + 1] = v.y;
+            }
+        }
+    };
+    const double f_rest = ld<TS>(src, f_at<TS>(K, 0, pos)), g_rest = ld<TS>(src, g_at<TS>(K, 0, pos));
+    Raw raw[2];
+    issue(std::integral_constant<int, 1>{}, raw[1]);
+    M.T00 = f_rest + fshift(K, 0);
+    M.N0 = g_rest + gshift(K, 0);
+    static_for<1>([&](auto ic) {
+        constexpr int s = decltype(ic)::value;
+        if constexpr (s <= 9) {
+            if constexpr (s < 9)
+                issue(std::integral_constant<int, s + 1>{}, raw[(s + 1) & 1]);
+            else
+                issue_h();
+            Raw& r = raw[s & 1];
+            arrive(ic, r);
+            auto add = [&](auto qc, double f0, double fm1, double fm2, double fp1, double g0, double gm1, double gm2,
+                           double gp1, double sx, double sy, double sz) {
+                constexpr int i = decltype(qc)::value;
+                const double lap = fma(-6.0, f0, sx + sy + sz);
+                const double fv = fma(K.kv, lap, advect<double, double>(f0, fm1, fm2, fp1, K.cour, K.slope, 1.0)) +
+                                  fshift(K, i);
+                const double gv = advect<double, double>(g0, gm1, gm2, gp1, K.cour, K.slope, 1.0) + gshift(K, i);
+                M.T00 += fv;
+                M.N0 += gv;
+                if (EX[i]) t0x += EX[i] * fv;
+                if (EY[i]) t0y += EY[i] * fv;
+                if (EZ[i]) t0z += EZ[i] * fv;
+                if (EX[i]) txx += fv;
+                if (EY[i]) tyy += fv;
+                if (EZ[i]) tzz += fv;
+                if (EX[i] * EY[i]) txy += (EX[i] * EY[i]) * fv;
+                if (EX[i] * EZ[i]) txz += (EX[i] * EZ[i]) * fv;
+                if (EY[i] * EZ[i]) tyz += (EY[i] * EZ[i]) * fv;
+            };
+            auto second = [](const Fs& v) { return (double)(PAIR ? v[1] : v[PAIR ? 1 : 2]); };
+            add(std::integral_constant<int, 2 * s - 1>{}, r.c.x, r.m1.x, r.m2[0], r.p1.x, r.c.y, r.m1.y, r.m2[1],
+                r.p1.y, (double)r.xp[0] + (double)r.xm[0], (double)r.yp[0] + (double)r.ym[0],
+                (double)r.zp[0] + (double)r.zm[0]);
+            add(std::integral_constant<int, 2 * s>{}, r.c.z, r.p1.z, r.p2[PAIR ? 0 : 2], r.m1.z, r.c.w, r.p1.w,
+                r.p2[PAIR ? 1 : 3], r.m1.w, second(r.xp) + second(r.xm), second(r.yp) + second(r.ym),
+                second(r.zp) + second(r.zm));
+            pin(M.T00), pin(M.N0);  // the slot's arithmetic stays here
+        }
+    });
+    M.T0[0] = KAPPA * t0x;
+    M.T0[1] = KAPPA * t0y;
+    M.T0[2] = KAPPA * t0z;
+    M.Tab[0] = KAPPA2 * txx;
+    M.Tab[1] = KAPPA2 * tyy;
+    M.Tab[2] = KAPPA2 * tzz;
+    M.Tab[3] = KAPPA2 * txy;
+    M.Tab[4] = KAPPA2 * txz;
+    M.Tab[5] = KAPPA2 * tyz;
+
+    // previous E and its Gauss charge
+    auto Ea = [&](int a, int o) { return ld<TE>(src, e_at<TS>(K, a, pos + o)); };
+    M.Ep[0] = Ea(0, 0);
+    M.Ep[1] = Ea(1, 0);
+    M.Ep[2] = Ea(2, 0);
+    M.rho_g = K.eps0 * K.inv_2dx *
+              ((Ea(0, nb.at(1, 0, 0)) - Ea(0, nb.at(-1, 0, 0))) + (Ea(1, nb.at(0, 1, 0)) - Ea(1, nb.at(0, -1, 0))) +
+               (Ea(2, nb.at(0, 0, 1)) - Ea(2, nb.at(0, 0, -1))));
+
+    // stream h (Eq. LB_Maxwell): h_k(x) = h*_k(x - v_k dt)
+    double ehx = 0, ehy = 0, ehz = 0, bx = 0, by = 0, bz = 0, hs = 0;
+#pragma unroll
+    for (int k = 0; k < QH; ++k) {
+        const double h = (double)hraw[k];
+        hs += h;
+        if (EHX[k]) ehx += EHX[k] * h;
+        if (EHY[k]) ehy += EHY[k] * h;
+        if (EHZ[k]) ehz += EHZ[k] * h;
+        if (BHX[k]) bx += BHX[k] * h;
+        if (BHY[k]) by += BHY[k] * h;
+        if (BHZ[k]) bz += BHZ[k] * h;
+    }
+    const double ec = K.c * INV_SQRT2;  // |e_k| / |ehat_k|
+    M.Epr[0] = ec * ehx;
+    M.Epr[1] = ec * ehy;
+    M.Epr[2] = ec * ehz;
+    M.B[0] = bx;
+    M.B[1] = by;
+    M.B[2] = bz;
+    M.rho = ld<TS>(src, h_at<TS>(K, QH, pos)) + hs;
+
+    if (K.divb) apply_face_b(K, faceB, x, y, z, M.B);
+    if (K.bprev) {
+        double Bp[3];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) Bp[a] = Ea(3 + a, 0);
+        solve_cell<GM>(K, M, Bp, gt);
+    } else {
+        solve_cell<GM>(K, M, M.B, gt);
+    }
 }
 
 // The two lanes of a cell are l and l ^ 32 of a wavefront: each half of the
@@ -1645,7 +1727,7 @@ constexpr double NO_INDEX = 9.0e15;  // larger than any cell index, exact in FP6
 // Every thread runs the cell pass (on the edge cell when past a ragged edge,
 // so that the network sees whole wavefronts); only real cells write.
 template <typename TS, typename TE, int GM>
-__global__ __launch_bounds__(TPB) void k_moments(const char* __restrict__ src, const double* __restrict__ faceB,
+__global__ __launch_bounds__(TPB, 2) void k_moments(const char* __restrict__ src, const double* __restrict__ faceB,
                                                  const GuessTables* __restrict__ gt, Consts K, int tiles_x,
                                                  int tiles_y, int ntiles, OutPtrs out, double* __restrict__ scratch,
                                                  double* __restrict__ part, double* __restrict__ nullp) {
@@ -1660,7 +1742,7 @@ __global__ __launch_bounds__(TPB) void k_moments(const char* __restrict__ src, c
     double key = __builtin_inf(), idx = NO_INDEX;
     const int cell = x + K.nx * (y + K.ny * z);
     const Nbr nb = make_nbr<true>(K, x, y, z);
-    Macro M;
+    CellSol M;
     if constexpr (GM == GUESS_NONE)
         macroscopic<GM, TS, TE>(src, faceB, gt, K, cell, nb, x, y, z, M);
     else if (*K.gflag_rd == K.gstep - 1)  // the guess the next step would take
@@ -1773,18 +1855,24 @@ __global__ __launch_bounds__(TPB) void k_moments(const char* __restrict__ src, c
     }
 }
 
-[[maybe_unused]] static __global__ __launch_bounds__(TPB) void k_reduce(const double* __restrict__ part, int nblk, int width, int is_max,
-                                                double* __restrict__ out) {
-    for (int j = 0; j < width; ++j) {
-        double acc = 0.0;
-        for (int b = threadIdx.x; b < nblk; b += TPB) {
-            const double v = part[(int64_t)b * width + j];
-            acc = is_max ? fmax(acc, v) : acc + v;
-        }
-        double r = is_max ? block_max_value(acc) : block_sum_value(acc);
-        if (threadIdx.x == 0) out[j] = r;
-        __syncthreads();
+[[maybe_unused]] static __global__ __launch_bounds__(TPB) void k_reduce(const double* __restrict__ part, int nblk, int width,
+                                                                        int is_max, double* __restrict__ out) {
+    const int j = blockIdx.x;  // one column per block; 16 rows of a thread in flight, added in order
+    double acc = 0.0;
+    int b = threadIdx.x;
+    for (; b + 15 * TPB < nblk; b += 16 * TPB) {
+        double v[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) v[u] = part[(int64_t)(b + u * TPB) * width + j];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) acc = is_max ? fmax(acc, v[u]) : acc + v[u];
     }
+    for (; b < nblk; b += TPB) {
+        const double v = part[(int64_t)b * width + j];
+        acc = is_max ? fmax(acc, v) : acc + v;
+    }
+    const double r = is_max ? block_max_value(acc) : block_sum_value(acc);
+    if (threadIdx.x == 0) out[j] = r;
 }
 
 // Sums of eps = n c^2 + p / (Gamma - 1) and n over the initial fields (the
@@ -1946,23 +2034,7 @@ __global__ __launch_bounds__(TPB) void k_init_state(InPtrs in, Consts K, int til
     const double eps = n * c2 + p / K.gm1;
     FeqCell fe;
     fe.setup(eps, p, gam, beta, Ep, Bv, c, K.eps0);
-    static_for<0>([&](auto ic) {
-        constexpr int i = decltype(ic)::value;
-        const double eb = EX[i] * beta[0] + EY[i] * beta[1] + EZ[i] * beta[2];
-        const double wpi = i == 0 ? K.wp[0] : (i <= 6 ? K.wp[1] : K.wp[2]);
-        st2<false, TS>(dst, f_at<TS>(K, i, pos), fe.template eq<i>() - fshift(K, i),
-                       wpi * n * gam * (1.0 + K.gc1 * eb + K.gc2 * eb * eb - K.gc3 * b2) - gshift(K, i));
-    });
-    const double cj = 1.0 / (16.0 * 1.4142135623730951 * c), ce = 1.0 / (8.0 * 1.4142135623730951 * c);
-#pragma unroll
-    for (int k = 0; k < QH; ++k) {
-        const int t = cell + nb.at(SX[k], SY[k], SZ[k]);
-        const double J0 = scr[t], J1 = scr[K.N + t], J2 = scr[2 * K.N + t];
-        const double P0 = scr[3 * K.N + t], P1 = scr[4 * K.N + t], P2 = scr[5 * K.N + t];
-        const double heq = cj * (SX[k] * J0 + SY[k] * J1 + SZ[k] * J2) + ce * (EHX[k] * P0 + EHY[k] * P1 + EHZ[k] * P2) +
-                           0.125 * (BHX[k] * in.B[0][t] + BHY[k] * in.B[1][t] + BHZ[k] * in.B[2][t]);
-        st<false, TS>(dst, h_at<TS>(K, k, pos), heq);
-    }
+    // rest value of h*, written with the rest pair in the quad layouts
     double rho;
     if (in.rho_c) {
         rho = in.rho_c[cell];
@@ -1972,43 +2044,135 @@ __global__ __launch_bounds__(TPB) void k_init_state(InPtrs in, Consts K, int til
                (in.E[1][cell + nb.at(0, 1, 0)] - in.E[1][cell + nb.at(0, -1, 0)]) +
                (in.E[2][cell + nb.at(0, 0, 1)] - in.E[2][cell + nb.at(0, 0, -1)]));
     }
-    st<false, TS>(dst, h_at<TS>(K, QH, pos), rho);
+    auto fg = [&](auto ic, double& f, double& g) {
+        constexpr int i = decltype(ic)::value;
+        const double eb = EX[i] * beta[0] + EY[i] * beta[1] + EZ[i] * beta[2];
+        const double wpi = i == 0 ? K.wp[0] : (i <= 6 ? K.wp[1] : K.wp[2]);
+        f = fe.template eq<i>() - fshift(K, i);
+        g = wpi * n * gam * (1.0 + K.gc1 * eb + K.gc2 * eb * eb - K.gc3 * b2) - gshift(K, i);
+    };
+    static_for<0>([&](auto ic) {
+        constexpr int i = decltype(ic)::value;
+        if constexpr (!quad_layout<TS>()) {
+            double f, g;
+            fg(ic, f, g);
+            st2<true, TS>(dst, f_at<TS>(K, i, pos), f, g);
+        } else if constexpr (i == 0 || (i & 1)) {  // the record half of directions i, i + 1 (or the rest quad)
+            vec4<double> v;
+            double f, g;
+            fg(ic, f, g);
+            v.x = f, v.y = g;
+            if constexpr (i == 0) {
+                v.z = rho, v.w = 0.0;
+            } else {
+                fg(std::integral_constant<int, i + 1>{}, f, g);
+                v.z = f, v.w = g;
+            }
+            st4<true, TS>(dst, f_at<TS>(K, i, pos), v);
+        }
+    });
+    const double cj = 1.0 / (16.0 * 1.4142135623730951 * c), ce = 1.0 / (8.0 * 1.4142135623730951 * c);
+    // the populations 2m and 2m + 1 go to the same cell
 #pragma unroll
-    for (int a = 0; a < 3; ++a) st<false, TE>(dst, e_at<TS>(K, a, pos), Ep[a]);
+    for (int m = 0; m < QH / 2; ++m) {
+        const int t = cell + nb.at(SX[2 * m], SY[2 * m], SZ[2 * m]);
+        const double J0 = scr[t], J1 = scr[K.N + t], J2 = scr[2 * K.N + t];
+        const double P0 = scr[3 * K.N + t], P1 = scr[4 * K.N + t], P2 = scr[5 * K.N + t];
+        const double B0 = in.B[0][t], B1 = in.B[1][t], B2 = in.B[2][t];
+        double heq[2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int k = 2 * m + j;
+            heq[j] = cj * (SX[k] * J0 + SY[k] * J1 + SZ[k] * J2) + ce * (EHX[k] * P0 + EHY[k] * P1 + EHZ[k] * P2) +
+                     0.125 * (BHX[k] * B0 + BHY[k] * B1 + BHZ[k] * B2);
+        }
+        if constexpr (quad_layout<TS>()) {
+            st2<true, TS>(dst, h_at<TS>(K, 2 * m, pos), heq[0], heq[1]);
+        } else {
+            st<true, TS>(dst, h_at<TS>(K, 2 * m, pos), heq[0]);
+            st<true, TS>(dst, h_at<TS>(K, 2 * m + 1, pos), heq[1]);
+        }
+    }
+    if constexpr (!quad_layout<TS>()) st<true, TS>(dst, h_at<TS>(K, QH, pos), rho);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) st<true, TE>(dst, e_at<TS>(K, a, pos), Ep[a]);
     if (K.bprev)
 #pragma unroll
-        for (int a = 0; a < 3; ++a) st<false, TE>(dst, e_at<TS>(K, 3 + a, pos), Bv[a]);
+        for (int a = 0; a < 3; ++a) st<true, TE>(dst, e_at<TS>(K, 3 + a, pos), Bv[a]);
 }
 
-// Raw state conversion to / from the FP64 interface layout (shifts added back).
+// Raw state conversion to / from the FP64 interface layout (shifts added
+// back): one thread per cell, which reads and writes whole records, so every
+// line of the state is touched once (with one thread per value each f-g
+// record was visited twice, and export and import of 256x256x64 cells in FP64
+// took 1.07 and 1.66 ms; so 0.80 and 0.76).
 template <typename TS, typename TE>
-__global__ void k_export(const char* __restrict__ s, double* __restrict__ d, Consts K) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= K.N * state_arrays(K)) return;
-    const int a = (int)(i / K.N), pos = (int)K.g0 + (int)(i - a * K.N);
-    if (a < OFF_G)
-        d[i] = ld<TS>(s, f_at<TS>(K, a, pos)) + fshift(K, a);
-    else if (a < OFF_H)
-        d[i] = ld<TS>(s, g_at<TS>(K, a - OFF_G, pos)) + gshift(K, a - OFF_G);
-    else if (a < OFF_E)
-        d[i] = ld<TS>(s, h_at<TS>(K, a - OFF_H, pos));
-    else
-        d[i] = ld<TE>(s, e_at<TS>(K, a - OFF_E, pos));
+__global__ __launch_bounds__(256) void k_export(const char* __restrict__ s, double* __restrict__ d, Consts K) {
+    const int64_t cell = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (cell >= K.N) return;
+    const int pos = (int)K.g0 + (int)cell;
+    auto put = [&](int a, double v) { __builtin_nontemporal_store(v, d + a * K.N + cell); };
+    auto put_fg = [&](int i, double f, double g) {
+        put(OFF_F + i, f + fshift(K, i));
+        put(OFF_G + i, g + gshift(K, i));
+    };
+    if constexpr (quad_layout<TS>()) {
+#pragma unroll
+        for (int q = 0; q < 10; ++q) {
+            const int i0 = q == 0 ? 0 : 2 * q - 1;
+            const vec4<double> v = ldv4<double, TS>(s, f_at<TS>(K, i0, pos));
+            put_fg(i0, v.x, v.y);
+            if (q == 0)
+                put(OFF_H + QH, v.z);
+            else
+                put_fg(i0 + 1, v.z, v.w);
+        }
+#pragma unroll
+        for (int k = 0; k < QH; k += 2) {
+            const vec2<double> v = ldv2<double, TS>(s, h_at<TS>(K, k, pos));
+            put(OFF_H + k, v.x);
+            put(OFF_H + k + 1, v.y);
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < Q; ++i) {
+            const vec2<double> v = ldv2<double, TS>(s, f_at<TS>(K, i, pos));
+            put_fg(i, v.x, v.y);
+        }
+#pragma unroll
+        for (int k = 0; k <= QH; ++k) put(OFF_H + k, ld<TS>(s, h_at<TS>(K, k, pos)));
+    }
+    for (int a = 0; a < state_arrays(K) - OFF_E; ++a) put(OFF_E + a, ld<TE>(s, e_at<TS>(K, a, pos)));
 }
 
 template <typename TS, typename TE>
-__global__ void k_import(const double* __restrict__ s, char* __restrict__ d, Consts K) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= K.N * state_arrays(K)) return;
-    const int a = (int)(i / K.N), pos = (int)K.g0 + (int)(i - a * K.N);
-    if (a < OFF_G)
-        st<false, TS>(d, f_at<TS>(K, a, pos), s[i] - fshift(K, a));
-    else if (a < OFF_H)
-        st<false, TS>(d, g_at<TS>(K, a - OFF_G, pos), s[i] - gshift(K, a - OFF_G));
-    else if (a < OFF_E)
-        st<false, TS>(d, h_at<TS>(K, a - OFF_H, pos), s[i]);
-    else
-        st<false, TE>(d, e_at<TS>(K, a - OFF_E, pos), s[i]);
+__global__ __launch_bounds__(256) void k_import(const double* __restrict__ s, char* __restrict__ d, Consts K) {
+    const int64_t cell = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (cell >= K.N) return;
+    const int pos = (int)K.g0 + (int)cell;
+    auto get = [&](int a) { return __builtin_nontemporal_load(s + a * K.N + cell); };
+    auto get_f = [&](int i) { return get(OFF_F + i) - fshift(K, i); };
+    auto get_g = [&](int i) { return get(OFF_G + i) - gshift(K, i); };
+    if constexpr (quad_layout<TS>()) {
+#pragma unroll
+        for (int q = 0; q < 10; ++q) {
+            const int i0 = q == 0 ? 0 : 2 * q - 1;
+            vec4<double> v;
+            v.x = get_f(i0);
+            v.y = get_g(i0);
+            v.z = q == 0 ? get(OFF_H + QH) : get_f(i0 + 1);
+            v.w = q == 0 ? 0.0 : get_g(i0 + 1);
+            st4<true, TS>(d, f_at<TS>(K, i0, pos), v);
+        }
+#pragma unroll
+        for (int k = 0; k < QH; k += 2) st2<true, TS>(d, h_at<TS>(K, k, pos), get(OFF_H + k), get(OFF_H + k + 1));
+    } else {
+#pragma unroll
+        for (int i = 0; i < Q; ++i) st2<true, TS>(d, f_at<TS>(K, i, pos), get_f(i), get_g(i));
+#pragma unroll
+        for (int k = 0; k <= QH; ++k) st<true, TS>(d, h_at<TS>(K, k, pos), get(OFF_H + k));
+    }
+    for (int a = 0; a < state_arrays(K) - OFF_E; ++a) st<true, TE>(d, e_at<TS>(K, a, pos), get(OFF_E + a));
 }
 
 // (features, targets) of sampled cells of the current state with the plain
@@ -2026,7 +2190,7 @@ __global__ __launch_bounds__(256) void k_guess_samples(const char* __restrict__ 
         const int64_t cell = (int64_t)i * K.N / ns;
         const int x = (int)(cell % K.nx), y = (int)((cell / K.nx) % K.ny), z = (int)(cell / ((int64_t)K.nx * K.ny));
         const Nbr nb = make_nbr<true>(K, x, y, z);
-        Macro M;
+        CellSol M;
         macroscopic<GUESS_NONE, TS, TE>(src, faceB, nullptr, K, (int)cell, nb, x, y, z, M);
         double Ef, S[3], Pi[6];
         fluid_tensor(K, M, M.B, Ef, S, Pi);  // the guess is not offered with the previous-B reading
@@ -2298,7 +2462,7 @@ hipError_t launch_moments(const char* src, const Consts& K, const OutPtrs& out, 
                            (const double*)D.faceB, gt, K, tx, ty, nt, out, D.scratch, D.part,
                            D.nullp);
     hipLaunchKernelGGL(k_divb, dim3(nb), dim3(TPB), 0, s, (const double*)D.scratch, K, tx, ty, nt, D.part2);
-    hipLaunchKernelGGL(k_reduce, dim3(1), dim3(TPB), 0, s, (const double*)D.part, nt, NPART, 0, D.result);
+    hipLaunchKernelGGL(k_reduce, dim3(NPART), dim3(TPB), 0, s, (const double*)D.part, nt, NPART, 0, D.result);
     hipLaunchKernelGGL(k_reduce, dim3(1), dim3(TPB), 0, s, (const double*)D.part2, nt, 1, 1, D.result + NPART);
     hipLaunchKernelGGL(k_null_reduce, dim3(1), dim3(TPB), 0, s, (const double*)D.nullp, nt,
                        (const double*)(D.scratch + 3 * K.N), (const double*)D.ez0, (const double*)D.b0,
@@ -2335,7 +2499,7 @@ hipError_t launch_ghost(const FacePtrs& in, const Consts& K, char* dst, hipStrea
 hipError_t launch_init_ref(const InPtrs& in, const Consts& K, double* part, double* result, hipStream_t s) {
     const int nblk = (int)((K.N + TPB - 1) / TPB);
     hipLaunchKernelGGL(k_init_ref, dim3(nblk), dim3(TPB), 0, s, in, K, part);
-    hipLaunchKernelGGL(k_reduce, dim3(1), dim3(TPB), 0, s, (const double*)part, nblk, 2, 0, result);
+    hipLaunchKernelGGL(k_reduce, dim3(2), dim3(TPB), 0, s, (const double*)part, nblk, 2, 0, result);
     return hipGetLastError();
 }
 #endif
@@ -2353,8 +2517,7 @@ hipError_t launch_init(const InPtrs& in, const Consts& K, double* scr, char* dst
 template <typename TS>
 hipError_t launch_export(const char* src, double* dst, const Consts& K, hipStream_t s) {
     using TE = typename StoreTypes<TS>::E;
-    const int64_t total = K.N * state_arrays(K);
-    const int64_t blocks = (total + 255) / 256;
+    const int64_t blocks = (K.N + 255) / 256;
     hipLaunchKernelGGL((k_export<TS, TE>), dim3((unsigned)blocks), dim3(256), 0, s, src, dst, K);
     return hipGetLastError();
 }
@@ -2362,8 +2525,7 @@ hipError_t launch_export(const char* src, double* dst, const Consts& K, hipStrea
 template <typename TS>
 hipError_t launch_import(const double* src, char* dst, const Consts& K, hipStream_t s) {
     using TE = typename StoreTypes<TS>::E;
-    const int64_t total = K.N * state_arrays(K);
-    const int64_t blocks = (total + 255) / 256;
+    const int64_t blocks = (K.N + 255) / 256;
     hipLaunchKernelGGL((k_import<TS, TE>), dim3((unsigned)blocks), dim3(256), 0, s, src, dst, K);
     return hipGetLastError();
 }
@@ -2376,7 +2538,7 @@ hipError_t launch_guess_samples(const char* src, const Consts& K, double* faceB,
     if (e != hipSuccess) return e;
     const int nblk = (ns + 255) / 256;
     hipLaunchKernelGGL((k_guess_samples<TS, TE>), dim3(nblk), dim3(256), 0, s, src, (const double*)faceB, K, ns, F, T, part);
-    hipLaunchKernelGGL(k_reduce, dim3(1), dim3(256), 0, s, (const double*)part, nblk, SAMPLE_SUMS, 0, result);
+    hipLaunchKernelGGL(k_reduce, dim3(SAMPLE_SUMS), dim3(256), 0, s, (const double*)part, nblk, SAMPLE_SUMS, 0, result);
     return hipGetLastError();
 }
 
