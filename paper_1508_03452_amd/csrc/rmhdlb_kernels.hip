@@ -1449,10 +1449,22 @@ __device__ __forceinline__ void quad_cell(const char* __restrict__ sd, char* __r
 // the same planes, so the y-halo meets in that XCD's L2 as well.
 // With the learned guess the network runs on whole wavefronts, so lanes past
 // a ragged edge stay and compute a copy of the edge cell without storing it.
+// The step's constants in memory that it never writes (its kernel arguments,
+// or a batch's table).  reread() hides from the compiler that they do not
+// change, so that a plane takes them anew by scalar loads: kept across the
+// walk they outgrow the scalar registers, and every spilled one costs a lane
+// move (and its wait state) where it is used.
+typedef const __attribute__((address_space(4))) Consts* ConstsPtr;
+__device__ __forceinline__ const Consts& reread(ConstsPtr kp) {
+    asm volatile("" : "+s"(kp));
+    return *(const Consts*)kp;
+}
+
 template <bool NT, typename TS, typename TE, typename V, int GM, int PXT, int VR, bool FLAT>
 __device__ __forceinline__ void fused_block(const char* __restrict__ sd, char* __restrict__ dd,
                                             const double* __restrict__ faceB, const GuessTables* __restrict__ gt,
-                                            const Consts& K, int tiles_x, int ncol, int zb, int zg, int yw, int b) {
+                                            ConstsPtr kp, int tiles_x, int ncol, int zb, int zg, int yw, int b) {
+    const Consts& K = *(const Consts*)kp;
     // pair layout (FP64): 128 cells per row group, two lanes each; quad and double-quad layouts (FP32,
     // FP16): 256 cells, one lane each
     constexpr bool ONE = quad_layout<TS>();
@@ -1497,13 +1509,14 @@ __device__ __forceinline__ void fused_block(const char* __restrict__ sd, char* _
             const bool active = xr < K.nx && yj < K.ny;
             int xp = x, yp = all_lanes ? min(yj, K.ny - 1) : yj, hp = h;
             if constexpr (opaque) asm volatile("" : "+v"(xp), "+v"(yp), "+v"(hp));
-            const int cell = xp + K.nx * (yp + K.ny * z);
-            const Nbr nb = make_nbr<true, FLAT>(K, xp, yp, z);
+            const Consts& Kp = reread(kp);
+            const int cell = xp + Kp.nx * (yp + Kp.ny * z);
+            const Nbr nb = make_nbr<true, FLAT>(Kp, xp, yp, z);
             if constexpr (ONE)
-                quad_cell<NT, TS, TE, V, GM, VR, FLAT>(sd, dd, faceB, gt, K, cell, nb, xp, yp, z,
+                quad_cell<NT, TS, TE, V, GM, VR, FLAT>(sd, dd, faceB, gt, Kp, cell, nb, xp, yp, z,
                                                  all_lanes ? active : true, bmax, gate);
             else
-                pair_cell<NT, TS, TE, V, GM, VR, FLAT>(sd, dd, faceB, gt, K, cell, nb, hp, xp, yp, z,
+                pair_cell<NT, TS, TE, V, GM, VR, FLAT>(sd, dd, faceB, gt, Kp, cell, nb, hp, xp, yp, z,
                                                  all_lanes ? active : true, bmax, gate);
         }
     }
@@ -1515,6 +1528,8 @@ __device__ __forceinline__ void fused_block(const char* __restrict__ sd, char* _
     }
 }
 
+constexpr int STEP_CONSTS_AT = 4 * sizeof(void*);  // K among k_fused_step's arguments: after four pointers
+static_assert(alignof(Consts) == sizeof(void*), "K follows the pointers without padding");
 template <bool NT, typename TS, typename TE, typename V, int GM, int PXT, int VR, bool FLAT>
 __global__ __launch_bounds__(PTPB, FUSED_WAVES) void k_fused_step(const char* __restrict__ sd,
                                                         char* __restrict__ dd, const double* __restrict__ faceB,
@@ -1531,7 +1546,9 @@ __global__ __launch_bounds__(PTPB, FUSED_WAVES) void k_fused_step(const char* __
         if (*K.gflag_rd != K.gstep - 1) return;
         if (blockIdx.x == 0 && threadIdx.x == 0 && K.gcount) *K.gcount += 1;  // one writer per step
     }
-    fused_block<NT, TS, TE, V, GM, PXT, VR, FLAT>(sd, dd, faceB, gt, K, tiles_x, ncol, zb, zg, yw, b);
+    const ConstsPtr kp = (ConstsPtr)((const __attribute__((address_space(4))) char*)__builtin_amdgcn_kernarg_segment_ptr() +
+                                     STEP_CONSTS_AT);
+    fused_block<NT, TS, TE, V, GM, PXT, VR, FLAT>(sd, dd, faceB, gt, kp, tiles_x, ncol, zb, zg, yw, b);
 }
 
 // Index of the instance whose range [first[i], first[i + 1]) holds v (first
@@ -1563,7 +1580,7 @@ __global__ __launch_bounds__(PTPB, WV) void k_fused_batch(const BatchInst* __res
     const int i = find_instance(ninst, b, [&](int j) { return I[j].blk0; });
     const BatchInst& B = I[i];
     fused_block<NT, TS, TE, V, GUESS_NONE, PXT, 0, FLAT>(
-        B.buf[parity], B.buf[1 - parity], B.faceB, nullptr, B.K, B.tiles_x, B.ncol, B.zb, 1, B.yw, (int)(b - B.blk0));
+        B.buf[parity], B.buf[1 - parity], B.faceB, nullptr, (ConstsPtr)(uintptr_t)&B.K, B.tiles_x, B.ncol, B.zb, 1, B.yw, (int)(b - B.blk0));
 }
 
 // B of Eq. Cal_B at a cell from the streamed h (population order, FP64).
@@ -1679,7 +1696,7 @@ __global__ __launch_bounds__(PTPB, WV) void k_fused_batch_persistent(const Batch
                 const int i = find_instance(ninst, b, [&](int jj) { return I[jj].blk0; });
                 const BatchInst& B = I[i];
                 fused_block<NT, TS, TE, V, GUESS_NONE, PXT, 0, FLAT>(
-                    B.buf[parity], B.buf[1 - parity], B.faceB, nullptr, B.K, B.tiles_x, B.ncol, B.zb, 1, B.yw,
+                    B.buf[parity], B.buf[1 - parity], B.faceB, nullptr, (ConstsPtr)(uintptr_t)&B.K, B.tiles_x, B.ncol, B.zb, 1, B.yw,
                     (int)(b - B.blk0));
             }
             if (threadIdx.x == 0) tile_sh = nj;
