@@ -193,20 +193,32 @@ hipError_t launch_ghost(const FacePtrs& in, const Consts& K, char* dst, hipStrea
 hipError_t launch_init_ref(const InPtrs& in, const Consts& K, double* part, double* result, hipStream_t s);
 template <typename TS>
 hipError_t launch_face_b(const char* src, const Consts& K, double* faceB, hipStream_t s);
-// Launch geometry of the fused step for a tile width px, zb planes per block
-// and zg blocks per column and chunk of zg * zb planes: tiles along x,
-// columns, blocks.
-void step_geometry(const Consts& K, int px, int zb, int zg, int yw, int cpb, int& tiles_x, int& ncol, int& nblk);
-// Cells per row group of a fused-step block: 128 in the pair layout (FP64 storage, two lanes per cell),
-// 256 in the quad and double-quad layouts (FP32 and FP16 storage, one lane per cell).
-inline int cells_per_block(bool quad) { return quad ? 256 : 128; }
-inline bool quad_storage(int32_t storage) { return storage != RMHDLB_STORE_F64; }
 // Whether the step takes the kernels for a single z-plane: there every
 // z-displacement of the stencil leads back to the cell itself (periodic or
 // open z; a driven face has planes below it), and 54 of a cell's 168 reads of
 // f fall on points already read.  ms per step, general -> flat: KH slab
 // 1024 x 2048 FP64 0.581 -> 0.541, sweep of 25.2 M cells FP32 4.19 -> 3.60.
 inline bool flat_grid(const Consts& K) { return K.nz == 1 && !K.drv; }
+// Cells per row group of a fused-step block: 128 in the pair layout (FP64 storage, elem = 8 bytes, two lanes
+// per cell), 256 in the quad and double-quad layouts (FP32 and FP16 storage, one lane per cell).
+__host__ __device__ constexpr int cells_per_block(int elem) { return elem == 8 ? 128 : 256; }
+// z-planes of a fused-step tile: two in FP64 and FP32 where the rows suffice
+// (at least four), so that half of the z-neighbour planes of the stencil are
+// the tile's own: 56 instead of 68 lines of L1 per 128 cells and direction
+// (FP64 at px = 32), ms per step at 256x256x512 one / two planes FP64 9.9 / 9.36, FP32
+// 4.9 / 4.75 (wavefronts in step).  FP16 is 1 % faster with one plane.
+__host__ __device__ constexpr int tile_planes(int elem, int px, bool flat) {
+    return flat || elem == 2 || cells_per_block(elem) / px < 4 ? 1 : 2;
+}
+// Launch geometry of the fused step for a tile width px, zb planes per block
+// and zg blocks per column and chunk of zg * zb planes: tiles along x,
+// columns, blocks.
+void step_geometry(const Consts& K, int px, int zb, int zg, int yw, int elem, bool flat, int& tiles_x, int& ncol,
+                   int& nblk);
+inline bool quad_storage(int32_t storage) { return storage != RMHDLB_STORE_F64; }
+inline int storage_bytes(int32_t storage) {
+    return storage == RMHDLB_STORE_F64 ? 8 : (storage == RMHDLB_STORE_F32 ? 4 : 2);
+}
 // One batched step (face pass of the instances that need it, then the fused
 // step of all) reading buffer `parity` of every instance; px the tile width
 // (128, 64, 32, 16), waves the occupancy variant (FP32: 2 or 3); flat: every

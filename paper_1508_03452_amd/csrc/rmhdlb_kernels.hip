@@ -770,7 +770,7 @@ __device__ __forceinline__ V pair_sum(V v) {
 // R4); bit 1 the limited Lax-Wendroff face values (else MUSCL, Reading R2);
 // bit 2 the external force; bit 3 the previous step's B in the recovery and
 // f_eq (else this step's, Reading R10), carried in the state.
-template <bool NT, typename TS, typename TE, typename V, int GM, int VR, bool FLAT>
+template <bool NT, typename TS, typename TE, typename V, int GM, int VR, bool FLAT, bool SYNC>
 __device__ __forceinline__ void pair_cell(const char* __restrict__ sd, char* __restrict__ dd,
                                           const double* __restrict__ faceB, const GuessTables* __restrict__ gt,
                                           const Consts& K, int cell, const Nbr& nb, int h, int x, int y, int z,
@@ -851,6 +851,7 @@ __device__ __forceinline__ void pair_cell(const char* __restrict__ sd, char* __r
             constexpr int i0 = 2 * s - 1;
             constexpr int ex = EX[i0], ey = EY[i0], ez = EZ[i0];
             using K_ = Link<s, FLAT>;
+            if constexpr (SYNC) __builtin_amdgcn_s_barrier();
             // the next slot's loads (after the last slot, the Maxwell populations') are in flight while this
             // slot's arrive and are used
             if constexpr (s < 9)
@@ -1067,7 +1068,7 @@ __device__ __forceinline__ void st8(char* __restrict__ d, int64_t o, const vec4<
 // of the cell they stream from.  The arithmetic per direction is that of
 // pair_cell (the readings it implements are listed there); only the
 // assignment of work to lanes and the order of the moment sums differ.
-template <bool NT, typename TS, typename TE, typename V, int GM, int VR, bool FLAT>
+template <bool NT, typename TS, typename TE, typename V, int GM, int VR, bool FLAT, bool SYNC>
 __device__ __forceinline__ void quad_cell(const char* __restrict__ sd, char* __restrict__ dd,
                                           const double* __restrict__ faceB, const GuessTables* __restrict__ gt,
                                           const Consts& K, int cell, const Nbr& nb, int x, int y, int z, bool active,
@@ -1222,6 +1223,7 @@ __device__ __forceinline__ void quad_cell(const char* __restrict__ sd, char* __r
     static_for<0>([&](auto rc) {
         constexpr int r = decltype(rc)::value;
         if constexpr (r < RECS) {
+            if constexpr (SYNC && r % 2 == 0) __builtin_amdgcn_s_barrier();
             if constexpr (r + 1 < RECS)
                 issue(std::integral_constant<int, r + 1>{}, raw[(r + 1) & 1]);
             else
@@ -1436,19 +1438,20 @@ __device__ __forceinline__ void quad_cell(const char* __restrict__ sd, char* __r
 
 // ------------------------------------------------------------------ kernels
 
-// One block owns a PXT x (128 / PXT) group of rows of cells (two lanes per
-// cell), yw such groups stacked along y (a tile of PXT x (128 / PXT) yw
-// cells), and walks zb z-planes, the yw groups of a plane one after another.  A chunk of zg * zb planes is shared by zg blocks
-// per column: block r of the zg takes planes r, r + zg, r + 2 zg, ... of the
-// chunk, so that the zg blocks of a column run at neighbouring planes at the
-// same time and the z-neighbour planes of the stencil are fetched once into
-// L2 for all of them (zg = 1: one block walks zb consecutive planes).  Blocks
-// are numbered column-fastest within a chunk, the zg blocks of a column next
-// to each other, and XCD k receives the contiguous block range [k P, (k + 1) P):
-// the columns one XCD runs at the same time are neighbours marching through
-// the same planes, so the y-halo meets in that XCD's L2 as well.
-// With the learned guess the network runs on whole wavefronts, so lanes past
-// a ragged edge stay and compute a copy of the edge cell without storing it.
+// Whether the wavefronts of a block keep in step through the slots (a barrier
+// per slot in FP64, per two in FP32).  What bounds the three-dimensional step
+// in these forms is the lines that a CU's L1 has under way to L2 (about 70 of
+// 128 bytes, at 700 cycles each): in step, the wavefronts of a tile find each
+// other's rows and planes in L1.  256x256x512 with tiles of two planes, ms per
+// step free / in step: FP64 10.0 / 9.36, FP32 5.0 / 4.75; FP16, which is bound
+// by arithmetic, 3.42 / 3.48, and slabs lose 2-4 %.  A wavefront that has no
+// rows left ends, and the barrier then waits for the others only.  Not in the
+// persistent kernel, whose blocks meet at barriers of their own.
+template <typename TS, bool FLAT>
+constexpr bool in_step() {
+    return !FLAT && sizeof(TS) >= 4;
+}
+
 // The step's constants in memory that it never writes (its kernel arguments,
 // or a batch's table).  reread() hides from the compiler that they do not
 // change, so that a plane takes them anew by scalar loads: kept across the
@@ -1460,7 +1463,22 @@ __device__ __forceinline__ const Consts& reread(ConstsPtr kp) {
     return *(const Consts*)kp;
 }
 
-template <bool NT, typename TS, typename TE, typename V, int GM, int PXT, int VR, bool FLAT>
+// One block owns a row group of 128 (FP64, two lanes per cell) or 256 cells:
+// ROWS = 128 / PXT or 256 / PXT rows of PXT cells, PYT of them along y in each
+// of ZT neighbouring planes (tile_planes), yw such groups stacked along y.  It
+// walks zb z-planes, the yw groups of its planes one after another.  A chunk
+// of zg * zb planes is shared by zg blocks per column, which take its planes
+// (ZT at a time) in turn, so that the zg blocks of a column run at
+// neighbouring planes at the same time and the z-neighbour planes of the
+// stencil are fetched once into L2 for all of them (zg = 1: one block walks zb
+// consecutive planes).  Blocks are numbered column-fastest within a chunk, the
+// zg blocks of a column next to each other, and XCD k receives the contiguous
+// block range [k P, (k + 1) P): the columns one XCD runs at the same time are
+// neighbours marching through the same planes, so the y-halo meets in that
+// XCD's L2 as well.
+// With the learned guess the network runs on whole wavefronts, so lanes past
+// a ragged edge stay and compute a copy of the edge cell without storing it.
+template <bool NT, typename TS, typename TE, typename V, int GM, int PXT, int VR, bool FLAT, bool SYNC>
 __device__ __forceinline__ void fused_block(const char* __restrict__ sd, char* __restrict__ dd,
                                             const double* __restrict__ faceB, const GuessTables* __restrict__ gt,
                                             ConstsPtr kp, int tiles_x, int ncol, int zb, int zg, int yw, int b) {
@@ -1468,7 +1486,7 @@ __device__ __forceinline__ void fused_block(const char* __restrict__ sd, char* _
     // pair layout (FP64): 128 cells per row group, two lanes each; quad and double-quad layouts (FP32,
     // FP16): 256 cells, one lane each
     constexpr bool ONE = quad_layout<TS>();
-    constexpr int PYT = (ONE ? 256 : 128) / PXT;
+    constexpr int ROWS = cells_per_block(sizeof(TS)) / PXT, ZT = tile_planes(sizeof(TS), PXT, FLAT), PYT = ROWS / ZT;
     const int per = ncol * zg, zc = b / per, r = b % per;
     const int col = r / zg, zoff = r % zg;
     const int tx = col % tiles_x, ty = col / tiles_x;
@@ -1478,7 +1496,9 @@ __device__ __forceinline__ void fused_block(const char* __restrict__ sd, char* _
     const int c = ONE ? (int)threadIdx.x : (int)(threadIdx.x >> 6) * 32 + (lane & 31), h = ONE ? 0 : lane >> 5;
     const int xr = tx * PXT + (c % PXT);
     int x = xr;
-    const int ybase = ty * PYT * yw + c / PXT;
+    const int ybase = ty * PYT * yw + c / PXT % PYT;
+    // plane of the tile this wavefront works on (its rows share it)
+    const int zl = ZT == 1 ? 0 : __builtin_amdgcn_readfirstlane(c / PXT / PYT);
     // with the force every lane stays (the wavefront's largest |beta| is
     // reduced over all 64 lanes)
     constexpr bool all_lanes = GM == GUESS_PAIR || GM == GUESS_SINGLE || (VR & 4) != 0;
@@ -1503,20 +1523,24 @@ __device__ __forceinline__ void fused_block(const char* __restrict__ sd, char* _
     // slower).
     constexpr bool opaque = sizeof(TS) != 4;
     const int groups = all_lanes ? yw : ng;
-    for (int z = z0 + zoff; z < z1; z += zg) {
+    for (int zp = z0 + zoff * ZT; zp < z1; zp += zg * ZT) {
+        // the last planes of a chunk may be fewer than the tile's
+        const bool inside = zp + zl < z1;
+        if (!all_lanes && !inside) break;
+        const int z = all_lanes ? min(zp + zl, z1 - 1) : zp + zl;
         for (int j = 0; j < groups; ++j) {
             const int yj = ybase + j * PYT;
-            const bool active = xr < K.nx && yj < K.ny;
+            const bool active = xr < K.nx && yj < K.ny && inside;
             int xp = x, yp = all_lanes ? min(yj, K.ny - 1) : yj, hp = h;
             if constexpr (opaque) asm volatile("" : "+v"(xp), "+v"(yp), "+v"(hp));
             const Consts& Kp = reread(kp);
             const int cell = xp + Kp.nx * (yp + Kp.ny * z);
             const Nbr nb = make_nbr<true, FLAT>(Kp, xp, yp, z);
             if constexpr (ONE)
-                quad_cell<NT, TS, TE, V, GM, VR, FLAT>(sd, dd, faceB, gt, Kp, cell, nb, xp, yp, z,
+                quad_cell<NT, TS, TE, V, GM, VR, FLAT, SYNC>(sd, dd, faceB, gt, Kp, cell, nb, xp, yp, z,
                                                  all_lanes ? active : true, bmax, gate);
             else
-                pair_cell<NT, TS, TE, V, GM, VR, FLAT>(sd, dd, faceB, gt, Kp, cell, nb, hp, xp, yp, z,
+                pair_cell<NT, TS, TE, V, GM, VR, FLAT, SYNC>(sd, dd, faceB, gt, Kp, cell, nb, hp, xp, yp, z,
                                                  all_lanes ? active : true, bmax, gate);
         }
     }
@@ -1548,7 +1572,7 @@ __global__ __launch_bounds__(PTPB, FUSED_WAVES) void k_fused_step(const char* __
     }
     const ConstsPtr kp = (ConstsPtr)((const __attribute__((address_space(4))) char*)__builtin_amdgcn_kernarg_segment_ptr() +
                                      STEP_CONSTS_AT);
-    fused_block<NT, TS, TE, V, GM, PXT, VR, FLAT>(sd, dd, faceB, gt, kp, tiles_x, ncol, zb, zg, yw, b);
+    fused_block<NT, TS, TE, V, GM, PXT, VR, FLAT, in_step<TS, FLAT>()>(sd, dd, faceB, gt, kp, tiles_x, ncol, zb, zg, yw, b);
 }
 
 // Index of the instance whose range [first[i], first[i + 1]) holds v (first
@@ -1579,7 +1603,7 @@ __global__ __launch_bounds__(PTPB, WV) void k_fused_batch(const BatchInst* __res
     if (b >= total) return;
     const int i = find_instance(ninst, b, [&](int j) { return I[j].blk0; });
     const BatchInst& B = I[i];
-    fused_block<NT, TS, TE, V, GUESS_NONE, PXT, 0, FLAT>(
+    fused_block<NT, TS, TE, V, GUESS_NONE, PXT, 0, FLAT, in_step<TS, FLAT>()>(
         B.buf[parity], B.buf[1 - parity], B.faceB, nullptr, (ConstsPtr)(uintptr_t)&B.K, B.tiles_x, B.ncol, B.zb, 1, B.yw, (int)(b - B.blk0));
 }
 
@@ -1695,7 +1719,7 @@ __global__ __launch_bounds__(PTPB, WV) void k_fused_batch_persistent(const Batch
             if (b < total) {
                 const int i = find_instance(ninst, b, [&](int jj) { return I[jj].blk0; });
                 const BatchInst& B = I[i];
-                fused_block<NT, TS, TE, V, GUESS_NONE, PXT, 0, FLAT>(
+                fused_block<NT, TS, TE, V, GUESS_NONE, PXT, 0, FLAT, false>(
                     B.buf[parity], B.buf[1 - parity], B.faceB, nullptr, (ConstsPtr)(uintptr_t)&B.K, B.tiles_x, B.ncol, B.zb, 1, B.yw,
                     (int)(b - B.blk0));
             }
@@ -2289,8 +2313,9 @@ hipError_t launch_face_b(const char* src, const Consts& K, double* faceB, hipStr
 }
 
 #if RMHDLB_FORM == 64  // what depends on no storage form is built once
-void step_geometry(const Consts& K, int px, int zb, int zg, int yw, int cpb, int& tiles_x, int& ncol, int& nblk) {
-    const int py = cpb / px * yw;
+void step_geometry(const Consts& K, int px, int zb, int zg, int yw, int elem, bool flat, int& tiles_x, int& ncol,
+                   int& nblk) {
+    const int py = cells_per_block(elem) / px / tile_planes(elem, px, flat) * yw;
     tiles_x = (K.nx + px - 1) / px;
     ncol = tiles_x * ((K.ny + py - 1) / py);
     nblk = ncol * zg * ((K.nz + zg * zb - 1) / (zg * zb));
@@ -2302,7 +2327,7 @@ static void launch_fused(const char* sd, char* dd, double* faceB, const GuessTab
     using TE = typename StoreTypes<TS>::E;
     using V = typename StoreTypes<TS>::V;
     int tx, ncol, nblk;
-    step_geometry(K, PXT, zb, zg, yw, cells_per_block(quad_layout<TS>()), tx, ncol, nblk);
+    step_geometry(K, PXT, zb, zg, yw, sizeof(TS), flat_grid(K), tx, ncol, nblk);
     const int grid = ((nblk + 7) / 8) * 8;
     if (flat_grid(K))
         hipLaunchKernelGGL((k_fused_step<true, TS, TE, V, GM, PXT, VR, true>), dim3(grid), dim3(PTPB), 0, s, sd, dd,
@@ -2333,7 +2358,7 @@ hipError_t launch_step(const char* src, char* dst, const Consts& K, const StepTu
         else
             launch_fused<TS, GUESS_NONE, 64, 4>(src, dst, faceB, gt, K, zb, 1, 1, s);
         int tx, ncol, nblk;
-        step_geometry(K, 64, zb, 1, 1, cells_per_block(quad_layout<TS>()), tx, ncol, nblk);
+        step_geometry(K, 64, zb, 1, 1, sizeof(TS), flat_grid(K), tx, ncol, nblk);
         hipLaunchKernelGGL(k_vmax_reduce, dim3(1), dim3(TPB), 0, s, K.vmax_part, (int64_t)nblk * (PTPB / 64),
                            const_cast<double*>(K.vmax_prev));
     } else if (vr) {  // the alternative readings: 64-wide tiles, no guess
