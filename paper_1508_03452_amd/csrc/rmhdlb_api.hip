@@ -428,13 +428,9 @@ int rmhdlb_init_fields(rmhdlb_ctx* C, const rmhdlb_fields_in* in) {
     } else {
         set_shifts(C->K, C->storage, 0.0, 0.0);
     }
-    hipError_t e = RMHD_DISPATCH(C, launch_init)(ip, C->K, C->scratch, C->buf[0], C->stream);
+    // also the references of the reconnection rate: E^z_0 and B0 = max |B|
+    hipError_t e = RMHD_DISPATCH(C, launch_init)(ip, C->K, C->scratch, C->buf[0], C->ez0, C->part2, C->aux, C->stream);
     if (e != hipSuccess) return RMHDLB_EDEVICE;
-    // references of the reconnection rate: E^z_0 and B0 = max |B|
-    if (hipMemcpyAsync(C->ez0, in->E[2], sizeof(double) * (size_t)C->K.N, hipMemcpyDeviceToDevice, C->stream) !=
-            hipSuccess ||
-        rmhd::launch_init_bmax(ip, C->K, C->part2, C->aux, C->stream) != hipSuccess)
-        return RMHDLB_EDEVICE;
     // a driven face starts from the fields of the first interior plane
     if (C->K.drv) {
         rmhd::FacePtrs fp;

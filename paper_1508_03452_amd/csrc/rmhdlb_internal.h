@@ -186,7 +186,6 @@ hipError_t launch_step(const char* src, char* dst, const Consts& K, const StepTu
 template <typename TS>
 hipError_t launch_moments(const char* src, const Consts& K, const OutPtrs& out, const DiagBufs& D,
                           const GuessTables* gt, hipStream_t s);
-hipError_t launch_init_bmax(const InPtrs& in, const Consts& K, double* part, double* b0, hipStream_t s);
 hipError_t launch_face_check(const FacePtrs& in, const Consts& K, double* part, double* result, hipStream_t s);
 template <typename TS>
 hipError_t launch_ghost(const FacePtrs& in, const Consts& K, char* dst, hipStream_t s);
@@ -239,8 +238,11 @@ hipError_t launch_guess_samples(const char* src, const Consts& K, double* faceB,
 hipError_t launch_guess_normalise(const double* F, const double* T, int ns, const Norm4& nm, float* X, float* Y,
                                   hipStream_t s);
 hipError_t launch_train(const TrainArgs& A, hipStream_t s);
+// Initial state from the fields in, with the references of the reconnection
+// rate: E^z_0 into ez0 and max |B| into b0 (part: one value per tile).
 template <typename TS>
-hipError_t launch_init(const InPtrs& in, const Consts& K, double* scr, char* dst, hipStream_t s);
+hipError_t launch_init(const InPtrs& in, const Consts& K, double* scr, char* dst, double* ez0, double* part,
+                       double* b0, hipStream_t s);
 // Plain copy of n16 16-byte words (the HBM reference rate).
 hipError_t launch_copy16(const void* src, void* dst, int64_t n16, hipStream_t s);
 template <typename TS>

@@ -41,7 +41,9 @@ __device__ __forceinline__ double ld(const char* __restrict__ s, int64_t o) {
 
 // Loads of values that no other cell of the step reads (each streamed h* is
 // pulled by exactly one cell): the non-temporal hint keeps them from
-// evicting the stencil lines that the neighbours' loads will hit.
+// evicting the stencil lines that the neighbours' loads will hit (256x256x256,
+// ms per step without / with: FP64 4.74 / 4.69, FP32 2.40 / 2.38, FP16 1.677 /
+// 1.663).
 template <typename V, typename T>
 __device__ __forceinline__ V ldv_once(const char* __restrict__ s, int64_t o) {
     return static_cast<V>(__builtin_nontemporal_load(reinterpret_cast<const T*>(s + o)));
@@ -1212,8 +1214,8 @@ __device__ __forceinline__ void quad_cell(const char* __restrict__ sd, char* __r
 #pragma unroll
         for (int m = 0; m < 12; ++m) {
             const int k0 = 2 * m;
-            hraw[m] = *reinterpret_cast<const HRaw*>(sd + L::H + CHUNK * L::HREC * m +
-                                                     lane_off<L::HREC>(K, pos + nb.at(-SX[k0], -SY[k0], -SZ[k0])));
+            hraw[m] = __builtin_nontemporal_load(reinterpret_cast<const HRaw*>(
+                sd + L::H + CHUNK * L::HREC * m + lane_off<L::HREC>(K, pos + nb.at(-SX[k0], -SY[k0], -SZ[k0]))));
         }
     };
     Rec rest_raw = {0, 0, 0, 0};
@@ -1514,14 +1516,9 @@ __device__ __forceinline__ void fused_block(const char* __restrict__ sd, char* _
     const int z0 = zc * zb * zg, z1 = min(K.nz, z0 + zb * zg);
     double bmax = 0.0;
     bool gate = false;  // a cell of the walk lay above the guess's gate (uniform over the wavefront)
-    // In FP64 and FP16 the lane's coordinates are made opaque at every plane,
-    // so that the x- and y-parts of the neighbour table are recomputed per
-    // plane (a few integer operations) instead of being kept across the walk:
-    // in FP64, whose cell code is at the register limit, that took 7 scratch
-    // reloads per plane out of the loop; in FP16 (double-quad layout) it is
-    // 0.4-1.2 % faster.  FP32 keeps them (recomputing them there measured 6 %
-    // slower).
-    constexpr bool opaque = sizeof(TS) != 4;
+    // The lane's coordinates are made opaque at every plane, so that the x- and
+    // y-parts of the neighbour table are recomputed per plane (a few integer
+    // operations) instead of being kept across the walk (FP16 1 % slower then).
     const int groups = all_lanes ? yw : ng;
     for (int zp = z0 + zoff * ZT; zp < z1; zp += zg * ZT) {
         // the last planes of a chunk may be fewer than the tile's
@@ -1532,7 +1529,7 @@ __device__ __forceinline__ void fused_block(const char* __restrict__ sd, char* _
             const int yj = ybase + j * PYT;
             const bool active = xr < K.nx && yj < K.ny && inside;
             int xp = x, yp = all_lanes ? min(yj, K.ny - 1) : yj, hp = h;
-            if constexpr (opaque) asm volatile("" : "+v"(xp), "+v"(yp), "+v"(hp));
+            asm volatile("" : "+v"(xp), "+v"(yp), "+v"(hp));
             const Consts& Kp = reread(kp);
             const int cell = xp + Kp.nx * (yp + Kp.ny * z);
             const Nbr nb = make_nbr<true, FLAT>(Kp, xp, yp, z);
@@ -1863,7 +1860,15 @@ __global__ __launch_bounds__(TPB, 2) void k_moments(const char* __restrict__ src
                                                      const double* __restrict__ b0, double* __restrict__ out) {
     __shared__ double res[2];
     double k = __builtin_inf(), i = NO_INDEX;
-    for (int b = threadIdx.x; b < nblk; b += TPB) argmin_merge(k, i, nullp[2 * (int64_t)b], nullp[2 * (int64_t)b + 1]);
+    int b = threadIdx.x;
+    for (; b + 7 * TPB < nblk; b += 8 * TPB) {  // 8 candidates of a thread in flight
+        vec2<double> v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const vec2<double>*>(nullp + 2 * (int64_t)(b + u * TPB));
+#pragma unroll
+        for (int u = 0; u < 8; ++u) argmin_merge(k, i, v[u].x, v[u].y);
+    }
+    for (; b < nblk; b += TPB) argmin_merge(k, i, nullp[2 * (int64_t)b], nullp[2 * (int64_t)b + 1]);
     block_argmin(k, i, res);
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -1880,7 +1885,18 @@ __global__ __launch_bounds__(TPB, 2) void k_moments(const char* __restrict__ src
 // cleared for the next step); one block.
 [[maybe_unused]] static __global__ __launch_bounds__(TPB) void k_vmax_reduce(double* __restrict__ part, int64_t n, double* __restrict__ out) {
     double m = 0.0;
-    for (int64_t i = threadIdx.x; i < n; i += TPB) {
+    int64_t i = threadIdx.x;
+    for (; i + 15 * TPB < n; i += 16 * TPB) {  // 16 partials of a thread in flight
+        double v[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) v[u] = part[i + u * TPB];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) {
+            m = fmax(m, v[u]);
+            part[i + u * TPB] = 0.0;
+        }
+    }
+    for (; i < n; i += TPB) {
         m = fmax(m, part[i]);
         part[i] = 0.0;
     }
@@ -1913,7 +1929,7 @@ __global__ __launch_bounds__(TPB, 2) void k_moments(const char* __restrict__ src
         acc = is_max ? fmax(acc, v) : acc + v;
     }
     const double r = is_max ? block_max_value(acc) : block_sum_value(acc);
-    if (threadIdx.x == 0) out[j] = r;
+    if (threadIdx.x == 0) out[j] = is_max == 2 ? sqrt(r) : r;
 }
 
 // Sums of eps = n c^2 + p / (Gamma - 1) and n over the initial fields (the
@@ -1926,18 +1942,6 @@ __global__ __launch_bounds__(TPB, 2) void k_moments(const char* __restrict__ src
         v[1] = in.n[i];
     }
     block_sum<2>(v, part + (int64_t)blockIdx.x * 2);
-}
-
-// Largest B^2 of the initial fields (as fma(B_x, B_x, fma(B_y, B_y, B_z B_z))), per block.
-[[maybe_unused]] static __global__ __launch_bounds__(TPB) void k_init_bmax(InPtrs in, Consts K, double* __restrict__ part) {
-    const int64_t i = (int64_t)blockIdx.x * TPB + threadIdx.x;
-    double v = 0.0;
-    if (i < K.N) v = fma(in.B[0][i], in.B[0][i], fma(in.B[1][i], in.B[1][i], in.B[2][i] * in.B[2][i]));
-    block_max1(v, part + blockIdx.x);
-}
-
-[[maybe_unused]] static __global__ void k_sqrt1(double* __restrict__ v) {
-    if (threadIdx.x == 0) v[0] = sqrt(v[0]);
 }
 
 // Face cells with |u| >= c, n <= 0 or p < 0, per block.
@@ -2013,37 +2017,45 @@ __global__ __launch_bounds__(TPB) void k_init_ghost(FacePtrs in, Consts K, char*
 
 // Initial state, pass 1: J0 from Eq. Ohm with the Gauss charge of E0, and
 // E'0 = E0 + (dt/2) mu0 c^2 J0 (Reading of the initial h), into scratch.
+// Also the references of the reconnection rate: E^z_0, and the largest B^2 per
+// tile (as fma(B_x, B_x, fma(B_y, B_y, B_z B_z))).
 [[maybe_unused]] static __global__ __launch_bounds__(TPB) void k_init_current(InPtrs in, Consts K, int tiles_x, int tiles_y, int ntiles,
-                                                      double* __restrict__ scr) {
+                                                      double* __restrict__ scr, double* __restrict__ ez0,
+                                                      double* __restrict__ part) {
     const int tile = tile_of_block(ntiles);
     if (tile >= ntiles) return;
     const int tx = tile % tiles_x, rest = tile / tiles_x;
     const int ty = rest % tiles_y, z = rest / tiles_y;
     const int x = tx * TX + (threadIdx.x % TX), y = ty * TY + (threadIdx.x / TX);
-    if (x >= K.nx || y >= K.ny) return;
-    const int cell = x + K.nx * (y + K.ny * z);
-    const Nbr nb = make_nbr<false>(K, x, y, z);
-    const double c = K.c, c2 = c * c;
-    double u[3], E[3], B[3];
+    double b2max = 0.0;
+    if (x < K.nx && y < K.ny) {
+        const int cell = x + K.nx * (y + K.ny * z);
+        const Nbr nb = make_nbr<false>(K, x, y, z);
+        const double c = K.c, c2 = c * c;
+        double u[3], E[3], B[3];
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        u[a] = in.u[a][cell];
-        E[a] = in.E[a][cell];
-        B[a] = in.B[a][cell];
-    }
-    const double rg = K.eps0 * K.inv_2dx *
-                      ((in.E[0][cell + nb.at(1, 0, 0)] - in.E[0][cell + nb.at(-1, 0, 0)]) +
-                       (in.E[1][cell + nb.at(0, 1, 0)] - in.E[1][cell + nb.at(0, -1, 0)]) +
-                       (in.E[2][cell + nb.at(0, 0, 1)] - in.E[2][cell + nb.at(0, 0, -1)]));
-    const double gam = 1.0 / sqrt(1.0 - (u[0] * u[0] + u[1] * u[1] + u[2] * u[2]) / c2);
-    const double uxB[3] = {u[1] * B[2] - u[2] * B[1], u[2] * B[0] - u[0] * B[2], u[0] * B[1] - u[1] * B[0]};
-    const double Eu = (E[0] * u[0] + E[1] * u[1] + E[2] * u[2]) / c2;
+        for (int a = 0; a < 3; ++a) {
+            u[a] = in.u[a][cell];
+            E[a] = in.E[a][cell];
+            B[a] = in.B[a][cell];
+        }
+        const double rg = K.eps0 * K.inv_2dx *
+                          ((in.E[0][cell + nb.at(1, 0, 0)] - in.E[0][cell + nb.at(-1, 0, 0)]) +
+                           (in.E[1][cell + nb.at(0, 1, 0)] - in.E[1][cell + nb.at(0, -1, 0)]) +
+                           (in.E[2][cell + nb.at(0, 0, 1)] - in.E[2][cell + nb.at(0, 0, -1)]));
+        const double gam = 1.0 / sqrt(1.0 - (u[0] * u[0] + u[1] * u[1] + u[2] * u[2]) / c2);
+        const double uxB[3] = {u[1] * B[2] - u[2] * B[1], u[2] * B[0] - u[0] * B[2], u[0] * B[1] - u[1] * B[0]};
+        const double Eu = (E[0] * u[0] + E[1] * u[1] + E[2] * u[2]) / c2;
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        const double J = K.sigma * gam * (E[a] + uxB[a] - Eu * u[a]) + rg * u[a];
-        scr[(int64_t)a * K.N + cell] = J;
-        scr[(int64_t)(3 + a) * K.N + cell] = E[a] + K.q * J;
+        for (int a = 0; a < 3; ++a) {
+            const double J = K.sigma * gam * (E[a] + uxB[a] - Eu * u[a]) + rg * u[a];
+            scr[(int64_t)a * K.N + cell] = J;
+            scr[(int64_t)(3 + a) * K.N + cell] = E[a] + K.q * J;
+        }
+        ez0[cell] = E[2];
+        b2max = fma(B[0], B[0], fma(B[1], B[1], B[2] * B[2]));
     }
+    block_max1(b2max, part + tile);
 }
 
 // Initial state, pass 2: f* = f_eq, g* = g_eq (stored minus their shifts),
@@ -2513,14 +2525,6 @@ hipError_t launch_moments(const char* src, const Consts& K, const OutPtrs& out, 
 }
 
 #if RMHDLB_FORM == 64  // what depends on no storage form is built once
-hipError_t launch_init_bmax(const InPtrs& in, const Consts& K, double* part, double* b0, hipStream_t s) {
-    const int nblk = (int)((K.N + TPB - 1) / TPB);
-    hipLaunchKernelGGL(k_init_bmax, dim3(nblk), dim3(TPB), 0, s, in, K, part);
-    hipLaunchKernelGGL(k_reduce, dim3(1), dim3(TPB), 0, s, (const double*)part, nblk, 1, 1, b0);
-    hipLaunchKernelGGL(k_sqrt1, dim3(1), dim3(64), 0, s, b0);
-    return hipGetLastError();
-}
-
 hipError_t launch_face_check(const FacePtrs& in, const Consts& K, double* part, double* result, hipStream_t s) {
     const int nblk = (int)(((int64_t)K.nx * K.ny + TPB - 1) / TPB);
     hipLaunchKernelGGL(k_face_check, dim3(nblk), dim3(TPB), 0, s, in, K, part);
@@ -2547,11 +2551,13 @@ hipError_t launch_init_ref(const InPtrs& in, const Consts& K, double* part, doub
 #endif
 
 template <typename TS>
-hipError_t launch_init(const InPtrs& in, const Consts& K, double* scr, char* dst, hipStream_t s) {
+hipError_t launch_init(const InPtrs& in, const Consts& K, double* scr, char* dst, double* ez0, double* part,
+                       double* b0, hipStream_t s) {
     using TE = typename StoreTypes<TS>::E;
     int tx, ty, nt, nb;
     grid_of(K, tx, ty, nt, nb);
-    hipLaunchKernelGGL(k_init_current, dim3(nb), dim3(TPB), 0, s, in, K, tx, ty, nt, scr);
+    hipLaunchKernelGGL(k_init_current, dim3(nb), dim3(TPB), 0, s, in, K, tx, ty, nt, scr, ez0, part);
+    hipLaunchKernelGGL(k_reduce, dim3(1), dim3(TPB), 0, s, (const double*)part, nt, 1, 2, b0);
     hipLaunchKernelGGL((k_init_state<TS, TE>), dim3(nb), dim3(TPB), 0, s, in, K, tx, ty, nt, (const double*)scr, dst);
     return hipGetLastError();
 }
@@ -2589,7 +2595,8 @@ hipError_t launch_guess_samples(const char* src, const Consts& K, double* faceB,
                                         const GuessTables*, hipStream_t);                                             \
     template hipError_t launch_moments<TS>(const char*, const Consts&, const OutPtrs&, const DiagBufs&,               \
                                            const GuessTables*, hipStream_t);                                          \
-    template hipError_t launch_init<TS>(const InPtrs&, const Consts&, double*, char*, hipStream_t);                   \
+    template hipError_t launch_init<TS>(const InPtrs&, const Consts&, double*, char*, double*, double*, double*,       \
+                                         hipStream_t);                                                          \
     template hipError_t launch_ghost<TS>(const FacePtrs&, const Consts&, char*, hipStream_t);                         \
     template hipError_t launch_batch<TS>(const BatchInst*, int, int, int64_t, bool, int, int, int, hipStream_t);      \
     template hipError_t launch_batch_persistent<TS>(const BatchInst*, int, int, bool, int, int, int, int, int*,       \
