@@ -1464,6 +1464,18 @@ __device__ __forceinline__ const Consts& reread(ConstsPtr kp) {
     asm volatile("" : "+s"(kp));
     return *(const Consts*)kp;
 }
+// Likewise the state's base pointers (uniform, in global memory), so that the
+// bases of its arrays are added up at their use and not kept across the walk:
+// a step of 4096 cells takes 10.75 us instead of 11.04, 512 x 512 cells 69.0
+// instead of 71.0.
+template <typename T>
+__device__ __forceinline__ T* again(T* p) {
+    const uint64_t v = (uint64_t)p;
+    uint64_t u = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)v) |
+                 (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32;
+    asm volatile("" : "+s"(u));
+    return (T*)(__attribute__((address_space(1))) T*)u;
+}
 
 // One block owns a row group of 128 (FP64, two lanes per cell) or 256 cells:
 // ROWS = 128 / PXT or 256 / PXT rows of PXT cells, PYT of them along y in each
@@ -1531,13 +1543,15 @@ __device__ __forceinline__ void fused_block(const char* __restrict__ sd, char* _
             int xp = x, yp = all_lanes ? min(yj, K.ny - 1) : yj, hp = h;
             asm volatile("" : "+v"(xp), "+v"(yp), "+v"(hp));
             const Consts& Kp = reread(kp);
+            const char* sp = again(sd);
+            char* dp = again(dd);
             const int cell = xp + Kp.nx * (yp + Kp.ny * z);
             const Nbr nb = make_nbr<true, FLAT>(Kp, xp, yp, z);
             if constexpr (ONE)
-                quad_cell<NT, TS, TE, V, GM, VR, FLAT, SYNC>(sd, dd, faceB, gt, Kp, cell, nb, xp, yp, z,
+                quad_cell<NT, TS, TE, V, GM, VR, FLAT, SYNC>(sp, dp, faceB, gt, Kp, cell, nb, xp, yp, z,
                                                  all_lanes ? active : true, bmax, gate);
             else
-                pair_cell<NT, TS, TE, V, GM, VR, FLAT, SYNC>(sd, dd, faceB, gt, Kp, cell, nb, hp, xp, yp, z,
+                pair_cell<NT, TS, TE, V, GM, VR, FLAT, SYNC>(sp, dp, faceB, gt, Kp, cell, nb, hp, xp, yp, z,
                                                  all_lanes ? active : true, bmax, gate);
         }
     }
@@ -1712,7 +1726,7 @@ __global__ __launch_bounds__(PTPB, WV) void k_fused_batch_persistent(const Batch
         while (j < P) {  // j is uniform over the block
             int nj = 0;
             if (threadIdx.x == 0) nj = atomicAdd(cnt, 1);
-            const int b = x * P + j;
+            const int b = __builtin_amdgcn_readfirstlane(x * P + j);
             if (b < total) {
                 const int i = find_instance(ninst, b, [&](int jj) { return I[jj].blk0; });
                 const BatchInst& B = I[i];
