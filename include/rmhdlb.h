@@ -340,9 +340,11 @@ int rmhdlb_mlp_eval(const float *w, const float *X, const float *Yt, int32_t n, 
  * The fused step runs blocks of 256 threads over row groups of px x (R / px)
  * cells, px in {64, 32, 16} (128 too in batches): R = 128 with FP64
  * storage (two lanes per cell), R = 256 with FP32 and FP16 (one lane per
- * cell);
- * a block takes yw such groups stacked along y (a tile of px x (R / px) yw
- * cells) and walks zb z-planes.  With zg > 1 the planes are taken in chunks
+ * cell).  With FP64 and FP32 storage and more than one z-plane (or a driven
+ * face), a group of four rows or more lies in two neighbouring planes, half
+ * of its rows in each;
+ * a block takes yw such groups stacked along y (a tile of R yw cells) and
+ * walks zb z-planes.  With zg > 1 the planes are taken in chunks
  * of zg * zb per column, and the zg blocks of a chunk walk them interleaved
  * (block r: planes r, r + zg, ...), so that they run at neighbouring planes
  * together and share the z-neighbour planes in the L2 cache.  The shape
@@ -352,7 +354,8 @@ int rmhdlb_mlp_eval(const float *w, const float *X, const float *Yt, int32_t n, 
 /* Time the launch shapes on the context's current state with HIP events and
  * keep the fastest for its later steps: every (px, zb) with zb in
  * {1, 2, 4, 8, 16} up to nz and zg = yw = 1, plus px = 64 with zb in
- * {16, 32, 64} and zg in {2, 4} where zg * zb <= nz; on a slab (nz = 1) every
+ * {16, 32, 64} and zg in {2, 4}, (64, 4, 2), (64, 4, 4), (64, 8, 2) and
+ * (32, 8, zg) with zg in {2, 4, 8}, each where zg * zb <= nz; on a slab (nz = 1) every
  * px with yw in {1, 2, 4}.  The state is not advanced (each timed step reads
  * the current buffer and writes the other).  Results are cached per process
  * by grid size, storage, boundary kinds, guess mode, collision, flux, force

@@ -825,9 +825,9 @@ int rmhdlb_autotune(rmhdlb_ctx* C, int32_t* px_out, int32_t* zb_out, int32_t* zg
     }
     if (!cached) {
         // Candidates: every tile width with zb in {1, 2, 4, 8, 16} walked by
-        // one block, and 64-wide tiles with long walks shared by 2 or 4
-        // interleaved blocks per column (chunks of up to 256 planes).  On a
-        // slab (nz = 1) the blocks instead take 1, 2 or 4 row groups.
+        // one block, 64-wide tiles with long walks shared by 2 or 4
+        // interleaved blocks per column (chunks of up to 256 planes), and
+        // shorter shared walks (below).  On a slab (nz = 1) the blocks instead take 1, 2 or 4 row groups.
         std::vector<rmhd::StepTuning> cand;
         const bool only64 = C->guess_mode || C->K.coll || C->K.flux || C->K.forced || C->K.bprev;
         for (int px : {64, 32, 16})
@@ -945,7 +945,7 @@ struct rmhdlb_batch {
     hipStream_t stream;
     int storage;
     int px;     // tile width (128, 64, 32, 16)
-    int yw;     // row groups per block (the tile is px x (128 / px) yw cells on a slab)
+    int yw;     // row groups per block (cells_per_block(elem) yw cells, px wide)
     int waves;  // occupancy variant of the FP32 kernel (2 or 3 waves per SIMD)
     std::vector<rmhd::BatchInst> host;
     rmhd::BatchInst* dev;

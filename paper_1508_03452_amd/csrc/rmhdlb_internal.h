@@ -100,9 +100,9 @@ int num_tiles(const Consts& K);
 __host__ __device__ inline int state_arrays(const Consts& K) { return NSTATE + (K.bprev ? 3 : 0); }
 
 // Launch shape of the fused step: z-planes walked per block, the tile width
-// along x (64, 32 or 16 cells; a row group has 128 cells), the number of
-// blocks that walk a column's chunk of zg * zb planes interleaved, and the
-// row groups per block stacked along y.
+// along x (64, 32 or 16 cells; a row group has cells_per_block cells, in
+// tile_planes planes), the number of blocks that walk a column's chunk of
+// zg * zb planes interleaved, and the row groups per block stacked along y.
 struct StepTuning {
     int zb;
     int px;
