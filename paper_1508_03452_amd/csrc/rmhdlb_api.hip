@@ -151,6 +151,9 @@ Consts make_consts(const rmhdlb_params* P) {
     K.gc2 = ct_c0 * 4.5 * ca * ca;
     K.gc3 = ct_c0 * 1.5;
     K.inv_2dx = 0.5 / P->dx;
+    K.inv1wg = 1.0 / (1.0 + K.wg);
+    K.cj = 1.0 / (16.0 * 1.4142135623730951 * K.c);
+    K.ce = 1.0 / (8.0 * 1.4142135623730951 * K.c);
     return K;
 }
 

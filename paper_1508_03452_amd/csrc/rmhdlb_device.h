@@ -71,6 +71,8 @@ struct Consts {
     double wp[3];        // g weights (rest, axis, diagonal)
     double gc1, gc2, gc3;  // (c_t/c_0) * (3 c_a, 9/2 c_a^2, 3/2) of the g equilibrium
     double inv_2dx;
+    double inv1wg;       // 1 / (1 + wg)
+    double cj, ce;       // weights of J and E in the h equilibrium: 1 / (16 sqrt(2) c) and 1 / (8 sqrt(2) c)
     // Stored f, g are deviations from these per-class shifts (rest, axis,
     // diagonal): w_i E_ref and w'_i N_ref rounded to the step's arithmetic
     // type, all 0 on the plain FP64 path.  fs0 = sum_i fsh_i, fsaa = the sum

@@ -963,7 +963,7 @@ __device__ __forceinline__ void pair_cell(const char* __restrict__ sd, char* __r
 
     // collisions and stores (new deviations)
     const V rate = (V)(M.gam * K.inv_tau);
-    const V wg = (V)K.wg, inv1wg = (V)(1.0 / (1.0 + K.wg));
+    const V wg = (V)K.wg, inv1wg = (V)K.inv1wg;
     const V ng = (V)(M.n * M.gam);
     const V gc1 = (V)K.gc1, gc2 = (V)K.gc2, gc3b2 = (V)(K.gc3 * norm2(M.beta));
     const V bx_ = (V)M.beta[0], by_ = (V)M.beta[1], bz_ = (V)M.beta[2];
@@ -1009,7 +1009,7 @@ __device__ __forceinline__ void pair_cell(const char* __restrict__ sd, char* __r
                 st2<NT, TS>(dd, cc + CHUNK * 16 * i0, fn, (Gv[s] + wg * (geq - (V)K.gsh[cls])) * inv1wg);
         }
     });
-    const V cj = (V)(1.0 / (16.0 * 1.4142135623730951 * K.c)), cE = (V)(1.0 / (8.0 * 1.4142135623730951 * K.c));
+    const V cj = (V)K.cj, cE = (V)K.ce;
     const V J0 = (V)M.J[0], J1 = (V)M.J[1], J2 = (V)M.J[2];
     const V E0 = (V)M.E[0], E1 = (V)M.E[1], E2 = (V)M.E[2];
 #pragma unroll
@@ -1340,7 +1340,7 @@ __device__ __forceinline__ void quad_cell(const char* __restrict__ sd, char* __r
 
     // collisions and stores (new deviations)
     const V rate = (V)(M.gam * K.inv_tau);
-    const V wg = (V)K.wg, inv1wg = (V)(1.0 / (1.0 + K.wg));
+    const V wg = (V)K.wg, inv1wg = (V)K.inv1wg;
     const V ng = (V)(M.n * M.gam);
     const V gc1 = (V)K.gc1, gc2 = (V)K.gc2, gc3b2 = (V)(K.gc3 * norm2(M.beta));
     const V bx_ = (V)M.beta[0], by_ = (V)M.beta[1], bz_ = (V)M.beta[2];
@@ -1417,7 +1417,7 @@ __device__ __forceinline__ void quad_cell(const char* __restrict__ sd, char* __r
             }
         });
     }
-    const V cj = (V)(1.0 / (16.0 * 1.4142135623730951 * K.c)), cE = (V)(1.0 / (8.0 * 1.4142135623730951 * K.c));
+    const V cj = (V)K.cj, cE = (V)K.ce;
     const V J0 = (V)M.J[0], J1 = (V)M.J[1], J2 = (V)M.J[2];
     const V E0 = (V)M.E[0], E1 = (V)M.E[1], E2 = (V)M.E[2];
 #pragma unroll
