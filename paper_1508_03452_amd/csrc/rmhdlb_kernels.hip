@@ -501,9 +501,15 @@ constexpr int PTPB = 256;  // threads of a fused-step block: 128 cells, two lane
 // leaves a wave the 256 registers that the cell's populations and two records'
 // loads in flight take (three spilled: FP32 batch kernel 67 registers).
 constexpr int FUSED_WAVES = 2;
-// The median of a, b and 0: minmod(a, b) in one instruction (FP64: four) instead of five (seven).
+// minmod(a, b): the median of a, b and 0, one instruction in FP32 (FP64: four) instead of five (seven).
 __device__ __forceinline__ float median0(float a, float b) { return __builtin_amdgcn_fmed3f(a, b, 0.0f); }
 __device__ __forceinline__ double median0(double a, double b) { return fmax(fmin(a, b), fmin(fmax(a, b), 0.0)); }
+// The same where a may be a NaN and b is then the slope: FP64's minima and maxima give b by themselves; in FP32 the
+// median is taken of them (of a NaN itself it would be min(b, 0)).
+__device__ __forceinline__ float median0_known(float a, float b) {
+    return __builtin_amdgcn_fmed3f(fminf(a, b), fmaxf(a, b), 0.0f);
+}
+__device__ __forceinline__ double median0_known(double a, double b) { return median0(a, b); }
 
 // x + y and x - y of stored values in the step's arithmetic.  FP16 values go
 // through a fused multiply-add by a 1 that the compiler does not see, which
@@ -519,13 +525,19 @@ __device__ __forceinline__ V difference(T x, T y, V one) {
 
 // A population after its transport along the link without viscosity:
 // f - C (face_p - face_m), face values f + slope minmod of the differences
-// on both sides.  (b 0 + f carries a NaN of the downwind neighbour on, as
-// comparisons would; the median of a NaN is one of the other two.)
+// on both sides.  minmod takes no part of a value that it does not choose: an
+// infinite downwind neighbour p1 leaves the finite slope f - m1, a NaN two
+// cells upwind (m2) likewise.  A NaN of p1 has to reach the cell; the median
+// does not carry it, so b = p1 - f goes back to the caller, who tests it
+// (unordered, two populations per comparison).  As fast as b 0 added to f, which
+// carries a NaN but turns an infinity into one too (FP16, 256x256x512, a pass of
+// 20 steps: 75.2 ms so, 75.4 now; FP32, 256x256x64: 13.7 and 13.6).
 template <typename V, typename T>
-__device__ __forceinline__ V advect(T f, T m1, T m2, T p1, V cour, V slope, V one) {
-    const V a = difference<V>(f, m1, one), b = difference<V>(p1, f, one), c = difference<V>(m1, m2, one);
-    const V face_p = fma(slope, median0(a, b), fma(b, V(0), V(f)));
-    const V face_m = fma(slope, median0(c, a), V(m1));
+__device__ __forceinline__ V advect(T f, T m1, T m2, T p1, V cour, V slope, V one, V& b) {
+    const V a = difference<V>(f, m1, one), c = difference<V>(m1, m2, one);
+    b = difference<V>(p1, f, one);
+    const V face_p = fma(slope, median0(a, b), V(f));
+    const V face_m = fma(slope, median0_known(c, a), V(m1));
     return fma(-cour, face_p - face_m, V(f));
 }
 
@@ -555,6 +567,8 @@ template <typename T>
 __device__ __forceinline__ void pin(T& v) {
     asm volatile("" : "+v"(v)::"memory");
 }
+// Likewise a mask of lanes, in scalar registers.
+__device__ __forceinline__ void pin_mask(uint64_t& m) { asm volatile("" : "+s"(m)); }
 
 // Transport (collide-then-transport reading of Eq. rlb): link-wise
 // minmod-MUSCL flux difference, plus the 7-point bulk-viscosity Laplacian
@@ -680,9 +694,11 @@ __device__ __forceinline__ void macroscopic(const char* __restrict__ src, const 
                            double gp1, double sx, double sy, double sz) {
                 constexpr int i = decltype(qc)::value;
                 const double lap = fma(-6.0, f0, sx + sy + sz);
-                const double fv = fma(K.kv, lap, advect<double, double>(f0, fm1, fm2, fp1, K.cour, K.slope, 1.0)) +
-                                  fshift(K, i);
-                const double gv = advect<double, double>(g0, gm1, gm2, gp1, K.cour, K.slope, 1.0) + gshift(K, i);
+                double bf, bg;
+                const double fa = advect<double, double>(f0, fm1, fm2, fp1, K.cour, K.slope, 1.0, bf);
+                const double ga = advect<double, double>(g0, gm1, gm2, gp1, K.cour, K.slope, 1.0, bg);
+                const double fv = fma(K.kv, lap, bf == bf ? fa : bf) + fshift(K, i);
+                const double gv = (bg == bg ? ga : bg) + gshift(K, i);
                 M.T00 += fv;
                 M.N0 += gv;
                 if (EX[i]) t0x += EX[i] * fv;
@@ -791,6 +807,7 @@ __device__ __forceinline__ void pair_cell(const char* __restrict__ sd, char* __r
     const V cour = (V)K.cour, kv = (V)K.kv, slope = (VR & 2) ? (V)K.slope : V(0.5);
     V Fv[10], Gv[10], Hv[13];
     V t00 = 0, t0x = 0, t0y = 0, t0z = 0, txx = 0, tyy = 0, tzz = 0, txy = 0, txz = 0, tyz = 0, n0 = 0;
+    uint64_t lost = 0;  // lanes with a NaN in a downwind neighbour: their energy, and with it the cell, becomes one
     // slot 0: f_0, g_0 (lane 0) and h_rest (lane 1)
     {
         const vec2<V> fg0 = ldv2<V, TS>(sd, c16);
@@ -868,8 +885,11 @@ __device__ __forceinline__ void pair_cell(const char* __restrict__ sd, char* __r
             const V lyp = K_::lap_y ? r.yp : up, lym = K_::lap_y ? r.ym : dn;
             const V lzp = K_::lap_z || FLAT ? r.zp : up, lzm = K_::lap_z || FLAT ? r.zm : dn;
             const V lap = (lxp + lxm) + (lyp + lym) + (lzp + lzm) - V(6) * f0;
-            const V fv = fma(kv, lap, advect<V, TS>(r.c0.x, r.m1.x, r.m2.x, r.p1.x, cour, slope, V(1)));
-            const V gv = advect<V, TS>(r.c0.y, r.m1.y, r.m2.y, r.p1.y, cour, slope, V(1));
+            V bf, bg;
+            const V fv = fma(kv, lap, advect<V, TS>(r.c0.x, r.m1.x, r.m2.x, r.p1.x, cour, slope, V(1), bf));
+            const V gv = advect<V, TS>(r.c0.y, r.m1.y, r.m2.y, r.p1.y, cour, slope, V(1), bg);
+            lost |= __builtin_amdgcn_ballot_w64(__builtin_isunordered(bf, bg));
+            pin_mask(lost);
             Fv[s] = fv;
             Gv[s] = gv;
             pin(Fv[s]), pin(Gv[s]);  // the slot's arithmetic stays here
@@ -917,7 +937,7 @@ __device__ __forceinline__ void pair_cell(const char* __restrict__ sd, char* __r
 #pragma unroll
     for (int a = 0; a < 3; ++a) M.Ep[a] = Ep[a];
     const double gpart = ((h ? -ga : ga) + (h ? gb : -gb)) + (h ? -gc : gc);
-    M.T00 = K.fs0 + (double)pair_sum(t00);
+    M.T00 = K.fs0 + (double)pair_sum(__builtin_amdgcn_inverse_ballot_w64(lost) ? V(__builtin_nan("")) : t00);
     M.N0 = K.gs0 + (double)pair_sum(n0);
     M.T0[0] = KAPPA * (double)pair_sum(t0x);
     M.T0[1] = KAPPA * (double)pair_sum(t0y);
@@ -1084,6 +1104,7 @@ __device__ __forceinline__ void quad_cell(const char* __restrict__ sd, char* __r
     const V cour = (V)K.cour, kv = (V)K.kv, slope = (VR & 2) ? (V)K.slope : V(0.5);
     V Fv[Q], Gv[Q], Hv[QH + 1];
     V t00 = 0, t0x = 0, t0y = 0, t0z = 0, txx = 0, tyy = 0, tzz = 0, txy = 0, txz = 0, tyz = 0, n0 = 0;
+    uint64_t lost = 0;  // lanes with a NaN in a downwind neighbour: their energy, and with it the cell, becomes one
     const int64_t lap_xp = rec(nb.at(1, 0, 0)), lap_xm = rec(nb.at(-1, 0, 0)), lap_yp = rec(nb.at(0, 1, 0)),
                   lap_ym = rec(nb.at(0, -1, 0)), lap_zp = rec(nb.at(0, 0, 1)), lap_zm = rec(nb.at(0, 0, -1));
     // Transport and moments of slot s from its quads at the link points x - 2e .. x + 2e and the
@@ -1100,12 +1121,16 @@ __device__ __forceinline__ void quad_cell(const char* __restrict__ sd, char* __r
         auto laplacian = [&](TS f0, TS xp, TS xm, TS yp, TS ym, TS zp, TS zm) {
             return fma(V(-6), V(f0), sum_of<V>(xp, xm, one) + sum_of<V>(yp, ym, one) + sum_of<V>(zp, zm, one));
         };
+        V bf0, bf1, bg0, bg1;
         const V fv0 = fma(kv, laplacian(q0.x, lxp.x, lxm.x, lyp.x, lym.x, lzp.x, lzm.x),
-                          advect<V, TS>(q0.x, qm1.x, qm2.x, qp1.x, cour, slope, one));
+                          advect<V, TS>(q0.x, qm1.x, qm2.x, qp1.x, cour, slope, one, bf0));
         const V fv1 = fma(kv, laplacian(q0.z, lxp.z, lxm.z, lyp.z, lym.z, lzp.z, lzm.z),
-                          advect<V, TS>(q0.z, qp1.z, qp2.z, qm1.z, cour, slope, one));
-        const V gv0 = advect<V, TS>(q0.y, qm1.y, qm2.y, qp1.y, cour, slope, one);
-        const V gv1 = advect<V, TS>(q0.w, qp1.w, qp2.w, qm1.w, cour, slope, one);
+                          advect<V, TS>(q0.z, qp1.z, qp2.z, qm1.z, cour, slope, one, bf1));
+        const V gv0 = advect<V, TS>(q0.y, qm1.y, qm2.y, qp1.y, cour, slope, one, bg0);
+        const V gv1 = advect<V, TS>(q0.w, qp1.w, qp2.w, qm1.w, cour, slope, one, bg1);
+        lost |= __builtin_amdgcn_ballot_w64(__builtin_isunordered(bf0, bf1)) |
+                __builtin_amdgcn_ballot_w64(__builtin_isunordered(bg0, bg1));
+        pin_mask(lost);
         Fv[i0] = fv0;
         Fv[i1] = fv1;
         Gv[i0] = gv0;
@@ -1295,7 +1320,7 @@ __device__ __forceinline__ void quad_cell(const char* __restrict__ sd, char* __r
                           ((double)gE[4] - (double)gE[5]);
         M.rho_g = K.eps0 * K.inv_2dx * dv;
     }
-    M.T00 = K.fs0 + (double)t00;
+    M.T00 = K.fs0 + (double)(__builtin_amdgcn_inverse_ballot_w64(lost) ? V(__builtin_nan("")) : t00);
     M.N0 = K.gs0 + (double)n0;
     M.T0[0] = KAPPA * (double)t0x;
     M.T0[1] = KAPPA * (double)t0y;
