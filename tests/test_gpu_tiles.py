@@ -1,0 +1,120 @@
+"""Launch shapes of the kernels with more than one plane, bit for bit: the arithmetic of a cell does not depend on the
+tile, so every shape, and every batch, gives the same state in every storage form."""
+import numpy as np
+import pytest
+
+from paper_1508_03452_amd import workloads as W
+
+from .parity_util import run_gpu
+
+pytestmark = pytest.mark.gpu
+STORAGES = ["f64", "f32", "f16"]
+PER, OPEN = ("periodic", "periodic"), ("open", "open")
+# the tuner's shared walks (px, zb, zg), one that divides neither the planes nor the tile's two, and plain walks;
+# 67 planes: every zg stays as given, the last chunk and (FP64, FP32) the last tile are ragged
+SHAPES = [(32, 8, 2), (32, 8, 4), (32, 8, 8), (64, 4, 2), (64, 4, 4), (64, 8, 2), (64, 16, 4), (64, 3, 2), (16, 5, 3),
+          (64, 1, 1), (32, 1, 1), (64, 67, 1)]
+
+
+def _torch_cuda():
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return torch
+
+
+def _state(s):
+    return s.get_state().cpu().numpy()
+
+
+def _box(shape=(70, 13, 67), **kw):
+    return W.random_state(shape=shape, seed=6, vmax=0.1, Bmag=0.2, Emag=0.02, sigma=3.0, bc=(OPEN, PER, OPEN), **kw)
+
+
+@pytest.mark.parametrize("storage", STORAGES)
+def test_shared_walks_give_identical_states(storage):
+    _torch_cuda()
+    w = _box()
+    ref = run_gpu(w, 3, storage=storage)
+    want = _state(ref)
+    assert np.isfinite(want).all()
+    s = run_gpu(w, 0, storage=storage)
+    for shape in SHAPES:
+        print(f"[tiles] {storage} {shape}", flush=True)
+        s.init_fields(w.fields)
+        s.set_tuning(*shape)
+        s.step(3)
+        assert np.array_equal(want, _state(s)), shape
+
+
+@pytest.mark.parametrize("storage", STORAGES)
+@pytest.mark.parametrize("kw", [dict(collision=1), dict(flux=1), dict(collision=1, flux=1), dict(b_prev=1)])
+def test_shared_walks_of_the_other_readings(storage, kw):
+    _torch_cuda()
+    print(f"[tiles] {storage} {kw}", flush=True)
+    w = _box((70, 13, 19), **kw)
+    want = _state(run_gpu(w, 3, storage=storage))
+    assert np.isfinite(want).all()
+    s = run_gpu(w, 0, storage=storage)
+    for shape in [(64, 4, 2), (64, 3, 2), (64, 1, 1), (64, 19, 1)]:
+        s.init_fields(w.fields)
+        s.set_tuning(*shape)
+        s.step(3)
+        assert np.array_equal(want, _state(s)), shape
+
+
+@pytest.mark.parametrize("storage", STORAGES)
+def test_shared_walks_with_the_learned_guess(storage):
+    """The network on a box with an odd number of planes: every lane stays, those without a cell compute a copy of the
+    edge cell.  The shapes agree bit for bit, and with the plain recovery within the forms' parity bounds (1e-12, 5e-5
+    and 5e-3 of each state array's scale): the root is the same."""
+    _torch_cuda()
+    w = W.random_state(shape=(70, 13, 17), seed=31, vmax=0.8, modes=1, Bmag=0.1, Emag=0.01, sigma=10.0, tau=3.0)
+    s = run_gpu(w, 0, storage=storage)
+    s.train_guess(W.mlp_init(11), n_samples=8192, iters=200)
+    s.set_guess(True)
+    states = []
+    for shape in [(64, 4, 1), (64, 4, 2), (64, 3, 2), (64, 1, 1)]:
+        print(f"[tiles] guess {storage} {shape}", flush=True)
+        s.init_fields(w.fields)
+        s.set_tuning(*shape)
+        s.step(3)
+        states.append(_state(s))
+        assert np.array_equal(states[0], states[-1]), shape
+    assert s.moments(fields=())["diag"]["guess_steps"] == 3
+    plain = _state(run_gpu(w, 3, storage=storage))
+    scale = np.maximum(np.abs(plain).reshape(plain.shape[0], -1).max(axis=1), 1e-2)
+    gap = (np.abs(states[0] - plain).reshape(plain.shape[0], -1).max(axis=1) / scale).max()
+    assert gap <= {"f64": 1e-12, "f32": 5e-5, "f16": 5e-3}[storage], gap
+
+
+def _batch(ws, storage, stream):
+    from paper_1508_03452_amd.rmhdlb import Batch
+    b = Batch([(w.shape, w.bc, w.params) for w in ws], storage=storage, stream=stream)
+    for w, s in zip(ws, b.instances):
+        s.init_fields(w.fields)
+    return b
+
+
+@pytest.mark.parametrize("storage", STORAGES)
+@pytest.mark.parametrize("kinds", ["slabs", "boxes", "mixed"])
+def test_batches_match_instances_stepped_alone(storage, kinds):
+    """Slabs whose fields have every component, boxes, and both: a slab beside a box takes the general kernels, alone
+    those for a single plane, and its state is the same."""
+    torch = _torch_cuda()
+    print(f"[tiles] batch {kinds} {storage}", flush=True)
+    ws = []
+    if kinds != "boxes":
+        ws += [_box((130, 9, 1)), W.random_state(shape=(63, 14, 1), seed=9, vmax=0.3, Bmag=0.2, Emag=0.05, sigma=3.0,
+                                                 bc=(PER, OPEN, PER))]
+    if kinds != "slabs":
+        ws += [_box((70, 13, 9)), W.random_state(shape=(33, 20, 6), seed=8, vmax=0.2, Bmag=0.2, Emag=0.02, sigma=3.0)]
+    want = [_state(run_gpu(w, 6, storage=storage)) for w in ws]
+    for px, yw in ((64, 1), (32, 2)):
+        b = _batch(ws, storage, torch.cuda.Stream())
+        b.set_tuning(px, yw, 2)
+        b.step(6)
+        torch.cuda.synchronize()
+        for w, s, r in zip(ws, b.instances, want):
+            assert np.array_equal(_state(s), r), (w.shape, px, yw)
+        b.close()
