@@ -984,10 +984,10 @@ int batch_table(rmhdlb_batch* B) {
         I.K = C->K;
         for (int b = 0; b < 2; ++b) I.buf[b] = C->buf[b];
         I.faceB = C->faceB;
-        I.zb = std::max(1, std::min(C->tune.zb, C->K.nz));
+        const int elem = rmhd::storage_bytes(B->storage);
+        I.zb = rmhd::walk_planes(elem, B->px, B->flat, C->tune.zb, C->K.nz);
         I.yw = B->yw;
-        rmhd::step_geometry(C->K, B->px, I.zb, 1, I.yw, rmhd::storage_bytes(B->storage), B->flat,
-                            I.tiles_x, I.ncol, I.nblk);
+        rmhd::step_geometry(C->K, B->px, I.zb, 1, I.yw, elem, B->flat, I.tiles_x, I.ncol, I.nblk);
         I.blk0 = blk;
         I.face0 = face;
         blk += I.nblk;

@@ -201,13 +201,23 @@ inline bool flat_grid(const Consts& K) { return K.nz == 1 && !K.drv; }
 // Cells per row group of a fused-step block: 128 in the pair layout (FP64 storage, elem = 8 bytes, two lanes
 // per cell), 256 in the quad and double-quad layouts (FP32 and FP16 storage, one lane per cell).
 __host__ __device__ constexpr int cells_per_block(int elem) { return elem == 8 ? 128 : 256; }
-// z-planes of a fused-step tile: two in FP64 and FP32 where the rows suffice
+// z-planes of a fused-step tile for walks of zb planes: two in FP64 and FP32 where the rows suffice
 // (at least four), so that half of the z-neighbour planes of the stencil are
 // the tile's own: 56 instead of 68 lines of L1 per 128 cells and direction
 // (FP64 at px = 32), ms per step at 256x256x512 one / two planes FP64 9.9 / 9.36, FP32
-// 4.9 / 4.75 (wavefronts in step).  FP16 is 1 % faster with one plane.
-__host__ __device__ constexpr int tile_planes(int elem, int px, bool flat) {
+// 4.9 / 4.75 (wavefronts in step).  FP16 is 1 % faster with one plane.  A walk of a single plane
+// takes one too: the second would leave half of every block idle (128x128x128, FP32 with zb = 1,
+// yw = 4: 0.504 ms with two planes, 0.304 with one; FP64 32-wide 1.022 and 0.607).
+__host__ __device__ constexpr int most_planes(int elem, int px, bool flat) {
     return flat || elem == 2 || cells_per_block(elem) / px < 4 ? 1 : 2;
+}
+__host__ __device__ constexpr int tile_planes(int elem, int px, bool flat, int zb) {
+    return zb < 2 ? 1 : most_planes(elem, px, flat);
+}
+// Planes that a block walks for a tuning's zb: at most the grid's, and whole tiles.
+inline int walk_planes(int elem, int px, bool flat, int zb, int nz) {
+    zb = zb < 1 ? 1 : (zb < nz ? zb : nz);
+    return tile_planes(elem, px, flat, zb) == 2 ? zb + (zb & 1) : zb;
 }
 // Launch geometry of the fused step for a tile width px, zb planes per block
 // and zg blocks per column and chunk of zg * zb planes: tiles along x,

@@ -1503,7 +1503,7 @@ __device__ __forceinline__ T* again(T* p) {
 }
 
 // One block owns a row group of 128 (FP64, two lanes per cell) or 256 cells:
-// ROWS = 128 / PXT or 256 / PXT rows of PXT cells, PYT of them along y in each
+// ROWS = 128 / PXT or 256 / PXT rows of PXT cells (a power of two), PYT of them along y in each
 // of ZT neighbouring planes (tile_planes), yw such groups stacked along y.  It
 // walks zb z-planes, the yw groups of its planes one after another.  A chunk
 // of zg * zb planes is shared by zg blocks per column, which take its planes
@@ -1525,7 +1525,8 @@ __device__ __forceinline__ void fused_block(const char* __restrict__ sd, char* _
     // pair layout (FP64): 128 cells per row group, two lanes each; quad and double-quad layouts (FP32,
     // FP16): 256 cells, one lane each
     constexpr bool ONE = quad_layout<TS>();
-    constexpr int ROWS = cells_per_block(sizeof(TS)) / PXT, ZT = tile_planes(sizeof(TS), PXT, FLAT), PYT = ROWS / ZT;
+    constexpr int ROWS = cells_per_block(sizeof(TS)) / PXT, MOST = most_planes(sizeof(TS), PXT, FLAT);
+    const int ZT = MOST == 1 ? 1 : (zb < 2 ? 1 : MOST), PYT = ZT == 1 ? ROWS : ROWS / MOST;  // as tile_planes
     const int per = ncol * zg, zc = b / per, r = b % per;
     const int col = r / zg, zoff = r % zg;
     const int tx = col % tiles_x, ty = col / tiles_x;
@@ -1535,9 +1536,9 @@ __device__ __forceinline__ void fused_block(const char* __restrict__ sd, char* _
     const int c = ONE ? (int)threadIdx.x : (int)(threadIdx.x >> 6) * 32 + (lane & 31), h = ONE ? 0 : lane >> 5;
     const int xr = tx * PXT + (c % PXT);
     int x = xr;
-    const int ybase = ty * PYT * yw + c / PXT % PYT;
+    const int ybase = ty * PYT * yw + (c / PXT & (PYT - 1));
     // plane of the tile this wavefront works on (its rows share it)
-    const int zl = ZT == 1 ? 0 : __builtin_amdgcn_readfirstlane(c / PXT / PYT);
+    const int zl = MOST == 1 ? 0 : __builtin_amdgcn_readfirstlane(c / PXT >= PYT);
     // with the force every lane stays (the wavefront's largest |beta| is
     // reduced over all 64 lanes)
     constexpr bool all_lanes = GM == GUESS_PAIR || GM == GUESS_SINGLE || (VR & 4) != 0;
@@ -2366,7 +2367,7 @@ hipError_t launch_face_b(const char* src, const Consts& K, double* faceB, hipStr
 #if RMHDLB_FORM == 64  // what depends on no storage form is built once
 void step_geometry(const Consts& K, int px, int zb, int zg, int yw, int elem, bool flat, int& tiles_x, int& ncol,
                    int& nblk) {
-    const int py = cells_per_block(elem) / px / tile_planes(elem, px, flat) * yw;
+    const int py = cells_per_block(elem) / px / tile_planes(elem, px, flat, zb) * yw;
     tiles_x = (K.nx + px - 1) / px;
     ncol = tiles_x * ((K.ny + py - 1) / py);
     nblk = ncol * zg * ((K.nz + zg * zb - 1) / (zg * zb));
@@ -2378,6 +2379,7 @@ static void launch_fused(const char* sd, char* dd, double* faceB, const GuessTab
     using TE = typename StoreTypes<TS>::E;
     using V = typename StoreTypes<TS>::V;
     int tx, ncol, nblk;
+    zb = walk_planes(sizeof(TS), PXT, flat_grid(K), zb, K.nz);
     step_geometry(K, PXT, zb, zg, yw, sizeof(TS), flat_grid(K), tx, ncol, nblk);
     const int grid = ((nblk + 7) / 8) * 8;
     if (flat_grid(K))
@@ -2393,7 +2395,7 @@ hipError_t launch_step(const char* src, char* dst, const Consts& K, const StepTu
                        double* faceB, const GuessTables* gt, hipStream_t s) {
     hipError_t e = launch_face_b<TS>(src, K, faceB, s);
     if (e != hipSuccess) return e;
-    const int zb = tune.zb > 0 ? (tune.zb < K.nz ? tune.zb : K.nz) : 1;
+    const int zb = tune.zb;
     // interleaved walks: zg blocks per column and chunk (the force path keeps
     // zg = 1, the geometry its per-wavefront maxima are sized for)
     const int zg = (tune.zg > 1 && !K.forced) ? tune.zg : 1;
@@ -2409,7 +2411,8 @@ hipError_t launch_step(const char* src, char* dst, const Consts& K, const StepTu
         else
             launch_fused<TS, GUESS_NONE, 64, 4>(src, dst, faceB, gt, K, zb, 1, 1, s);
         int tx, ncol, nblk;
-        step_geometry(K, 64, zb, 1, 1, sizeof(TS), flat_grid(K), tx, ncol, nblk);
+        step_geometry(K, 64, walk_planes(sizeof(TS), 64, flat_grid(K), zb, K.nz), 1, 1, sizeof(TS), flat_grid(K), tx,
+                      ncol, nblk);
         hipLaunchKernelGGL(k_vmax_reduce, dim3(1), dim3(TPB), 0, s, K.vmax_part, (int64_t)nblk * (PTPB / 64),
                            const_cast<double*>(K.vmax_prev));
     } else if (vr) {  // the alternative readings: 64-wide tiles, no guess

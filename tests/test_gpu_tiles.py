@@ -118,3 +118,44 @@ def test_batches_match_instances_stepped_alone(storage, kinds):
         for w, s, r in zip(ws, b.instances, want):
             assert np.array_equal(_state(s), r), (w.shape, px, yw)
         b.close()
+
+
+@pytest.mark.parametrize("storage", STORAGES)
+def test_walks_of_one_plane_and_of_an_odd_number(storage):
+    """One-plane walks, stacked groups and odd walks of the two-plane tiles, on boxes of 7 planes and on a single plane
+    above a driven face (the general kernels with one plane)."""
+    _torch_cuda()
+    driven = W.flare(nx=70, ny=24, nz=1, Lz=6.0, sigma=1e3)
+    for w in (_box((70, 29, 7)), driven):
+        ref = run_gpu(w, 0, storage=storage)
+        ref.set_tuning(64, 2, 1, 1)
+        ref.step(3)
+        want = _state(ref)
+        assert np.isfinite(want).all()
+        for shape in [(64, 1, 1, 4), (32, 1, 1, 4), (16, 1, 4, 2), (32, 3, 2, 1), (64, 7, 1, 8), (32, 5, 1, 2)]:
+            print(f"[tiles] {storage} {w.shape} {shape}", flush=True)
+            s = run_gpu(w, 0, storage=storage)
+            s.set_tuning(*shape)
+            s.step(3)
+            assert np.array_equal(want, _state(s)), (w.shape, shape)
+
+
+@pytest.mark.parametrize("storage,px", [("f32", 64), ("f64", 32)])
+def test_walks_of_one_plane_leave_no_half_block_idle(storage, px):
+    """With four groups stacked, a step of one-plane walks takes about as long as one of four-plane walks: with two
+    planes to the tile there as well, half of every block found no rows and the step took 1.5 times as long (FP32; FP64
+    1.6 times)."""
+    torch = _torch_cuda()
+    s = run_gpu(_box((128, 128, 128)), 2, storage=storage)
+    ms = {}
+    for zb, yw in ((1, 4), (4, 1)) * 2:
+        s.set_tuning(px, zb, 1, yw)
+        s.step(3)
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record(s.stream)
+        s.step(20)
+        b.record(s.stream)
+        torch.cuda.synchronize()
+        ms[zb] = min(ms.get(zb, 1e9), a.elapsed_time(b) / 20)
+    print(f"[tiles] {storage} px {px}: one plane {ms[1]:.4f} ms, four {ms[4]:.4f}", flush=True)
+    assert ms[1] <= 1.25 * ms[4], ms
