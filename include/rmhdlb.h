@@ -407,8 +407,8 @@ int rmhdlb_batch_step(rmhdlb_batch *batch, int64_t nsteps);
  * storage (two lanes per cell) and 256 with FP32 and FP16 (one lane per
  * cell), so that the shapes 64 x 4, 32 x 8, 128 x 2, 16 x 16 and 64 x 8 are
  * among them for every storage type (eight shapes in all), each with the
- * kernel compiled for 2 and (FP32 storage) 3 waves per SIMD.  Cached per process by storage and the grids
- * of the instances.  *px, *yw, *waves receive the choice (any may be NULL).
+ * kernel compiled for 2 and (FP32 storage) 3 waves per SIMD.  Cached per process by storage and, of
+ * every instance, the grid and whether its low z-face is driven.  *px, *yw, *waves receive the choice (any may be NULL).
  * Synchronises.  RMHDLB_ESTATE as for rmhdlb_batch_step. */
 int rmhdlb_batch_autotune(rmhdlb_batch *batch, int32_t *px, int32_t *yw, int32_t *waves);
 

@@ -1070,8 +1070,9 @@ int check_batch_state(rmhdlb_batch* B) {
     return RMHDLB_OK;
 }
 
-// Batch tuning cache: storage and every instance's grid.
-typedef std::pair<int, std::vector<std::tuple<int, int, int>>> BatchKey;
+// Batch tuning cache: storage, and every instance's grid and whether its low z-face is driven (with which a single
+// plane takes the general kernels, and all instances of its batch do).
+typedef std::pair<int, std::vector<std::tuple<int, int, int, int>>> BatchKey;
 struct BatchShape {
     int px, yw, waves;
 };
@@ -1230,7 +1231,7 @@ int rmhdlb_batch_autotune(rmhdlb_batch* B, int32_t* px_out, int32_t* yw_out, int
     const int parity = B->ctx[0]->cur;
     BatchKey key;
     key.first = B->storage;
-    for (rmhdlb_ctx* C : B->ctx) key.second.emplace_back(C->K.nx, C->K.ny, C->K.nz);
+    for (rmhdlb_ctx* C : B->ctx) key.second.emplace_back(C->K.nx, C->K.ny, C->K.nz, C->K.drv);
     BatchShape best{64, 1, 2};
     bool cached = false;
     {
