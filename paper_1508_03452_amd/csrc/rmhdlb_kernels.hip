@@ -496,10 +496,11 @@ __device__ __forceinline__ void static_for(Fn&& fn) {
 // path): the transport is linear and the shift is uniform, so the transported
 // value is shift + transport(d); the moments add the exact sums of the shifts;
 // the collisions write the new deviations directly.
-constexpr int PTPB = 256;  // threads of a fused-step block: 128 cells, two lanes each
+constexpr int PTPB = 256;  // threads of a fused-step block: 128 cells, two lanes each (FP64), or 256, one lane each
 // Waves per SIMD the fused kernels are compiled for: two in every form, which
 // leaves a wave the 256 registers that the cell's populations and two records'
-// loads in flight take (three spilled: FP32 batch kernel 67 registers).
+// loads in flight take (three spill in the FP32 batch kernels: 24 registers on
+// single planes, 41-46 on boxes).
 constexpr int FUSED_WAVES = 2;
 // minmod(a, b): the median of a, b and 0, one instruction in FP32 (FP64: four) instead of five (seven).
 __device__ __forceinline__ float median0(float a, float b) { return __builtin_amdgcn_fmed3f(a, b, 0.0f); }
@@ -585,7 +586,6 @@ template <int GM, typename TS, typename TE>
 __device__ __forceinline__ void macroscopic(const char* __restrict__ src, const double* __restrict__ faceB,
                                             const GuessTables* __restrict__ gt, const Consts& K, int cell,
                                             const Nbr& nb, int x, int y, int z, CellSol& M) {
-    using L = Lay<TS>;
     constexpr bool PAIR = !quad_layout<TS>();
     const int pos = (int)K.g0 + cell;
     double t0x = 0, t0y = 0, t0z = 0, txx = 0, tyy = 0, tzz = 0, txy = 0, txz = 0, tyz = 0;
@@ -1052,20 +1052,6 @@ __device__ __forceinline__ void pair_cell(const char* __restrict__ sd, char* __r
 // ---------------------------------------------------- one lane per cell
 
 // 16 bytes of FP16 (two quads)
-template <typename V, typename T>
-__device__ __forceinline__ void ldv8(const char* __restrict__ s, int64_t o, vec4<V>& lo, vec4<V>& hi) {
-    typedef T vec8 __attribute__((ext_vector_type(8)));
-    const vec8 v = *reinterpret_cast<const vec8*>(s + o);
-    lo.x = static_cast<V>(v[0]);
-    lo.y = static_cast<V>(v[1]);
-    lo.z = static_cast<V>(v[2]);
-    lo.w = static_cast<V>(v[3]);
-    hi.x = static_cast<V>(v[4]);
-    hi.y = static_cast<V>(v[5]);
-    hi.z = static_cast<V>(v[6]);
-    hi.w = static_cast<V>(v[7]);
-}
-
 template <bool NT, typename T, typename V>
 __device__ __forceinline__ void st8(char* __restrict__ d, int64_t o, const vec4<V>& lo, const vec4<V>& hi) {
     typedef T vec8 __attribute__((ext_vector_type(8)));
@@ -1471,7 +1457,11 @@ __device__ __forceinline__ void quad_cell(const char* __restrict__ sd, char* __r
 // 128 bytes, at 700 cycles each): in step, the wavefronts of a tile find each
 // other's rows and planes in L1.  256x256x512 with tiles of two planes, ms per
 // step free / in step: FP64 10.0 / 9.36, FP32 5.0 / 4.75; FP16, which is bound
-// by arithmetic, 3.42 / 3.48, and slabs lose 2-4 %.  A wavefront that has no
+// by arithmetic, 3.42 / 3.48, and slabs lose 2-4 %.  Batches of boxes and tiles
+// of one plane gain too: 16 boxes of 64x64x64 FP64 1.22 / 1.14, FP32 0.598 /
+// 0.585; 256x256x64 in FP64's 64-wide tiles with the printed collision 1.27 /
+// 1.21, Lax-Wendroff faces 1.27 / 1.20, the previous-B reading 1.31 / 1.25.
+// A wavefront that has no
 // rows left ends, and the barrier then waits for the others only.  Not in the
 // persistent kernel, whose blocks meet at barriers of their own.
 template <typename TS, bool FLAT>
@@ -1920,7 +1910,6 @@ __global__ __launch_bounds__(TPB, 2) void k_moments(const char* __restrict__ src
     }
 }
 
-// Fixed-order reduction of the per-block partials by one block.
 // Largest |beta| of a forced step from its per-wavefront partials (which are
 // cleared for the next step); one block.
 [[maybe_unused]] static __global__ __launch_bounds__(TPB) void k_vmax_reduce(double* __restrict__ part, int64_t n, double* __restrict__ out) {
@@ -1952,6 +1941,7 @@ __global__ __launch_bounds__(TPB, 2) void k_moments(const char* __restrict__ src
     }
 }
 
+// Fixed-order reduction of the per-block partials, one column of them per block.
 [[maybe_unused]] static __global__ __launch_bounds__(TPB) void k_reduce(const double* __restrict__ part, int nblk, int width,
                                                                         int is_max, double* __restrict__ out) {
     const int j = blockIdx.x;  // one column per block; 16 rows of a thread in flight, added in order
