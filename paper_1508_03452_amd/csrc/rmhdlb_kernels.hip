@@ -2185,77 +2185,109 @@ __global__ __launch_bounds__(TPB) void k_init_state(InPtrs in, Consts K, int til
 }
 
 // Raw state conversion to / from the FP64 interface layout (shifts added
-// back): one thread per cell, which reads and writes whole records, so every
-// line of the state is touched once (with one thread per value each f-g
-// record was visited twice, and export and import of 256x256x64 cells in FP64
-// took 1.07 and 1.66 ms; so 0.80 and 0.76).
-template <typename TS, typename TE>
+// back) by whole records of a cell, so every line of the state is touched once
+// (with one thread per value each f-g record was visited twice, and export and
+// import of 256x256x64 cells in FP64 took 1.07 and 1.66 ms; so 0.80 and 0.76).
+// Record r of a cell: the f-g records, then the Maxwell ones, then E_prev
+// (and B_prev) value by value.
+template <typename TS>
+constexpr int FG_RECORDS = quad_layout<TS>() ? 10 : Q;
+template <typename TS>
+__host__ __device__ inline int state_records(const Consts& K) {
+    return FG_RECORDS<TS> + Lay<TS>::HRECORDS + state_arrays(K) - OFF_E;
+}
+template <typename TS, typename TE, typename Put>
+__device__ __forceinline__ void export_record(const char* __restrict__ s, const Consts& K, int r, int pos, Put&& put) {
+    constexpr int NF = FG_RECORDS<TS>, NH = Lay<TS>::HRECORDS;
+    auto put_fg = [&](int i, double f, double g) {
+        put(OFF_F + i, f + fshift(K, i));
+        put(OFF_G + i, g + gshift(K, i));
+    };
+    if (r < NF) {
+        if constexpr (quad_layout<TS>()) {
+            const int i0 = r == 0 ? 0 : 2 * r - 1;
+            const vec4<double> v = ldv4<double, TS>(s, f_at<TS>(K, i0, pos));
+            put_fg(i0, v.x, v.y);
+            if (r == 0)
+                put(OFF_H + QH, v.z);
+            else
+                put_fg(i0 + 1, v.z, v.w);
+        } else {
+            const vec2<double> v = ldv2<double, TS>(s, f_at<TS>(K, r, pos));
+            put_fg(r, v.x, v.y);
+        }
+    } else if (r < NF + NH) {
+        if constexpr (quad_layout<TS>()) {
+            const int k = 2 * (r - NF);
+            const vec2<double> v = ldv2<double, TS>(s, h_at<TS>(K, k, pos));
+            put(OFF_H + k, v.x);
+            put(OFF_H + k + 1, v.y);
+        } else {
+            put(OFF_H + r - NF, ld<TS>(s, h_at<TS>(K, r - NF, pos)));
+        }
+    } else {
+        put(OFF_E + r - NF - NH, ld<TE>(s, e_at<TS>(K, r - NF - NH, pos)));
+    }
+}
+template <typename TS, typename TE, typename Get>
+__device__ __forceinline__ void import_record(char* __restrict__ d, const Consts& K, int r, int pos, Get&& get) {
+    constexpr int NF = FG_RECORDS<TS>, NH = Lay<TS>::HRECORDS;
+    auto get_f = [&](int i) { return get(OFF_F + i) - fshift(K, i); };
+    auto get_g = [&](int i) { return get(OFF_G + i) - gshift(K, i); };
+    if (r < NF) {
+        if constexpr (quad_layout<TS>()) {
+            const int i0 = r == 0 ? 0 : 2 * r - 1;
+            vec4<double> v;
+            v.x = get_f(i0);
+            v.y = get_g(i0);
+            v.z = r == 0 ? get(OFF_H + QH) : get_f(i0 + 1);
+            v.w = r == 0 ? 0.0 : get_g(i0 + 1);
+            st4<true, TS>(d, f_at<TS>(K, i0, pos), v);
+        } else {
+            st2<true, TS>(d, f_at<TS>(K, r, pos), get_f(r), get_g(r));
+        }
+    } else if (r < NF + NH) {
+        if constexpr (quad_layout<TS>()) {
+            const int k = 2 * (r - NF);
+            st2<true, TS>(d, h_at<TS>(K, k, pos), get(OFF_H + k), get(OFF_H + k + 1));
+        } else {
+            st<true, TS>(d, h_at<TS>(K, r - NF, pos), get(OFF_H + r - NF));
+        }
+    } else {
+        st<true, TE>(d, e_at<TS>(K, r - NF - NH, pos), get(OFF_E + r - NF - NH));
+    }
+}
+// One thread per cell, or (EACH) per record of a cell, record blockIdx.y: see record_threads.
+template <typename TS, typename TE, bool EACH>
 __global__ __launch_bounds__(256) void k_export(const char* __restrict__ s, double* __restrict__ d, Consts K) {
     const int64_t cell = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (cell >= K.N) return;
     const int pos = (int)K.g0 + (int)cell;
     auto put = [&](int a, double v) { __builtin_nontemporal_store(v, d + a * K.N + cell); };
-    auto put_fg = [&](int i, double f, double g) {
-        put(OFF_F + i, f + fshift(K, i));
-        put(OFF_G + i, g + gshift(K, i));
-    };
-    if constexpr (quad_layout<TS>()) {
-#pragma unroll
-        for (int q = 0; q < 10; ++q) {
-            const int i0 = q == 0 ? 0 : 2 * q - 1;
-            const vec4<double> v = ldv4<double, TS>(s, f_at<TS>(K, i0, pos));
-            put_fg(i0, v.x, v.y);
-            if (q == 0)
-                put(OFF_H + QH, v.z);
-            else
-                put_fg(i0 + 1, v.z, v.w);
-        }
-#pragma unroll
-        for (int k = 0; k < QH; k += 2) {
-            const vec2<double> v = ldv2<double, TS>(s, h_at<TS>(K, k, pos));
-            put(OFF_H + k, v.x);
-            put(OFF_H + k + 1, v.y);
-        }
+    if constexpr (EACH) {
+        export_record<TS, TE>(s, K, blockIdx.y, pos, put);
     } else {
+        constexpr int N = FG_RECORDS<TS> + Lay<TS>::HRECORDS + 3;
 #pragma unroll
-        for (int i = 0; i < Q; ++i) {
-            const vec2<double> v = ldv2<double, TS>(s, f_at<TS>(K, i, pos));
-            put_fg(i, v.x, v.y);
-        }
-#pragma unroll
-        for (int k = 0; k <= QH; ++k) put(OFF_H + k, ld<TS>(s, h_at<TS>(K, k, pos)));
+        for (int r = 0; r < N; ++r) export_record<TS, TE>(s, K, r, pos, put);
+        for (int r = N; r < state_records<TS>(K); ++r) export_record<TS, TE>(s, K, r, pos, put);
     }
-    for (int a = 0; a < state_arrays(K) - OFF_E; ++a) put(OFF_E + a, ld<TE>(s, e_at<TS>(K, a, pos)));
 }
 
-template <typename TS, typename TE>
+template <typename TS, typename TE, bool EACH>
 __global__ __launch_bounds__(256) void k_import(const double* __restrict__ s, char* __restrict__ d, Consts K) {
     const int64_t cell = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (cell >= K.N) return;
     const int pos = (int)K.g0 + (int)cell;
     auto get = [&](int a) { return __builtin_nontemporal_load(s + a * K.N + cell); };
-    auto get_f = [&](int i) { return get(OFF_F + i) - fshift(K, i); };
-    auto get_g = [&](int i) { return get(OFF_G + i) - gshift(K, i); };
-    if constexpr (quad_layout<TS>()) {
-#pragma unroll
-        for (int q = 0; q < 10; ++q) {
-            const int i0 = q == 0 ? 0 : 2 * q - 1;
-            vec4<double> v;
-            v.x = get_f(i0);
-            v.y = get_g(i0);
-            v.z = q == 0 ? get(OFF_H + QH) : get_f(i0 + 1);
-            v.w = q == 0 ? 0.0 : get_g(i0 + 1);
-            st4<true, TS>(d, f_at<TS>(K, i0, pos), v);
-        }
-#pragma unroll
-        for (int k = 0; k < QH; k += 2) st2<true, TS>(d, h_at<TS>(K, k, pos), get(OFF_H + k), get(OFF_H + k + 1));
+    if constexpr (EACH) {
+        import_record<TS, TE>(d, K, blockIdx.y, pos, get);
     } else {
+        constexpr int N = FG_RECORDS<TS> + Lay<TS>::HRECORDS + 3;
 #pragma unroll
-        for (int i = 0; i < Q; ++i) st2<true, TS>(d, f_at<TS>(K, i, pos), get_f(i), get_g(i));
-#pragma unroll
-        for (int k = 0; k <= QH; ++k) st<true, TS>(d, h_at<TS>(K, k, pos), get(OFF_H + k));
+        for (int r = 0; r < N; ++r) import_record<TS, TE>(d, K, r, pos, get);
+        for (int r = N; r < state_records<TS>(K); ++r) import_record<TS, TE>(d, K, r, pos, get);
     }
-    for (int a = 0; a < state_arrays(K) - OFF_E; ++a) st<true, TE>(d, e_at<TS>(K, a, pos), get(OFF_E + a));
 }
 
 // (features, targets) of sampled cells of the current state with the plain
@@ -2594,19 +2626,33 @@ hipError_t launch_init(const InPtrs& in, const Consts& K, double* scr, char* dst
     return hipGetLastError();
 }
 
+// Whether export and import take a thread per record: below a block of 256 cells
+// for every CU a thread per cell leaves most of the chip idle while it goes
+// through its 25 (FP32, FP16) to 47 records.  A set_state call of 4096 cells, a thread per cell / per
+// record, us: FP64 18.0 / 15.0, FP32 17.1 / 14.9, FP16 21.0 / 15.4; of 65536
+// cells 25.0 / 25.5, 21.6 / 20.9, 25.8 / 21.6; of 4194304 772 / 801, 568 / 622,
+// 528 / 713.
+static inline bool record_threads(const Consts& K) { return K.N < 256 * 256; }
+
 template <typename TS>
 hipError_t launch_export(const char* src, double* dst, const Consts& K, hipStream_t s) {
     using TE = typename StoreTypes<TS>::E;
-    const int64_t blocks = (K.N + 255) / 256;
-    hipLaunchKernelGGL((k_export<TS, TE>), dim3((unsigned)blocks), dim3(256), 0, s, src, dst, K);
+    const unsigned blocks = (unsigned)((K.N + 255) / 256);
+    if (record_threads(K))
+        hipLaunchKernelGGL((k_export<TS, TE, true>), dim3(blocks, state_records<TS>(K)), dim3(256), 0, s, src, dst, K);
+    else
+        hipLaunchKernelGGL((k_export<TS, TE, false>), dim3(blocks), dim3(256), 0, s, src, dst, K);
     return hipGetLastError();
 }
 
 template <typename TS>
 hipError_t launch_import(const double* src, char* dst, const Consts& K, hipStream_t s) {
     using TE = typename StoreTypes<TS>::E;
-    const int64_t blocks = (K.N + 255) / 256;
-    hipLaunchKernelGGL((k_import<TS, TE>), dim3((unsigned)blocks), dim3(256), 0, s, src, dst, K);
+    const unsigned blocks = (unsigned)((K.N + 255) / 256);
+    if (record_threads(K))
+        hipLaunchKernelGGL((k_import<TS, TE, true>), dim3(blocks, state_records<TS>(K)), dim3(256), 0, s, src, dst, K);
+    else
+        hipLaunchKernelGGL((k_import<TS, TE, false>), dim3(blocks), dim3(256), 0, s, src, dst, K);
     return hipGetLastError();
 }
 
