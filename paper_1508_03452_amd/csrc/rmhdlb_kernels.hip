@@ -530,9 +530,10 @@ __device__ __forceinline__ V difference(T x, T y, V one) {
 // infinite downwind neighbour p1 leaves the finite slope f - m1, a NaN two
 // cells upwind (m2) likewise.  A NaN of p1 has to reach the cell; the median
 // does not carry it, so b = p1 - f goes back to the caller, who tests it
-// (unordered, two populations per comparison).  As fast as b 0 added to f, which
-// carries a NaN but turns an infinity into one too (FP16, 256x256x512, a pass of
-// 20 steps: 75.2 ms so, 75.4 now; FP32, 256x256x64: 13.7 and 13.6).
+// (unordered, two populations per comparison).  Against b 0 added to f, which
+// carries a NaN but turns an infinity into one too, and a plain median upwind
+// (ms per step, then / now): FP16 256x256x256 1.663 / 1.664, its slab of
+// 1024x2048 0.187 / 0.189, FP32 2.342 / 2.337 and 0.257 / 0.258.
 template <typename V, typename T>
 __device__ __forceinline__ V advect(T f, T m1, T m2, T p1, V cour, V slope, V one, V& b) {
     const V a = difference<V>(f, m1, one), c = difference<V>(m1, m2, one);
