@@ -340,9 +340,10 @@ int rmhdlb_mlp_eval(const float *w, const float *X, const float *Yt, int32_t n, 
  * The fused step runs blocks of 256 threads over row groups of px x (R / px)
  * cells, px in {64, 32, 16} (128 too in batches): R = 128 with FP64
  * storage (two lanes per cell), R = 256 with FP32 and FP16 (one lane per
- * cell).  With FP64 and FP32 storage, more than one z-plane (or a driven
- * face) and zb > 1, a group of four rows or more lies in two neighbouring
- * planes, half of its rows in each, and an odd zb acts as zb + 1;
+ * cell).  With FP64 and FP32 storage and more than one z-plane (or a driven
+ * face), a group of four rows or more lies in two neighbouring planes, half
+ * of its rows in each, and an odd zb > 1 acts as zb + 1; with zb = 1 it lies
+ * in one plane if the step then has 256 blocks or more;
  * a block takes yw such groups stacked along y (a tile of R yw cells) and
  * walks zb z-planes.  With zg > 1 the planes are taken in chunks
  * of zg * zb per column, and the zg blocks of a chunk walk them interleaved

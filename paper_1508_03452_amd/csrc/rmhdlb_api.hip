@@ -977,17 +977,20 @@ BatchGeom batch_geom(const rmhdlb_batch* B) {
 // Per-instance table of the batched launches from the instances' current
 // constants and buffers.
 int batch_table(rmhdlb_batch* B) {
-    int64_t blk = 0, face = 0;
+    int64_t blk = 0, face = 0, blocks = 0;
+    const int elem = rmhd::storage_bytes(B->storage);
+    for (const rmhdlb_ctx* C : B->ctx) blocks += rmhd::plane_blocks(C->K, B->px, B->yw, elem);
     for (int i = 0; i < B->n; ++i) {
         rmhdlb_ctx* C = B->ctx[i];
         rmhd::BatchInst& I = B->host[i];
         I.K = C->K;
         for (int b = 0; b < 2; ++b) I.buf[b] = C->buf[b];
         I.faceB = C->faceB;
-        const int elem = rmhd::storage_bytes(B->storage);
-        I.zb = rmhd::walk_planes(elem, B->px, B->flat, C->tune.zb, C->K.nz);
+        const rmhd::StepWalk w = rmhd::step_walk(C->K, B->px, C->tune.zb, elem, B->flat, blocks);
+        I.zb = w.zb;
+        I.zt = w.zt;
         I.yw = B->yw;
-        rmhd::step_geometry(C->K, B->px, I.zb, 1, I.yw, elem, B->flat, I.tiles_x, I.ncol, I.nblk);
+        rmhd::step_geometry(C->K, B->px, w, 1, I.yw, elem, I.tiles_x, I.ncol, I.nblk);
         I.blk0 = blk;
         I.face0 = face;
         blk += I.nblk;

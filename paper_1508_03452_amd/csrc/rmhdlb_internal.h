@@ -101,7 +101,7 @@ __host__ __device__ inline int state_arrays(const Consts& K) { return NSTATE + (
 
 // Launch shape of the fused step: z-planes walked per block, the tile width
 // along x (64, 32 or 16 cells; a row group has cells_per_block cells, in
-// tile_planes planes), the number of blocks that walk a column's chunk of
+// StepWalk::zt planes), the number of blocks that walk a column's chunk of
 // zg * zb planes interleaved, and the row groups per block stacked along y.
 struct StepTuning {
     int zb;
@@ -116,7 +116,7 @@ struct BatchInst {
     Consts K;
     char* buf[2];
     double* faceB;
-    int tiles_x, ncol, zb, yw, nblk;
+    int tiles_x, ncol, zb, zt, yw, nblk;
     int64_t blk0;
     int64_t face0;
 };
@@ -201,28 +201,42 @@ inline bool flat_grid(const Consts& K) { return K.nz == 1 && !K.drv; }
 // Cells per row group of a fused-step block: 128 in the pair layout (FP64 storage, elem = 8 bytes, two lanes
 // per cell), 256 in the quad and double-quad layouts (FP32 and FP16 storage, one lane per cell).
 __host__ __device__ constexpr int cells_per_block(int elem) { return elem == 8 ? 128 : 256; }
-// z-planes of a fused-step tile for walks of zb planes: two in FP64 and FP32 where the rows suffice
+// Most z-planes of a fused-step tile: two in FP64 and FP32 where the rows suffice
 // (at least four), so that half of the z-neighbour planes of the stencil are
 // the tile's own: 56 instead of 68 lines of L1 per 128 cells and direction
 // (FP64 at px = 32), ms per step at 256x256x512 one / two planes FP64 9.9 / 9.36, FP32
-// 4.9 / 4.75 (wavefronts in step).  FP16 is 1 % faster with one plane.  A walk of a single plane
-// takes one too: the second would leave half of every block idle (128x128x128, FP32 with zb = 1,
-// yw = 4: 0.504 ms with two planes, 0.304 with one; FP64 32-wide 1.022 and 0.607).
+// 4.9 / 4.75 (wavefronts in step).  FP16 is 1 % faster with one plane.
 __host__ __device__ constexpr int most_planes(int elem, int px, bool flat) {
     return flat || elem == 2 || cells_per_block(elem) / px < 4 ? 1 : 2;
 }
-__host__ __device__ constexpr int tile_planes(int elem, int px, bool flat, int zb) {
-    return zb < 2 ? 1 : most_planes(elem, px, flat);
+// Blocks of a step whose tiles hold one plane and walk one.
+inline int64_t plane_blocks(const Consts& K, int px, int yw, int elem) {
+    const int py = cells_per_block(elem) / px * yw;
+    return (int64_t)((K.nx + px - 1) / px) * ((K.ny + py - 1) / py) * K.nz;
 }
-// Planes that a block walks for a tuning's zb: at most the grid's, and whole tiles.
-inline int walk_planes(int elem, int px, bool flat, int zb, int nz) {
-    zb = zb < 1 ? 1 : (zb < nz ? zb : nz);
-    return tile_planes(elem, px, flat, zb) == 2 ? zb + (zb & 1) : zb;
+// What a tuning's zb becomes: the planes of a tile and those that a block
+// walks, at most the grid's and whole tiles (an odd number is rounded up).
+// A walk of a single plane takes tiles of one where the step then has a block
+// for every CU (blocks: plane_blocks, or their sum in a batch): in tiles of two half of
+// every block finds no rows (64x64x32 cells, 512 blocks of FP32 64-wide, 22.5 us per step with one
+// plane, 26.5 with two; FP64 32-wide 1024 blocks 40.3 and 51.1).  With fewer
+// blocks the half-filled ones spread the same wavefronts over twice as many CUs (64x32x8, 64 blocks,
+// FP32 12.7 and 11.7; FP64 128 blocks 13.7 and 12.4); at 256 the two are equal within 2 %.
+constexpr int FULL_CHIP = 256;  // compute units
+struct StepWalk {
+    int zb, zt;
+};
+inline StepWalk step_walk(const Consts& K, int px, int zb, int elem, bool flat, int64_t blocks) {
+    StepWalk w;
+    w.zb = zb < 1 ? 1 : (zb < K.nz ? zb : K.nz);
+    w.zt = w.zb == 1 && blocks >= FULL_CHIP ? 1 : most_planes(elem, px, flat);
+    if (w.zt == 2 && w.zb > 1) w.zb += w.zb & 1;
+    return w;
 }
-// Launch geometry of the fused step for a tile width px, zb planes per block
+// Launch geometry of the fused step for a tile width px, w.zb planes per block
 // and zg blocks per column and chunk of zg * zb planes: tiles along x,
 // columns, blocks.
-void step_geometry(const Consts& K, int px, int zb, int zg, int yw, int elem, bool flat, int& tiles_x, int& ncol,
+void step_geometry(const Consts& K, int px, const StepWalk& w, int zg, int yw, int elem, int& tiles_x, int& ncol,
                    int& nblk);
 inline bool quad_storage(int32_t storage) { return storage != RMHDLB_STORE_F64; }
 inline int storage_bytes(int32_t storage) {

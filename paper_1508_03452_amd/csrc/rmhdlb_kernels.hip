@@ -1495,7 +1495,7 @@ __device__ __forceinline__ T* again(T* p) {
 
 // One block owns a row group of 128 (FP64, two lanes per cell) or 256 cells:
 // ROWS = 128 / PXT or 256 / PXT rows of PXT cells (a power of two), PYT of them along y in each
-// of ZT neighbouring planes (tile_planes), yw such groups stacked along y.  It
+// of ZT neighbouring planes (step_walk), yw such groups stacked along y.  It
 // walks zb z-planes, the yw groups of its planes one after another.  A chunk
 // of zg * zb planes is shared by zg blocks per column, which take its planes
 // (ZT at a time) in turn, so that the zg blocks of a column run at
@@ -1511,13 +1511,14 @@ __device__ __forceinline__ T* again(T* p) {
 template <bool NT, typename TS, typename TE, typename V, int GM, int PXT, int VR, bool FLAT, bool SYNC>
 __device__ __forceinline__ void fused_block(const char* __restrict__ sd, char* __restrict__ dd,
                                             const double* __restrict__ faceB, const GuessTables* __restrict__ gt,
-                                            ConstsPtr kp, int tiles_x, int ncol, int zb, int zg, int yw, int b) {
+                                            ConstsPtr kp, int tiles_x, int ncol, int zb, int zt, int zg, int yw, int b) {
     const Consts& K = *(const Consts*)kp;
     // pair layout (FP64): 128 cells per row group, two lanes each; quad and double-quad layouts (FP32,
     // FP16): 256 cells, one lane each
     constexpr bool ONE = quad_layout<TS>();
     constexpr int ROWS = cells_per_block(sizeof(TS)) / PXT, MOST = most_planes(sizeof(TS), PXT, FLAT);
-    const int ZT = MOST == 1 ? 1 : (zb < 2 ? 1 : MOST), PYT = ZT == 1 ? ROWS : ROWS / MOST;  // as tile_planes
+    constexpr int LG_ROWS = __builtin_ctz(ROWS);
+    const int ZT = MOST == 1 ? 1 : zt, lg = LG_ROWS + 1 - ZT, PYT = 1 << lg;  // ZT is 1 or 2
     const int per = ncol * zg, zc = b / per, r = b % per;
     const int col = r / zg, zoff = r % zg;
     const int tx = col % tiles_x, ty = col / tiles_x;
@@ -1527,7 +1528,7 @@ __device__ __forceinline__ void fused_block(const char* __restrict__ sd, char* _
     const int c = ONE ? (int)threadIdx.x : (int)(threadIdx.x >> 6) * 32 + (lane & 31), h = ONE ? 0 : lane >> 5;
     const int xr = tx * PXT + (c % PXT);
     int x = xr;
-    const int ybase = ty * PYT * yw + (c / PXT & (PYT - 1));
+    const int ybase = (ty * yw << lg) + (c / PXT & (PYT - 1));
     // plane of the tile this wavefront works on (its rows share it)
     const int zl = MOST == 1 ? 0 : __builtin_amdgcn_readfirstlane(c / PXT >= PYT);
     // with the force every lane stays (the wavefront's largest |beta| is
@@ -1536,7 +1537,7 @@ __device__ __forceinline__ void fused_block(const char* __restrict__ sd, char* _
     // row groups of this lane that lie inside the grid (the later groups are further along y)
     int ng = yw;
     if (ybase >= K.ny) ng = 0;
-    else if (ybase + (yw - 1) * PYT >= K.ny) ng = (K.ny - 1 - ybase) / PYT + 1;
+    else if (ybase + (yw - 1) * PYT >= K.ny) ng = ((K.ny - 1 - ybase) >> lg) + 1;
     if constexpr (!all_lanes) {
         if (x >= K.nx || ng == 0) return;  // both lanes of a pair leave together
     } else {
@@ -1586,7 +1587,7 @@ template <bool NT, typename TS, typename TE, typename V, int GM, int PXT, int VR
 __global__ __launch_bounds__(PTPB, FUSED_WAVES) void k_fused_step(const char* __restrict__ sd,
                                                         char* __restrict__ dd, const double* __restrict__ faceB,
                                                         const GuessTables* __restrict__ gt, Consts K,
-                                                        int tiles_x, int ncol, int zb, int zg, int yw, int nblk) {
+                                                        int tiles_x, int ncol, int zb, int zt, int zg, int yw, int nblk) {
     const int b = tile_of_block(nblk);
     if (b >= nblk) return;  // uniform over the block
     // With the guess enabled every step launches the network kernel and the monitor kernel (its own
@@ -1600,7 +1601,7 @@ __global__ __launch_bounds__(PTPB, FUSED_WAVES) void k_fused_step(const char* __
     }
     const ConstsPtr kp = (ConstsPtr)((const __attribute__((address_space(4))) char*)__builtin_amdgcn_kernarg_segment_ptr() +
                                      STEP_CONSTS_AT);
-    fused_block<NT, TS, TE, V, GM, PXT, VR, FLAT, in_step<TS, FLAT>()>(sd, dd, faceB, gt, kp, tiles_x, ncol, zb, zg, yw, b);
+    fused_block<NT, TS, TE, V, GM, PXT, VR, FLAT, in_step<TS, FLAT>()>(sd, dd, faceB, gt, kp, tiles_x, ncol, zb, zt, zg, yw, b);
 }
 
 // Index of the instance whose range [first[i], first[i + 1]) holds v (first
@@ -1632,7 +1633,7 @@ __global__ __launch_bounds__(PTPB, WV) void k_fused_batch(const BatchInst* __res
     const int i = find_instance(ninst, b, [&](int j) { return I[j].blk0; });
     const BatchInst& B = I[i];
     fused_block<NT, TS, TE, V, GUESS_NONE, PXT, 0, FLAT, in_step<TS, FLAT>()>(
-        B.buf[parity], B.buf[1 - parity], B.faceB, nullptr, (ConstsPtr)(uintptr_t)&B.K, B.tiles_x, B.ncol, B.zb, 1, B.yw, (int)(b - B.blk0));
+        B.buf[parity], B.buf[1 - parity], B.faceB, nullptr, (ConstsPtr)(uintptr_t)&B.K, B.tiles_x, B.ncol, B.zb, B.zt, 1, B.yw, (int)(b - B.blk0));
 }
 
 // B of Eq. Cal_B at a cell from the streamed h (population order, FP64).
@@ -1748,7 +1749,7 @@ __global__ __launch_bounds__(PTPB, WV) void k_fused_batch_persistent(const Batch
                 const int i = find_instance(ninst, b, [&](int jj) { return I[jj].blk0; });
                 const BatchInst& B = I[i];
                 fused_block<NT, TS, TE, V, GUESS_NONE, PXT, 0, FLAT, false>(
-                    B.buf[parity], B.buf[1 - parity], B.faceB, nullptr, (ConstsPtr)(uintptr_t)&B.K, B.tiles_x, B.ncol, B.zb, 1, B.yw,
+                    B.buf[parity], B.buf[1 - parity], B.faceB, nullptr, (ConstsPtr)(uintptr_t)&B.K, B.tiles_x, B.ncol, B.zb, B.zt, 1, B.yw,
                     (int)(b - B.blk0));
             }
             if (threadIdx.x == 0) tile_sh = nj;
@@ -2388,12 +2389,12 @@ hipError_t launch_face_b(const char* src, const Consts& K, double* faceB, hipStr
 }
 
 #if RMHDLB_FORM == 64  // what depends on no storage form is built once
-void step_geometry(const Consts& K, int px, int zb, int zg, int yw, int elem, bool flat, int& tiles_x, int& ncol,
+void step_geometry(const Consts& K, int px, const StepWalk& w, int zg, int yw, int elem, int& tiles_x, int& ncol,
                    int& nblk) {
-    const int py = cells_per_block(elem) / px / tile_planes(elem, px, flat, zb) * yw;
+    const int py = cells_per_block(elem) / px / w.zt * yw;
     tiles_x = (K.nx + px - 1) / px;
     ncol = tiles_x * ((K.ny + py - 1) / py);
-    nblk = ncol * zg * ((K.nz + zg * zb - 1) / (zg * zb));
+    nblk = ncol * zg * ((K.nz + zg * w.zb - 1) / (zg * w.zb));
 }
 #endif
 
@@ -2402,15 +2403,15 @@ static void launch_fused(const char* sd, char* dd, double* faceB, const GuessTab
     using TE = typename StoreTypes<TS>::E;
     using V = typename StoreTypes<TS>::V;
     int tx, ncol, nblk;
-    zb = walk_planes(sizeof(TS), PXT, flat_grid(K), zb, K.nz);
-    step_geometry(K, PXT, zb, zg, yw, sizeof(TS), flat_grid(K), tx, ncol, nblk);
+    const StepWalk w = step_walk(K, PXT, zb, sizeof(TS), flat_grid(K), plane_blocks(K, PXT, yw, sizeof(TS)));
+    step_geometry(K, PXT, w, zg, yw, sizeof(TS), tx, ncol, nblk);
     const int grid = ((nblk + 7) / 8) * 8;
     if (flat_grid(K))
         hipLaunchKernelGGL((k_fused_step<true, TS, TE, V, GM, PXT, VR, true>), dim3(grid), dim3(PTPB), 0, s, sd, dd,
-                           (const double*)faceB, gt, K, tx, ncol, zb, zg, yw, nblk);
+                           (const double*)faceB, gt, K, tx, ncol, w.zb, w.zt, zg, yw, nblk);
     else
         hipLaunchKernelGGL((k_fused_step<true, TS, TE, V, GM, PXT, VR, false>), dim3(grid), dim3(PTPB), 0, s, sd, dd,
-                           (const double*)faceB, gt, K, tx, ncol, zb, zg, yw, nblk);
+                           (const double*)faceB, gt, K, tx, ncol, w.zb, w.zt, zg, yw, nblk);
 }
 
 template <typename TS>
@@ -2434,8 +2435,8 @@ hipError_t launch_step(const char* src, char* dst, const Consts& K, const StepTu
         else
             launch_fused<TS, GUESS_NONE, 64, 4>(src, dst, faceB, gt, K, zb, 1, 1, s);
         int tx, ncol, nblk;
-        step_geometry(K, 64, walk_planes(sizeof(TS), 64, flat_grid(K), zb, K.nz), 1, 1, sizeof(TS), flat_grid(K), tx,
-                      ncol, nblk);
+        const StepWalk w = step_walk(K, 64, zb, sizeof(TS), flat_grid(K), plane_blocks(K, 64, 1, sizeof(TS)));
+        step_geometry(K, 64, w, 1, 1, sizeof(TS), tx, ncol, nblk);
         hipLaunchKernelGGL(k_vmax_reduce, dim3(1), dim3(TPB), 0, s, K.vmax_part, (int64_t)nblk * (PTPB / 64),
                            const_cast<double*>(K.vmax_prev));
     } else if (vr) {  // the alternative readings: 64-wide tiles, no guess

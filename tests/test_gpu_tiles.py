@@ -183,3 +183,30 @@ def test_batch_tuner_times_each_kernel_family():
     assert not timed([slab(), slab()])
     assert timed([driven(), driven()])
     assert timed([slab(), driven()])       # a slab beside a driven one takes the general kernels as well
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32"])
+@pytest.mark.parametrize("nz", [7, 8, 9])
+def test_one_plane_walks_on_both_sides_of_the_line(storage, nz):
+    """Around 256 blocks a walk of one plane takes tiles of one plane or of two: the state is the same on both sides
+    (64-wide FP32 tiles of 64 x 4 cells: 32 per plane of 64 x 128; 32-wide FP64 ones likewise), in a batch as alone."""
+    torch = _torch_cuda()
+    w = _box((64, 128, nz))
+    px = 64 if storage == "f32" else 32
+    want = run_gpu(w, 0, storage=storage)
+    want.set_tuning(64, 2, 1, 1)
+    want.step(3)
+    want = _state(want)
+    s = run_gpu(w, 0, storage=storage)
+    s.set_tuning(px, 1)
+    s.step(3)
+    assert np.array_equal(want, _state(s))
+    b = _batch([w, w], storage, torch.cuda.Stream())
+    b.set_tuning(px, 1, 2)
+    for i in b.instances:
+        i.set_tuning(px, 1)
+    b.step(3)
+    torch.cuda.synchronize()
+    for i in b.instances:
+        assert np.array_equal(want, _state(i))
+    b.close()
