@@ -48,28 +48,28 @@ KERNEL_SOURCES = ("paper_1508_03452_amd/csrc/rmhdlb_kernels.hip", "paper_1508_03
 # shape the autotuner picks, and a changed kernel or an unmeasured shape
 # reports null.
 MEASURED_TRAFFIC = {
-    ("flare", "f64", "1164d790b77d", "32,8,2"): 54.03,  # profiles/fused_step_f64_flare256x256x512.md
-    ("flare", "f64", "1164d790b77d", "32,8,4"): 54.05,  # profiles/fused_step_f64_flare256x256x512.md
-    ("flare", "f64", "1164d790b77d", "32,8,8"): 52.99,  # profiles/fused_step_f64_flare256x256x512.md
-    ("flare", "f64", "1164d790b77d", "64,4,4"): 53.16,  # profiles/fused_step_f64_flare256x256x512.md
-    ("flare", "f64", "1164d790b77d", "64,8,2"): 60.74,  # profiles/fused_step_f64_flare256x256x512.md
-    ("flare", "f64", "1164d790b77d", "64,16,4"): 48.41,  # profiles/fused_step_f64_flare256x256x512.md
-    ("flare", "f32", "1164d790b77d", "32,8,2"): 25.3,  # profiles/fused_step_f32_flare256x256x512.md
-    ("flare", "f32", "1164d790b77d", "32,8,4"): 24.74,  # profiles/fused_step_f32_flare256x256x512.md
-    ("flare", "f32", "1164d790b77d", "32,8,8"): 24.47,  # profiles/fused_step_f32_flare256x256x512.md
-    ("flare", "f32", "1164d790b77d", "64,4,4"): 23.00,  # profiles/fused_step_f32_flare256x256x512.md
-    ("flare", "f32", "1164d790b77d", "64,8,2"): 24.4,  # profiles/fused_step_f32_flare256x256x512.md
-    ("flare", "f32", "1164d790b77d", "64,16,4"): 25.82,  # profiles/fused_step_f32_flare256x256x512.md
-    ("flare", "f32", "1164d790b77d", "64,32,2"): 24.55,  # profiles/fused_step_f32_flare256x256x512.md
-    ("flare", "f32", "1164d790b77d", "64,32,4"): 24.06,  # profiles/fused_step_f32_flare256x256x512.md
-    ("flare", "f16", "1164d790b77d", "32,8,4"): 12.92,  # profiles/fused_step_f16_flare256x256x512.md
-    ("flare", "f16", "1164d790b77d", "32,8,8"): 12.82,  # profiles/fused_step_f16_flare256x256x512.md
-    ("flare", "f16", "1164d790b77d", "64,16,4"): 13.03,  # profiles/fused_step_f16_flare256x256x512.md
-    ("flare", "f16", "1164d790b77d", "64,32,4"): 12.99,  # profiles/fused_step_f16_flare256x256x512.md
-    ("flare", "f16", "1164d790b77d", "64,64,4"): 14.92,  # profiles/fused_step_f16_flare256x256x512.md
-    ("flare", "f16+guess", "1164d790b77d", "64,16,4"): 12.97,  # profiles/fused_step_f16g_flare256x256x512.md
-    ("flare", "f16+guess", "1164d790b77d", "64,32,4"): 13.02,  # profiles/fused_step_f16g_flare256x256x512.md
-    ("flare", "f16+guess", "1164d790b77d", "64,64,4"): 14.91,  # profiles/fused_step_f16g_flare256x256x512.md
+    ("flare", "f64", "1ea308e9cc24", "32,8,2"): 54.04,  # profiles/fused_step_f64_flare256x256x512.md
+    ("flare", "f64", "1ea308e9cc24", "32,8,4"): 54.01,  # profiles/fused_step_f64_flare256x256x512.md
+    ("flare", "f64", "1ea308e9cc24", "32,8,8"): 53.07,  # profiles/fused_step_f64_flare256x256x512.md
+    ("flare", "f64", "1ea308e9cc24", "64,4,4"): 53.16,  # profiles/fused_step_f64_flare256x256x512.md
+    ("flare", "f64", "1ea308e9cc24", "64,8,2"): 60.66,  # profiles/fused_step_f64_flare256x256x512.md
+    ("flare", "f64", "1ea308e9cc24", "64,16,4"): 48.42,  # profiles/fused_step_f64_flare256x256x512.md
+    ("flare", "f32", "1ea308e9cc24", "32,8,2"): 25.3,  # profiles/fused_step_f32_flare256x256x512.md
+    ("flare", "f32", "1ea308e9cc24", "32,8,4"): 24.73,  # profiles/fused_step_f32_flare256x256x512.md
+    ("flare", "f32", "1ea308e9cc24", "32,8,8"): 24.47,  # profiles/fused_step_f32_flare256x256x512.md
+    ("flare", "f32", "1ea308e9cc24", "64,4,4"): 23.00,  # profiles/fused_step_f32_flare256x256x512.md
+    ("flare", "f32", "1ea308e9cc24", "64,8,2"): 24.41,  # profiles/fused_step_f32_flare256x256x512.md
+    ("flare", "f32", "1ea308e9cc24", "64,16,4"): 25.78,  # profiles/fused_step_f32_flare256x256x512.md
+    ("flare", "f32", "1ea308e9cc24", "64,32,2"): 24.39,  # profiles/fused_step_f32_flare256x256x512.md
+    ("flare", "f32", "1ea308e9cc24", "64,32,4"): 24.06,  # profiles/fused_step_f32_flare256x256x512.md
+    ("flare", "f16", "1ea308e9cc24", "32,8,4"): 12.94,  # profiles/fused_step_f16_flare256x256x512.md
+    ("flare", "f16", "1ea308e9cc24", "32,8,8"): 12.83,  # profiles/fused_step_f16_flare256x256x512.md
+    ("flare", "f16", "1ea308e9cc24", "64,16,4"): 13.03,  # profiles/fused_step_f16_flare256x256x512.md
+    ("flare", "f16", "1ea308e9cc24", "64,32,4"): 13.03,  # profiles/fused_step_f16_flare256x256x512.md
+    ("flare", "f16", "1ea308e9cc24", "64,64,4"): 14.83,  # profiles/fused_step_f16_flare256x256x512.md
+    ("flare", "f16+guess", "1ea308e9cc24", "64,16,4"): 12.95,  # profiles/fused_step_f16g_flare256x256x512.md
+    ("flare", "f16+guess", "1ea308e9cc24", "64,32,4"): 12.99,  # profiles/fused_step_f16g_flare256x256x512.md
+    ("flare", "f16+guess", "1ea308e9cc24", "64,64,4"): 14.62,  # profiles/fused_step_f16g_flare256x256x512.md
 }
 
 
