@@ -210,3 +210,24 @@ def test_one_plane_walks_on_both_sides_of_the_line(storage, nz):
     for i in b.instances:
         assert np.array_equal(want, _state(i))
     b.close()
+
+
+@pytest.mark.parametrize("storage", STORAGES)
+def test_persistent_batch_of_boxes_matches_graph_replays(storage):
+    """Boxes in the persistent launch, whose wavefronts are not kept in step, against graph replays: the tile's planes
+    come from the batch's table there as well.  The device is idle before the cooperative launch."""
+    torch = _torch_cuda()
+    print(f"[tiles] persistent boxes {storage}", flush=True)
+    ws = [W.random_state(shape=sh, seed=8, vmax=0.1, Bmag=0.2, Emag=0.02, sigma=3.0)
+          for sh in ((70, 13, 9), (33, 20, 6), (64, 48, 31))]
+    states = []
+    for persistent in (False, True):
+        b = _batch(ws, storage, torch.cuda.Stream())
+        b.set_persistent(persistent)
+        torch.cuda.synchronize()
+        b.step(5)
+        torch.cuda.synchronize()
+        states.append([_state(s) for s in b.instances])
+        b.close()
+    for g, p in zip(*states):
+        assert np.array_equal(g, p)
